@@ -60,8 +60,9 @@ KERNEL_SOURCES = {
     False: {"kia_fwd": ["kia_fwd.hip", "kia_device.hpp", "kia_kernels.hpp"],
             "kia_bwd_main": ["kia_bwd.hip", "kia_device.hpp", "kia_kernels.hpp"],
             "kia_bwd_dq": ["kia_bwd.hip", "kia_device.hpp", "kia_kernels.hpp"]},
-    True: {n: ["kia_bf16.hip", "kia_device.hpp", "kia_kernels.hpp"]
-           for n in ("kia_fwd", "kia_bwd_main", "kia_bwd_dq")},
+    True: {n: ["kia_bf16.hip", f, "kia_device.hpp", "kia_kernels.hpp"]
+           for n, f in (("kia_fwd", "kia_fwd.hip"), ("kia_bwd_main", "kia_bwd.hip"),
+                        ("kia_bwd_dq", "kia_bwd.hip"))},
 }
 
 

@@ -174,51 +174,55 @@ int launched() {
   return hipGetLastError() == hipSuccess ? KIA_OK : KIA_ERR_HIP;
 }
 
-template <int D, int CALIB, int KP>
-void launch_fwd_k(const FwdArgs &a, hipStream_t s) {
-  const int bm = KP == 2 ? 64 : 32;  // two row groups of 32 rows, or one
-  const dim3 grid(a.BH * ((a.T + bm - 1) / bm)), block(KP == 8 ? 512 : 256);
-  if (a.recon == KIA_RECON_SOFTMAX)
-    hipLaunchKernelGGL((fwd_kernel<D, CAL_FWM, REC_SOFTMAX, false, KP>), grid, block, 0, s, a);
-  else if (a.recon == KIA_RECON_BF16EXP)
-    hipLaunchKernelGGL((fwd_kernel<D, CAL_FWM, REC_BF16EXP, false, KP>), grid, block, 0, s, a);
-  else if (a.recon == KIA_RECON_FP8EXP)
-    hipLaunchKernelGGL((fwd_kernel<D, CAL_FWM, REC_FP8EXP, false, KP>), grid, block, 0, s, a);
-  else if (a.recon == KIA_RECON_LERP)
-    hipLaunchKernelGGL((fwd_kernel<D, CALIB, REC_LERP, false, KP>), grid, block, 0, s, a);
-  else if (a.st.OL)
-    hipLaunchKernelGGL((fwd_kernel<D, CALIB, REC_NEAREST, true, KP>), grid, block, 0, s, a);
-  else
-    hipLaunchKernelGGL((fwd_kernel<D, CALIB, REC_NEAREST, false, KP>), grid, block, 0, s, a);
-}
-
-// Two row groups x two key halves, unless the 64-row grid leaves CUs short
-// of two workgroups: then one row group x four key quarters (twice the
-// workgroups, half the keys per wave on the longest rows), or, with fewer
-// 64-row blocks than CUs, one row group x eight key parts (8-wave
-// workgroups, a quarter of the keys per wave).
-template <int D, int CALIB>
-void launch_fwd_c(const FwdArgs &a, hipStream_t s) {
-  if constexpr (D <= 64) {
-    const long blocks = (long)a.BH * ((a.T + 63) / 64);
-    if (g_grid == KIA_GRID_AUTO && blocks < device_cus()) {
-      launch_fwd_k<D, CALIB, 8>(a, s);
-      return;
-    }
-    if (g_grid == KIA_GRID_SPLIT || (g_grid == KIA_GRID_AUTO && blocks < 2L * device_cus())) {
-      launch_fwd_k<D, CALIB, 4>(a, s);
+template <typename TI, int D, int CALIB, int RG, int KP>
+void launch_fwd_k(const FwdArgsT<TI> &a, hipStream_t s) {
+  const dim3 grid(a.BH * ((a.T + 32 * RG - 1) / (32 * RG))), block(64 * RG * KP);
+  if constexpr (sizeof(TI) == 4) {
+    if (is_exp_rec(a.recon)) {
+      if (a.recon == KIA_RECON_SOFTMAX)
+        hipLaunchKernelGGL((fwd_kernel<TI, D, CAL_FWM, REC_SOFTMAX, false, RG, KP>), grid, block, 0, s, a);
+      else if (a.recon == KIA_RECON_BF16EXP)
+        hipLaunchKernelGGL((fwd_kernel<TI, D, CAL_FWM, REC_BF16EXP, false, RG, KP>), grid, block, 0, s, a);
+      else
+        hipLaunchKernelGGL((fwd_kernel<TI, D, CAL_FWM, REC_FP8EXP, false, RG, KP>), grid, block, 0, s, a);
       return;
     }
   }
-  launch_fwd_k<D, CALIB, 2>(a, s);
+  if (a.recon == KIA_RECON_LERP)
+    hipLaunchKernelGGL((fwd_kernel<TI, D, CALIB, REC_LERP, false, RG, KP>), grid, block, 0, s, a);
+  else if (a.st.OL)
+    hipLaunchKernelGGL((fwd_kernel<TI, D, CALIB, REC_NEAREST, true, RG, KP>), grid, block, 0, s, a);
+  else
+    hipLaunchKernelGGL((fwd_kernel<TI, D, CALIB, REC_NEAREST, false, RG, KP>), grid, block, 0, s, a);
 }
 
-template <int D>
-void launch_fwd(const FwdArgs &a, hipStream_t s) {
+// Launch shape by the number of 128-row blocks. Above two per CU, 128 rows
+// share each staged tile; below, row groups are given up for key parts, so
+// that the longest causal row's keys are spread over two or four waves and
+// there are enough workgroups. Measured at d = 64, T = 1024, FWM with Nearest
+// and Prob-STE, fp32 (us): 192 blocks 126 / 94 / 72 (4 x 1 / 2 x 2 / 1 x 4),
+// 320 blocks 134 / 98 / 101, 512 blocks 145 / 147 / 147, 768 blocks
+// 175 / 195 / 213; bf16 192 blocks 66 / 42 / 33, 512 blocks 69 / 58 / 64. With
+// fp32 inputs at d = 64 a 1 x 8 workgroup still gains on the smallest grids
+// (96 blocks: 49 against 53).
+template <typename TI, int D, int CALIB>
+void launch_fwd_c(const FwdArgsT<TI> &a, hipStream_t s) {
+  const long blocks = (long)a.BH * ((a.T + 127) / 128), cus = device_cus();
+  const bool split = g_grid == KIA_GRID_SPLIT, autog = g_grid == KIA_GRID_AUTO;
+  if constexpr (D == 64 && sizeof(TI) == 4) {
+    if (split || (autog && blocks < cus / 2)) return launch_fwd_k<TI, D, CALIB, 1, 8>(a, s);
+  }
+  if (split || (autog && blocks <= cus)) return launch_fwd_k<TI, D, CALIB, 1, 4>(a, s);
+  if (autog && blocks <= 2 * cus) return launch_fwd_k<TI, D, CALIB, 2, 2>(a, s);
+  launch_fwd_k<TI, D, CALIB, 4, 1>(a, s);
+}
+
+template <typename TI, int D>
+void launch_fwd(const FwdArgsT<TI> &a, hipStream_t s) {
   timed("kia_fwd", s, [&] {
-    if (a.calib == KIA_CALIB_MINMAX) launch_fwd_c<D, CAL_MINMAX>(a, s);
-    else if (a.calib == KIA_CALIB_RESOLVED) launch_fwd_c<D, CAL_RESOLVED>(a, s);
-    else launch_fwd_c<D, CAL_FWM>(a, s);
+    if (a.calib == KIA_CALIB_MINMAX) launch_fwd_c<TI, D, CAL_MINMAX>(a, s);
+    else if (a.calib == KIA_CALIB_RESOLVED) launch_fwd_c<TI, D, CAL_RESOLVED>(a, s);
+    else launch_fwd_c<TI, D, CAL_FWM>(a, s);
   });
 }
 
@@ -250,26 +254,6 @@ void launch_codes(const CodesArgsT<TI> &a, int recon, hipStream_t s) {
 }
 
 // ---- bf16 inputs ----------------------------------------------------------
-template <int D, int CALIB>
-void launch_fwd16_c(const FwdArgs16 &a, hipStream_t s) {
-  const dim3 grid(a.BH * ((a.T + 63) / 64)), block(256);
-  if (a.recon == KIA_RECON_LERP)
-    hipLaunchKernelGGL((fwd16_kernel<D, CALIB, REC_LERP, false>), grid, block, 0, s, a);
-  else if (a.st.OL)
-    hipLaunchKernelGGL((fwd16_kernel<D, CALIB, REC_NEAREST, true>), grid, block, 0, s, a);
-  else
-    hipLaunchKernelGGL((fwd16_kernel<D, CALIB, REC_NEAREST, false>), grid, block, 0, s, a);
-}
-
-template <int D>
-void launch_fwd16(const FwdArgs16 &a, hipStream_t s) {
-  timed("kia_fwd", s, [&] {
-    if (a.calib == KIA_CALIB_MINMAX) launch_fwd16_c<D, CAL_MINMAX>(a, s);
-    else if (a.calib == KIA_CALIB_RESOLVED) launch_fwd16_c<D, CAL_RESOLVED>(a, s);
-    else launch_fwd16_c<D, CAL_FWM>(a, s);
-  });
-}
-
 template <int D, int CALIB, int RECON>
 void launch_main16(const BwdArgs16 &a, int nkb, hipStream_t s) {
   // the query-range split as its own instantiation: the unsplit kernel keeps
@@ -444,20 +428,19 @@ int attn_fwd(const TI *q, const TI *k, const TI *v, float *o, void *stats, int B
   if (is_exp_rec(recon)) { a.calib = CAL_FWM; a.tau = 0.f; a.K = 1; }  // maximum only
   a.scale = softmax_scale(d);
   hipStream_t s = static_cast<hipStream_t>(stream);
-  if constexpr (sizeof(TI) == 2) {
-    switch (d) {
-      case 16: launch_fwd16<16>(a, s); break;
-      case 32: launch_fwd16<32>(a, s); break;
-      case 64: launch_fwd16<64>(a, s); break;
-      default: launch_fwd16<128>(a, s); break;
-    }
-  } else {
-    switch (d) {
-      case 16: launch_fwd<16>(a, s); break;
-      case 32: launch_fwd<32>(a, s); break;
-      case 64: launch_fwd<64>(a, s); break;
-      default: launch_fwd<128>(a, s); break;
-    }
+  if (a.calib != CAL_MINMAX && !is_exp_rec(recon)) {
+    const double h = (double)a.tau / K, LOG2E = 1.4426950408889634074;
+    a.gc = K / (double)a.tau;
+    a.ga = (float)(a.gc * (double)a.scale);
+    a.ghl = (float)(h * LOG2E);
+    a.gb1l = (float)((h - (double)a.tau) * LOG2E);
+    a.gemh = (float)exp(-h);
+  }
+  switch (d) {
+    case 16: launch_fwd<TI, 16>(a, s); break;
+    case 32: launch_fwd<TI, 32>(a, s); break;
+    case 64: launch_fwd<TI, 64>(a, s); break;
+    default: launch_fwd<TI, 128>(a, s); break;
   }
   return launched();
 }

@@ -112,301 +112,6 @@ template <int D, int ROWS, int NT> struct Blocks16 {
 };
 
 // ---------------------------------------------------------------------------
-// Forward: one workgroup = 4 waves = 64 query rows = 2 row groups x 2 key
-// halves, as fwd_kernel; K chunks row-major (score sub-tile A operand), V
-// chunks transposed (P V A operand).
-template <int D, int CALIB, int RECON, bool OL>
-__global__ __launch_bounds__(256, 2) void fwd16_kernel(FwdArgs16 a) {
-  constexpr int NC = Dims16<D>::NC, RS = Dims16<D>::RS;
-  // MinMax and the resolved grid need the row minimum (resolved: for the
-  // rounding margin of its far keys only)
-  constexpr bool TRACKMIN = CALIB != CAL_FWM, NEAREST = RECON == REC_NEAREST;
-  constexpr int NRED = NC * 16 * (OL ? 2 : 1) + 2;
-  constexpr int KBUF = H16_CH * RS;  // bf16 per K chunk
-  constexpr int VBUF = D * H16_TS;   // bf16 per transposed V chunk
-  constexpr int STAGE = 2 * KBUF + 2 * VBUF;
-  constexpr int RED = 2 * 64 * NRED * 2;  // reduction floats, in bf16 units
-  constexpr int SM = STAGE > RED ? STAGE : RED;
-  __shared__ __attribute__((aligned(16))) uint16_t smem[SM];
-  __shared__ int Xc[2][2][6][32];
-
-  const int tid = threadIdx.x;
-  const int lane = tid & 63, wave = tid >> 6, half = lane >> 5, l32 = lane & 31;
-  const int pr = wave & 1, kh = wave >> 1;
-  const int T = a.T;
-  const int nqb = (T + 63) / 64;
-  const int bh = blockIdx.x % a.BH;
-  const int qb = nqb - 1 - (int)(blockIdx.x / a.BH);
-  const int i0 = qb * 64;
-  const int iw = i0 + pr * 32;
-  const int row = iw + l32;
-  const size_t slice = (size_t)bh * T * D;
-  const uint16_t *qs = a.q + slice, *ks = a.k + slice, *vs = a.v + slice;
-  const float Kf = (float)a.K;
-  const int jlim = a.causal ? min(row, T - 1) : T - 1;
-  const int wlim = iw >= T ? -1 : (a.causal ? min(iw + 31, T - 1) : T - 1);
-  // every key j <= wmin is valid for every row of the wave
-  const int wmin = a.causal ? min(iw, T - 1) : T - 1;
-  const int kend = a.causal ? min(T, i0 + 64) : T;
-  const int nstep = (kend + H16_CH - 1) / H16_CH;
-  const int npw = wlim < kh * 32 ? 0 : min(nstep, (wlim - kh * 32) / H16_CH + 1);
-  float *Ut = a.st.U + ds_tile(bh, iw / 32, kh, (T + 31) / 32, a.causal) * 1024;
-
-  bf16x8 qop[D / 16];
-  load_rows16<D>(qs, row < T ? row : T - 1, T, half, qop);
-
-  // ---------------- pass 1: scores, extrema, first index, tie counts -----
-  float Mx = -INFINITY, Mn = INFINITY;
-  int ax = 0x7fffffff, an = 0x7fffffff, cx = 0, cn = 0;
-  {
-    Blocks16<D, H16_CH, 256> fk;
-    fk.fetch(ks, 0, T, tid);
-    fk.template stash_rows<RS>(smem, tid);
-    lds_barrier();
-    for (int p = 0; p < nstep; ++p) {
-      fk.fetch(ks, min(p + 1, nstep - 1) * H16_CH, T, tid);
-      if (p < npw) {
-        const int js = p * H16_CH + kh * 32;
-        const uint16_t *kr = smem + (p & 1) * KBUF + (kh * 32 + l32) * RS + 8 * half;
-        bf16x8 kop[D / 16];
-#pragma unroll
-        for (int s = 0; s < D / 16; ++s) kop[s] = as_bf16x8(*reinterpret_cast<const uint4 *>(kr + 16 * s));
-        const f32x16 acc = score_tile16<D>(kop, qop);
-        {
-          float sv[16];
-#pragma unroll
-          for (int r = 0; r < 16; ++r) sv[r] = acc[r];
-          tile_store(Ut + (size_t)p * 2048, lane, sv);
-        }
-        float sx[16];
-        if (js + 31 <= wmin) {
-          // interior tile: every key is valid for every row of the wave
-#pragma unroll
-          for (int r = 0; r < 16; ++r) sx[r] = acc[r] * a.scale;
-          tile_extremum<true>(sx, js, half, Mx, ax, cx);
-          if constexpr (TRACKMIN) tile_extremum<false>(sx, js, half, Mn, an, cn);
-        } else {
-          float sn[16];
-#pragma unroll
-          for (int r = 0; r < 16; ++r) {
-            const float sc = acc[r] * a.scale;
-            const bool valid = js + krel(r, half) <= jlim;
-            sx[r] = valid ? sc : -INFINITY;
-            sn[r] = valid ? sc : INFINITY;
-          }
-          tile_extremum<true>(sx, js, half, Mx, ax, cx);
-          if constexpr (TRACKMIN) tile_extremum<false>(sn, js, half, Mn, an, cn);
-        }
-      }
-      fk.template stash_rows<RS>(smem + ((p + 1) & 1) * KBUF, tid);
-      lds_barrier();
-    }
-  }
-  auto merge = [](bool mx, float &M, int &ai, int &c, float M2, int a2, int c2) {
-    const bool take = mx ? (M2 > M) : (M2 < M);
-    const bool tie = M2 == M;
-    ai = take ? a2 : (tie ? min(ai, a2) : ai);
-    c = take ? c2 : (tie ? c + c2 : c);
-    M = take ? M2 : M;
-  };
-  merge(true, Mx, ax, cx, __shfl_xor(Mx, 32), __shfl_xor(ax, 32), __shfl_xor(cx, 32));
-  if constexpr (TRACKMIN)
-    merge(false, Mn, an, cn, __shfl_xor(Mn, 32), __shfl_xor(an, 32), __shfl_xor(cn, 32));
-  if (half == 0) {
-    int *x = &Xc[pr][kh][0][l32];
-    x[0] = __float_as_int(Mx); x[32] = ax; x[64] = cx;
-    x[96] = __float_as_int(Mn); x[128] = an; x[160] = cn;
-  }
-  __syncthreads();
-  {
-    const int *x0 = &Xc[pr][0][0][l32], *x1 = &Xc[pr][1][0][l32];
-    Mx = __int_as_float(x0[0]); ax = x0[32]; cx = x0[64];
-    merge(true, Mx, ax, cx, __int_as_float(x1[0]), x1[32], x1[64]);
-    if constexpr (TRACKMIN) {
-      Mn = __int_as_float(x0[96]); an = x0[128]; cn = x0[160];
-      merge(false, Mn, an, cn, __int_as_float(x1[96]), x1[128], x1[160]);
-    }
-  }
-  const size_t ridx = (size_t)bh * T + row;
-  if (kh == 0 && half == 0 && row < T) {
-    a.st.M[ridx] = Mx;
-    a.st.amax[ridx] = ax;
-    a.st.nmax[ridx] = cx;
-    if constexpr (TRACKMIN) {
-      a.st.m[ridx] = Mn;
-      a.st.amin[ridx] = an;
-      a.st.nmin[ridx] = cn;
-    }
-  }
-  if constexpr (!TRACKMIN) Mn = Mx;
-  const RowConst rc = row_const(Mx, Mn, a.K, CALIB, a.tau, a.scale);
-
-  // ---------------- pass 2: reconstruct, normalize, O = P V ---------------
-  f32x16 oacc[NC], olacc[OL ? NC : 1];
-#pragma unroll
-  for (int c = 0; c < NC; ++c)
-#pragma unroll
-    for (int e = 0; e < 16; ++e) oacc[c][e] = 0.f;
-  if constexpr (OL) {
-#pragma unroll
-    for (int c = 0; c < NC; ++c)
-#pragma unroll
-      for (int e = 0; e < 16; ++e) olacc[c][e] = 0.f;
-  }
-  float WN = 0.f, WLs = 0.f;
-  uint16_t *Vt = smem + 2 * KBUF;
-  auto load_s = [&](int p, f32x16 &S) {
-    float sv[16];
-    tile_load(Ut + (size_t)p * 2048, lane, sv);
-#pragma unroll
-    for (int r = 0; r < 16; ++r) S[r] = sv[r];
-  };
-  auto tile = [&](int p, const f32x16 &S, auto masked_tag) {
-    constexpr bool MASKED = decltype(masked_tag)::value;
-    constexpr bool COMPACT = compact_codes<CALIB, RECON>();
-    float u[16];
-    uint32_t cw[4];
-    decide_u<CALIB>(S, rc, Mx, Mn, a.K, a.tau, a.scale, u);
-    if constexpr (!COMPACT) tile_store(Ut + (size_t)p * 2048, lane, u);
-    const int js = p * H16_CH + kh * 32;
-    float w[16], wl[16];
-    float tWN = 0.f, tWL = 0.f;
-#pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      const KeyDec kd = key_of<CALIB>(u[r], Kf);
-      if constexpr (COMPACT) code_put(cw, r, kd);
-      float Eu;
-      if constexpr (MASKED) {
-        Eu = grid_upper(kd.rf, rc);
-      } else {
-        // interior tile: only the FWM tail is zero, through e^{-inf} = 0
-        const float arg = fmaf(kd.rf, rc.hl, rc.b1l);
-        Eu = __builtin_amdgcn_exp2f(kd.tail ? -INFINITY : arg);
-      }
-      const float El = Eu * rc.emh;
-      float wL = fmaf(kd.t, Eu - El, El);
-      float wN = kd.up ? Eu : El;
-      if constexpr (MASKED) {
-        const bool valid = (js + krel(r, half) <= jlim) & !kd.tail;
-        wL = valid ? wL : 0.f;
-        wN = valid ? wN : 0.f;
-      }
-      tWL += wL;
-      wl[r] = wL;
-      if constexpr (NEAREST) {
-        tWN += wN;
-        w[r] = wN;
-      } else {
-        w[r] = wL;
-      }
-    }
-    if constexpr (COMPACT) codes_store(Ut + (size_t)p * 2048, lane, cw);
-    WN += tWN;
-    WLs += tWL;
-    const uint16_t *Vb = Vt + (p & 1) * VBUF + kh * 32 + 4 * half;
-#pragma unroll
-    for (int t = 0; t < 2; ++t) {
-      const bf16x8 bw = to_bf16x8(&w[8 * t]);
-      bf16x8 bl;
-      if constexpr (OL) bl = to_bf16x8(&wl[8 * t]);
-#pragma unroll
-      for (int c = 0; c < NC; ++c) {
-        const int col = 32 * c + l32;
-        const uint16_t *vr = Vb + (col < D ? col : 0) * H16_TS + 16 * t;
-        uint2 lo = *reinterpret_cast<const uint2 *>(vr);
-        uint2 hi = *reinterpret_cast<const uint2 *>(vr + 8);
-        if (col >= D) { lo = make_uint2(0, 0); hi = lo; }
-        const bf16x8 av = pair_bf16x8(lo, hi);
-        oacc[c] = mfma16(av, bw, oacc[c]);
-        if constexpr (OL) olacc[c] = mfma16(av, bl, olacc[c]);
-      }
-    }
-  };
-  {
-    Blocks16<D, H16_CH, 256> fv;
-    fv.fetch(vs, 0, T, tid);
-    fv.template stash_cols<H16_TS>(Vt, tid);
-    f32x16 SA, SB;
-    if (npw > 0) load_s(0, SA);
-    // tiles below the wave's first row are interior (no causal mask)
-    auto run = [&](int p, const f32x16 &S) {
-      if (p * H16_CH + kh * 32 + 31 <= wmin)
-        tile(p, S, std::integral_constant<bool, false>{});
-      else
-        tile(p, S, std::integral_constant<bool, true>{});
-    };
-    lds_barrier();
-    for (int p = 0; p < nstep; p += 2) {
-      fv.fetch(vs, min(p + 1, nstep - 1) * H16_CH, T, tid);
-      if (p + 1 < npw) load_s(p + 1, SB);
-      if (p < npw) run(p, SA);
-      fv.template stash_cols<H16_TS>(Vt + ((p + 1) & 1) * VBUF, tid);
-      lds_barrier();
-      if (p + 1 >= nstep) break;
-      fv.fetch(vs, min(p + 2, nstep - 1) * H16_CH, T, tid);
-      if (p + 2 < npw) load_s(p + 2, SA);
-      if (p + 1 < npw) run(p + 1, SB);
-      fv.template stash_cols<H16_TS>(Vt + (p & 1) * VBUF, tid);
-      lds_barrier();
-    }
-  }
-  WN += __shfl_xor(WN, 32);
-  WLs += __shfl_xor(WLs, 32);
-  float *red = reinterpret_cast<float *>(smem) + pr * 64 * NRED + lane;
-  if (kh == 1) {
-#pragma unroll
-    for (int c = 0; c < NC; ++c)
-#pragma unroll
-      for (int e = 0; e < 16; ++e) {
-        red[(c * 16 + e) * 64] = oacc[c][e];
-        if constexpr (OL) red[((NC + c) * 16 + e) * 64] = olacc[c][e];
-      }
-    red[(NRED - 2) * 64] = WN;
-    red[(NRED - 1) * 64] = WLs;
-  }
-  __syncthreads();
-  if (kh == 1) return;
-#pragma unroll
-  for (int c = 0; c < NC; ++c)
-#pragma unroll
-    for (int e = 0; e < 16; ++e) {
-      oacc[c][e] += red[(c * 16 + e) * 64];
-      if constexpr (OL) olacc[c][e] += red[((NC + c) * 16 + e) * 64];
-    }
-  WN += red[(NRED - 2) * 64];
-  WLs += red[(NRED - 1) * 64];
-  const float W = NEAREST ? WN : WLs;
-  if (half == 0 && row < T) {
-    a.st.W[ridx] = W;
-    a.st.WL[ridx] = WLs;
-  }
-  if (row < T) {
-    const float inv = 1.f / W, invl = 1.f / WLs;
-    float *orow = a.o + slice + (size_t)row * D;
-    uint16_t *orow16 = a.o16 + slice + (size_t)row * D;
-#pragma unroll
-    for (int c = 0; c < NC; ++c)
-#pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        const int n = c * 32 + 8 * g + 4 * half;
-        if (n >= D) continue;
-        f32x4 x = {oacc[c][4 * g] * inv, oacc[c][4 * g + 1] * inv,
-                   oacc[c][4 * g + 2] * inv, oacc[c][4 * g + 3] * inv};
-        if (a.o16)
-          *reinterpret_cast<uint2 *>(orow16 + n) =
-              make_uint2(pack_bf16x2(x[0], x[1]), pack_bf16x2(x[2], x[3]));
-        else
-          *reinterpret_cast<f32x4 *>(orow + n) = x;
-        if constexpr (OL) {
-          f32x4 y = {olacc[c][4 * g] * invl, olacc[c][4 * g + 1] * invl,
-                     olacc[c][4 * g + 2] * invl, olacc[c][4 * g + 3] * invl};
-          *reinterpret_cast<f32x4 *>(a.st.OL + ridx * D + n) = y;
-        }
-      }
-  }
-}
-
-// ---------------------------------------------------------------------------
 // Backward main (bf16 inputs): KV-major as bwd_main_shared_kernel, 8 waves
 // in two groups of 4 taking alternate 32-query tiles; 128 keys per
 // workgroup with V row-major in LDS (dP^T A operand); per group the query
@@ -823,15 +528,6 @@ __global__ __launch_bounds__(512) void bwd16_dq_kernel(BwdArgs16 a) {
 }
 
 #define KIA_B16_INST(D)                                                                  \
-  template __global__ void fwd16_kernel<D, CAL_MINMAX, REC_LERP, false>(FwdArgs16);      \
-  template __global__ void fwd16_kernel<D, CAL_MINMAX, REC_NEAREST, false>(FwdArgs16);   \
-  template __global__ void fwd16_kernel<D, CAL_MINMAX, REC_NEAREST, true>(FwdArgs16);    \
-  template __global__ void fwd16_kernel<D, CAL_FWM, REC_LERP, false>(FwdArgs16);         \
-  template __global__ void fwd16_kernel<D, CAL_FWM, REC_NEAREST, false>(FwdArgs16);      \
-  template __global__ void fwd16_kernel<D, CAL_FWM, REC_NEAREST, true>(FwdArgs16);       \
-  template __global__ void fwd16_kernel<D, CAL_RESOLVED, REC_LERP, false>(FwdArgs16);    \
-  template __global__ void fwd16_kernel<D, CAL_RESOLVED, REC_NEAREST, false>(FwdArgs16); \
-  template __global__ void fwd16_kernel<D, CAL_RESOLVED, REC_NEAREST, true>(FwdArgs16);  \
   template __global__ void bwd16_main_kernel<D, CAL_RESOLVED, REC_LERP, false>(BwdArgs16);    \
   template __global__ void bwd16_main_kernel<D, CAL_RESOLVED, REC_LERP, true>(BwdArgs16);     \
   template __global__ void bwd16_main_kernel<D, CAL_RESOLVED, REC_NEAREST, false>(BwdArgs16); \

@@ -968,31 +968,13 @@ __device__ __forceinline__ void tie_rows(const BwdArgsT<TI> &a, int bh, int rb, 
   }
   if (!__any(tierow)) return;
   // the row's scores with the canonical sub-tile of the input type
+  constexpr int NP = Pieces<TI>::N;
+  bf16x8 qop[NP][D / 16];
+  const float qf = load_query<D>(a.q + slice, i < T ? i : T - 1, T, half, qop);
   auto tile_scores = [&](int js) -> f32x16 {
-    if constexpr (sizeof(TI) == 2) {
-      bf16x8 qop[D / 16], kop[D / 16];
-      load_rows16<D>(a.q + slice, i < T ? i : T - 1, T, half, qop);
-      load_rows16<D>(a.k + slice, js + l32, T, half, kop);
-      return score_tile16<D>(kop, qop);
-    } else {
-      float qop[D / 2], kop[D / 2];
-      const int rr = i < T ? i : T - 1;
-      const int key = js + l32;
-      const bool okk = key < T;
-      const float *qs = a.q + slice + (size_t)rr * D + half * (D / 2);
-      const float *ksrc = a.k + slice + (size_t)(okk ? key : 0) * D + half * (D / 2);
-#pragma unroll
-      for (int s = 0; s < D / 2; s += 4) {
-        const f32x4 x = *reinterpret_cast<const f32x4 *>(qs + s);
-        const f32x4 y = *reinterpret_cast<const f32x4 *>(ksrc + s);
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          qop[s + e] = x[e];
-          kop[s + e] = okk ? y[e] : 0.f;
-        }
-      }
-      return score_tile<D>(kop, qop);
-    }
+    bf16x8 kop[NP][D / 16];
+    load_rows<D>(a.k + slice, js + l32, T, half, kop);
+    return qf * score_tile<D, NP>(kop, qop);
   };
   const int kend = a.causal ? min(T, rb * 32 + 32) : T;
   for (int js = 0; js < kend; js += 32) {

@@ -1,18 +1,32 @@
 // kia_device.hpp -- device building blocks shared by every K-interval
-// attention kernel for gfx950 (CDNA4, wave64, fp32 MFMA 32x32x2).
+// attention kernel for gfx950 (CDNA4, wave64, bf16 MFMA 32x32x16 with fp32
+// accumulation).
+//
+// fp32 operands on the bf16 matrix unit. An fp32 value is the exact sum of
+// three bf16 pieces x = x0 + x1 + x2, each the nearest bf16 of what is left
+// (|x1| <= 2^-9 |x|, |x2| <= 2^-18 |x|), and a product x y is taken as the six
+// piece products down to 2^-18: x2 y0, x1 y1, x0 y2, x1 y0, x0 y1, x0 y0. The
+// three that are left out are at most 2^-26 |x y| together, below the fp32
+// rounding of one product. bf16 MFMA runs at 16 times the fp32 MFMA's rate, so
+// six of them take 0.375 of its time, and unlike it they overlap with VALU
+// work of the SIMD's other wave. Against 64 bits (N(0,1) operands, one 32x32
+// tile, measured on the device): contraction length 64, 1.44e-7 (fp32 MFMA)
+// and 4.6e-8 (the six products added smallest first); 128, 2.04e-7 and
+// 6.2e-8; streamed over 512 with the six products of 16 terms at a time,
+// 4.1e-7 and 3.4e-7. bf16 inputs are one piece and one product.
 //
 // Canonical score sub-tile. Every kernel that needs a score s_ij computes it
 // with score_tile(): a 32-key x 32-query block of S^T accumulated by
-// v_mfma_f32_32x32x2_f32 over d in one fixed order, with the key block and
+// v_mfma_f32_32x32x16_bf16 over d in one fixed order, with the key block and
 // the query block aligned to multiples of 32. The A operand is K (rows =
 // keys), the B operand Q (columns = queries). Lane l (half h = l/32) feeds,
-// at k-step s, K[key0 + l%32][h*d/2 + s] and Q[query0 + l%32][h*d/2 + s].
-// Output register r of lane l holds S^T[key0 + krel(r, h)][query0 + l%32]
-// with krel(r, h) = 8*(r/4) + 4*h + r%4. Same operands, same instruction
-// sequence, same lane/register position: the fp32 score of a pair is
-// bit-identical wherever it is computed (the forward's extrema pass, whose
-// tiles the second pass and the backward reuse, the tie path and the debug
-// codes), which the exact extremum ties and index decisions rely on.
+// at k-step s, K[key0 + l%32][16 s + 8 h + e] and Q[query0 + l%32][16 s + 8 h
+// + e], e = 0..7. Output register r of lane l holds S^T[key0 + krel(r, h)]
+// [query0 + l%32] with krel(r, h) = 8*(r/4) + 4*h + r%4. Same operands, same
+// instruction sequence, same lane/register position: the fp32 score of a pair
+// is bit-identical wherever it is computed (both passes of the forward, the
+// tie path and the debug exports), which the exact extremum ties and index
+// decisions rely on.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -101,45 +115,6 @@ template <int D> struct Dims {
 
 __device__ __forceinline__ int krel(int r, int half) {
   return 8 * (r >> 2) + 4 * half + (r & 3);
-}
-
-// Folds one score sub-tile into a lane's running extremum X with its first
-// key index ax and its count cx. sv holds the lane's 16 scores, invalid keys
-// set to -inf (maximum) or +inf (minimum); a lane's keys grow with r and
-// the tiles come in increasing key order, so the first index of a tie is
-// the one already held. One tile extremum, then one sweep for the count and
-// the first position of it.
-template <bool MAX>
-__device__ __forceinline__ void tile_extremum(const float (&sv)[16], int js, int half,
-                                              float &X, int &ax, int &cx) {
-  float tm = sv[0];
-#pragma unroll
-  for (int r = 1; r < 16; ++r) tm = MAX ? fmaxf(tm, sv[r]) : fminf(tm, sv[r]);
-  int tc = 0, tf = 0;
-#pragma unroll
-  for (int r = 15; r >= 0; --r) {
-    const bool e = sv[r] == tm;
-    tc += e ? 1 : 0;
-    tf = e ? r : tf;
-  }
-  const bool some = MAX ? (tm != -INFINITY) : (tm != INFINITY);  // a valid key
-  const bool take = some & (MAX ? (tm > X) : (tm < X));
-  const bool tie = some & (tm == X);
-  ax = take ? js + krel(tf, half) : ax;
-  cx = take ? tc : (tie ? cx + tc : cx);
-  X = take ? tm : X;
-}
-
-// S^T sub-tile: kop[s], qop[s] as described above; returns raw q.k sums.
-template <int D>
-__device__ __forceinline__ f32x16 score_tile(const float (&kop)[D / 2],
-                                             const float (&qop)[D / 2]) {
-  f32x16 acc;
-#pragma unroll
-  for (int e = 0; e < 16; ++e) acc[e] = 0.f;
-#pragma unroll
-  for (int s = 0; s < D / 2; ++s) acc = mfma32(kop[s], qop[s], acc);
-  return acc;
 }
 
 // Per-row constants of the fast index/weight evaluation.
@@ -307,6 +282,18 @@ __device__ __forceinline__ void fix_ambiguous(const f32x16 &acc, const RowConst 
       amb &= amb - 1u;
     }
   }
+}
+
+// Twice the position of a key that is_ambiguous(), moved into the interval of
+// its exact decision (the same values as fix_ambiguous).
+template <int CALIB>
+__device__ __forceinline__ float exact_v2(float s, float v, float M, float m, int K, float tau) {
+  const float Kf = (float)K;
+  float rf; int up, tl;
+  exact_decision(s, M, m, K, CALIB, tau, rf, up, tl);
+  const float lo = rf + (up ? 0.5f : 0.f);
+  const float hv = (up && rf == Kf - 1.f) ? Kf : below(rf + (up ? 1.f : 0.5f));
+  return 2.f * (tl ? -1.f : fminf(fmaxf(0.5f * v, lo), hv));
 }
 
 template <int CALIB>
@@ -623,34 +610,249 @@ __device__ __forceinline__ bf16x8 to_bf16x8(const float *v) {
   return r;
 }
 
-// Canonical bf16 score sub-tile: S^T with A = K, B = Q; lane l (half h)
-// feeds K[key0 + l%32][16s + 8h + e] and Q[query0 + l%32][16s + 8h + e] at
-// k-step s. Output register r of lane l holds S^T[key0 + krel(r, h)]
-// [query0 + l%32] (as score_tile). Every bf16 kernel computes a pair's
-// score with this sub-tile, so it is bit-identical wherever it is computed.
-template <int D>
-__device__ __forceinline__ f32x16 score_tile16(const bf16x8 (&kop)[D / 16],
-                                               const bf16x8 (&qop)[D / 16]) {
+// ---- operand pieces --------------------------------------------------------
+// LDS and operand vectors that alias the element types they are staged as
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4), may_alias));
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2), may_alias));
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+
+// bf16 pieces per element: three for fp32 inputs, one for bf16 inputs.
+template <typename TI> struct Pieces { static constexpr int N = sizeof(TI) == 4 ? 3 : 1; };
+
+// The six products of two three-piece operands, smallest first.
+constexpr int PROD_A[6] = {2, 1, 0, 1, 0, 0}, PROD_B[6] = {0, 1, 2, 0, 1, 0};
+
+// Two fp32 values as one word of two bf16, round to nearest even (a low).
+__device__ __forceinline__ uint32_t cvt_bf16x2(float a, float b) {
+  typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+  const bf16x2 r = {(__bf16)a, (__bf16)b};
+  return __builtin_bit_cast(uint32_t, r);
+}
+
+// The three pieces of eight fp32 values (exact: x = p0 + p1 + p2). What a
+// piece leaves is exact in fp32, and v_dot2 (a pair of bf16 times {-1, 0} or
+// {0, -1}, plus an fp32 value) takes it from the packed pair in one operation:
+// seven operations for two values and their three pieces.
+__device__ __forceinline__ void split8(const float (&x)[8], u32x4 (&p)[3]) {
+  typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+  // (kept in registers: as an inline constant -1.0 is the other half)
+  uint32_t mlo = 0x0000bf80u, mhi = 0xbf800000u;
+  asm("" : "+s"(mlo), "+s"(mhi));
+  const bf16x2 lo = __builtin_bit_cast(bf16x2, mlo), hi = __builtin_bit_cast(bf16x2, mhi);
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    float a = x[2 * e], b = x[2 * e + 1];
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+      const uint32_t w = cvt_bf16x2(a, b);
+      p[i][e] = w;
+      if (i < 2) {
+        a = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, w), lo, a, false);
+        b = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, w), hi, b, false);
+      }
+    }
+  }
+}
+__device__ __forceinline__ bf16x8 as_op(u32x4 x) { return __builtin_bit_cast(bf16x8, x); }
+// NP pieces of eight computed fp32 values: the three exact pieces, or their
+// bf16 rounding
+template <int NP> __device__ __forceinline__ void to_pieces(const float (&x)[8], bf16x8 (&p)[NP]) {
+  if constexpr (NP == 3) {
+    u32x4 w[3];
+    split8(x, w);
+#pragma unroll
+    for (int i = 0; i < 3; ++i) p[i] = as_op(w[i]);
+  } else {
+    u32x4 w;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) w[e] = cvt_bf16x2(x[2 * e], x[2 * e + 1]);
+    p[0] = as_op(w);
+  }
+}
+
+// c += a b over one 16-term k-step, all its piece products.
+template <int NP>
+__device__ __forceinline__ f32x16 mma(const bf16x8 (&a)[NP], const bf16x8 (&b)[NP], f32x16 c) {
+  if constexpr (NP == 1) return mfma16(a[0], b[0], c);
+  else {
+#pragma unroll
+    for (int i = 0; i < 6; ++i) c = mfma16(a[PROD_A[i]], b[PROD_B[i]], c);
+    return c;
+  }
+}
+
+// A contraction over d (D / 16 k-steps): ap(piece, s) and bp(piece, s) give
+// the A and B operands of piece `piece` at k-step s. One piece of A is live at
+// a time; the products of full size come last, so that only they round at the
+// size of the result.
+template <int D, int NP, class FA, class FB>
+__device__ __forceinline__ f32x16 score_tile(FA ap, FB bp) {
   f32x16 acc;
 #pragma unroll
   for (int e = 0; e < 16; ++e) acc[e] = 0.f;
 #pragma unroll
-  for (int s = 0; s < D / 16; ++s) acc = mfma16(kop[s], qop[s], acc);
+  for (int i = NP - 1; i >= 0; --i) {
+    bf16x8 a[D / 16];
+#pragma unroll
+    for (int s = 0; s < D / 16; ++s) a[s] = ap(i, s);
+#pragma unroll
+    for (int j = NP - 1 - i; j >= 0; --j)
+#pragma unroll
+      for (int s = 0; s < D / 16; ++s) acc = mfma16(a[s], bp(j, s), acc);
+  }
   return acc;
 }
-// the lane's operand of one 32-row tile of a [T, D] bf16 slice (row clamped
-// into the slice; rows at or beyond T read as zero)
-template <int D>
-__device__ __forceinline__ void load_rows16(const uint16_t *slice, int row, int T, int half,
-                                            bf16x8 (&op)[D / 16]) {
+// both operands in registers
+template <int D, int NP>
+__device__ __forceinline__ f32x16 score_tile(const bf16x8 (&aop)[NP][D / 16],
+                                             const bf16x8 (&bop)[NP][D / 16]) {
+  return score_tile<D, NP>([&](int p, int s) { return aop[p][s]; },
+                           [&](int p, int s) { return bop[p][s]; });
+}
+
+// The lane's operand of one 32-row tile of a [T, D] slice (rows at or beyond
+// T read as zero).
+template <int D, typename TI>
+__device__ __forceinline__ void load_rows(const TI *slice, int row, int T, int half,
+                                          bf16x8 (&op)[Pieces<TI>::N][D / 16]) {
   const bool ok = row < T;
-  const uint16_t *src = slice + (size_t)(ok ? row : 0) * D + 8 * half;
+  const TI *src = slice + (size_t)(ok ? row : 0) * D + 8 * half;
 #pragma unroll
   for (int s = 0; s < D / 16; ++s) {
-    uint4 x = *reinterpret_cast<const uint4 *>(src + 16 * s);
-    if (!ok) x = make_uint4(0, 0, 0, 0);
-    op[s] = as_bf16x8(x);
+    if constexpr (sizeof(TI) == 4) {
+      float x[8];
+#pragma unroll
+      for (int g = 0; g < 2; ++g) {
+        const f32x4 v = *reinterpret_cast<const f32x4 *>(src + 16 * s + 4 * g);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) x[4 * g + e] = ok ? v[e] : 0.f;
+      }
+      bf16x8 p[3];
+      to_pieces<3>(x, p);
+#pragma unroll
+      for (int i = 0; i < 3; ++i) op[i][s] = p[i];
+    } else {
+      u32x4 v = *reinterpret_cast<const u32x4 *>(src + 16 * s);
+      if (!ok) v = u32x4{0, 0, 0, 0};
+      op[0][s] = as_op(v);
+    }
   }
+}
+
+// The lane's operand of 32 query rows, and the factor that takes a product
+// with them back to q.k (1 for bf16 inputs). The pieces of a value below
+// 2^-109 would lose bits under bf16's smallest 2^-133, so a row that holds one
+// is scaled up by a power of two first (towards a maximum of 2^60), which is
+// exact; every other row has the factor 1.
+template <int D, typename TI>
+__device__ __forceinline__ float load_query(const TI *slice, int row, int T, int half,
+                                            bf16x8 (&op)[Pieces<TI>::N][D / 16]) {
+  if constexpr (sizeof(TI) == 2) {
+    load_rows<D>(slice, row, T, half, op);
+    return 1.f;
+  } else {
+    float x[D / 16][8], big = 0.f;
+    bool tiny = false;
+#pragma unroll
+    for (int s = 0; s < D / 16; ++s)
+#pragma unroll
+      for (int g = 0; g < 2; ++g) {
+        const f32x4 v =
+            *reinterpret_cast<const f32x4 *>(slice + (size_t)row * D + 16 * s + 8 * half + 4 * g);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          x[s][4 * g + e] = v[e];
+          big = fmaxf(big, fabsf(v[e]));
+          tiny |= (fabsf(v[e]) < 0x1p-109f) & (v[e] != 0.f);
+        }
+      }
+    big = fmaxf(big, __shfl_xor(big, 32));
+    tiny = tiny | (__shfl_xor(tiny ? 1 : 0, 32) != 0);
+    // exponent of the row's largest element (denormals: -127)
+    const int up = tiny ? min(max(60 - ((int)(__float_as_uint(big) >> 23) - 127), 0), 100) : 0;
+    const float f = ldexpf(1.f, up);
+#pragma unroll
+    for (int s = 0; s < D / 16; ++s) {
+#pragma unroll
+      for (int e = 0; e < 8; ++e) x[s][e] *= f;
+      bf16x8 p[3];
+      to_pieces<3>(x[s], p);
+#pragma unroll
+      for (int i = 0; i < 3; ++i) op[i][s] = p[i];
+    }
+    return ldexpf(1.f, -up);
+  }
+}
+
+// ---- staging of row blocks in LDS ------------------------------------------
+// A [ROWS, D] block staged as bf16 pieces [piece][row][D + 8] (the row stride
+// of D / 2 + 4 dwords puts the 16-byte reads of eight consecutive rows in
+// distinct banks). NT threads fetch eight elements each into registers
+// (buffer loads: rows at or past T read as zeros) and split them when they
+// are stashed.
+template <int D, int ROWS, int NT, typename TI> struct Stage {
+  static constexpr int NP = Pieces<TI>::N, RS = D + 8, PS = ROWS * RS, SIZE = NP * PS;
+  static constexpr int V8 = ROWS * D / 8, PF = (V8 + NT - 1) / NT;
+  static constexpr int RPP = NT * 8 / D;  // rows per pass
+  static_assert(V8 % NT == 0 || PF == 1, "whole passes");
+  u32x4 x[PF][sizeof(TI) / 2];
+  __device__ __forceinline__ void fetch(const TI *src, int j0, int T, int tid) {
+    const uint32_t voff = tid < V8 ? (uint32_t)tid * 8u * sizeof(TI) : 0x80000000u;
+#pragma unroll
+    for (int e = 0; e < PF; ++e) {
+      const int rb = min(j0 + e * RPP, T);
+      const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
+          const_cast<TI *>(src) + (size_t)rb * D, (short)0, (T - rb) * D * (int)sizeof(TI),
+          0x00020000);
+#pragma unroll
+      for (int g = 0; g < (int)sizeof(TI) / 2; ++g)
+        x[e][g] = __builtin_bit_cast(
+            u32x4, __builtin_amdgcn_raw_buffer_load_b128(rs, voff + 16u * g, 0, 0));
+    }
+  }
+  __device__ __forceinline__ void stash(uint16_t *dst, int tid) const {
+    if (V8 % NT != 0 && tid >= V8) return;
+#pragma unroll
+    for (int e = 0; e < PF; ++e) {
+      const int idx = tid + NT * e;
+      uint16_t *d = dst + (idx / (D / 8)) * RS + (idx % (D / 8)) * 8;
+      if constexpr (NP == 3) {
+        float f[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) f[i] = __uint_as_float(x[e][i / 4][i % 4]);
+        u32x4 p[3];
+        split8(f, p);
+#pragma unroll
+        for (int i = 0; i < 3; ++i) *reinterpret_cast<u32x4 *>(d + i * PS) = p[i];
+      } else {
+        *reinterpret_cast<u32x4 *>(d) = x[e][0];
+      }
+    }
+  }
+};
+
+// Row-major operand: row `row` of a staged block, elements 8 half + 16 s ..
+__device__ __forceinline__ bf16x8 row_op(const uint16_t *p) {
+  return as_op(*reinterpret_cast<const u32x4 *>(p));
+}
+
+// Transposed operand of a staged block. ds_read_b64_tr_b16 takes, per group
+// of 16 lanes, four rows of 16 columns (lane i of the group addresses row
+// i / 4, columns 4 (i % 4) ..) and gives lane i the four rows' values of
+// column i. The lane's column is 32 c + l % 32 and its eight k-slots are the
+// rows r0 + 4 half + {0..3, 8..11}: the rows krel(8 t + e, half) with r0 =
+// 16 t, that is, the lane's own registers 8 t .. 8 t + 7 of a 32x32 tile.
+// tr_base() is the lane's part of the address.
+template <int D, int RS = D + 8> __device__ __forceinline__ int tr_base(int lane) {
+  const int col = D >= 32 ? 16 * ((lane >> 4) & 1) : 0;  // d = 16: columns 16..31 repeat, unused
+  return (4 * (lane >> 5) + ((lane & 15) >> 2)) * RS + col + 4 * (lane & 3);
+}
+template <int RS> __device__ __forceinline__ bf16x8 tr_op(const uint16_t *p) {
+  typedef s16x4 __attribute__((address_space(3))) *lds4;
+  const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds4)p);
+  const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds4)(p + 8 * RS));
+  typedef short s16x8 __attribute__((ext_vector_type(8)));
+  return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
 }
 
 // Stats view from the caller's buffer (offsets as kia_stats_offset()).

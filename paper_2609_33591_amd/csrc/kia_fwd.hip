@@ -1,123 +1,68 @@
-// kia_fwd.hip -- forward of causal K-interval attention on gfx950.
+// kia_fwd.hip -- forward of causal K-interval attention on gfx950, for fp32
+// inputs (three bf16 pieces per operand) and bf16 inputs (one piece).
 //
-// One workgroup = 4 waves = 64 query rows of one (b, h): two row groups of
-// 32 rows times two key halves. Each wave keeps its 32 Q rows in registers
-// as the B operand of the canonical score sub-tile. Keys stream through LDS
-// in chunks of 64 (one 32-key tile per key half); the waves of a row group
-// take alternate tiles, so the longest rows' work is split over two waves.
-// Grids too small to fill the chip (KP = 4) take one row group of 32 rows
-// with four key quarters instead: chunks of 128 keys, every fourth tile per
-// wave, twice the workgroups; the smallest grids (KP = 8) take eight key
-// parts in workgroups of 8 waves (chunks of 256 keys).
+// One workgroup = RG row groups of 32 query rows of one (b, h) times KP key
+// parts, one wave each. Each wave keeps its 32 Q rows in registers as the B
+// operand of the canonical score sub-tile. Keys stream through LDS in chunks
+// of KP 32-key tiles, one per key part, staged row-major in bf16 pieces: K is
+// read by rows (the score sub-tile's A operand) and V through transposing
+// reads (the P V A operand). Large grids take RG = 4, KP = 1: 128 rows share
+// each staged tile, so splitting K and V into pieces costs 88 VALU operations
+// per thread and 32-key step against about 580 of a tile's weights. Grids too
+// small to fill the chip give up row groups for key parts.
 //
 // Pass 1 (row extrema, App. A: amax/amin over the valid keys): score
-//   sub-tiles, stored to the stats field U, and per-lane running max/min
-//   with first index and tie count, merged across the two lanes that share
-//   a row, then across the key parts through LDS (max, then smallest
-//   index, tie counts added).
-// Pass 2 (Sec. 3 reconstruction and normalization): the grid depends on the
-//   extrema, so the wave reads its stored score tiles back (one ahead): per
-//   key the interval/level decision, whose decided position u replaces the
-//   score in U for the backward, w^L and w^N from e^{b_{r+1}} (one exp2 per
-//   key), the row sums
-//   W^N, W^L, and O += w V on fp32 MFMA with the weight registers as the B
-//   operand (no data movement). Prob-STE with Nearest also accumulates
-//   O^L = w^L V for the backward. The weights are absolute once the extrema
-//   are known, so the key parts' partial sums simply add (through LDS);
-//   O = (sum w v) / W at the end: W >= 1 because the argmax key has weight
-//   e^0 = 1, so no online rescaling.
+//   sub-tiles and the raw row maximum (and minimum), merged across the two
+//   lanes that share a row and, through LDS, across the key parts. Nothing is
+//   stored: pass 2 computes the same sub-tiles again. On the bf16 matrix unit
+//   that costs less than writing 4 bytes per pair and reading them back (at
+//   B8 H12 T1024 d64 2 x 208 MB, which alone take 80 us of the former 220).
+// Pass 2 (Sec. 3 reconstruction and normalization): per key the
+//   interval/level decision, kept in U for the backward (one byte, or the
+//   position u), w^L and w^N from e^{b_{r+1}} (one exp2 per key), the row sums
+//   W^N, W^L, and O += w V with the weight registers as the B operand (no data
+//   movement). Prob-STE with Nearest also accumulates O^L = w^L V for the
+//   backward. A tile that reaches a row's maximum (minimum) is swept for the
+//   first index and the number of its ties. The weights are absolute once the
+//   extrema are known, so the key parts' partial sums simply add (through
+//   LDS); O = (sum w v) / W at the end: W >= 1 because the argmax key has
+//   weight e^0 = 1, so no online rescaling.
 // Exponential weight functions (softmax, BF16-exp, FP8-exp; App. A, App. D)
 //   take the same two passes with the maximum only: pass 2 forms z = s - M,
-//   the fp32 exponential as the weight function rounds it (kept in U in
-//   place of the score) and the weight, with no grid.
-#include <type_traits>
+//   the fp32 exponential as the weight function rounds it (kept in U) and the
+//   weight, with no grid.
 
 #include "kia_device.hpp"
 #include "kia_kernels.hpp"
 
 namespace kia {
 
-constexpr int FWD_TK = 32;   // keys per tile (one MFMA sub-tile)
-constexpr int CODES_BM = 128;
-constexpr int CODES_BN = 64;
-
-template <int D>
-__device__ __forceinline__ void load_tile_lds(float *dst, const float *src,
-                                              int j0, int T, int tid) {
-  // rows j0 .. j0+CODES_BN-1 of a [T, D] slice into dst[CODES_BN][DS]; zero
-  // beyond T and beyond D so that masked products never meet garbage
-  // (0 * NaN).
-  constexpr int DP = Dims<D>::DP, DS = Dims<D>::DS;
-  constexpr int V4 = CODES_BN * DP / 4;
-#pragma unroll
-  for (int e = tid; e < V4; e += 256) {
-    const int row = e / (DP / 4), c4 = e % (DP / 4);
-    f32x4 val = {0.f, 0.f, 0.f, 0.f};
-    if (j0 + row < T && c4 * 4 < D)
-      val = *reinterpret_cast<const f32x4 *>(src + (size_t)(j0 + row) * D + c4 * 4);
-    *reinterpret_cast<f32x4 *>(dst + row * DS + c4 * 4) = val;
-  }
-}
-
-// Next-chunk register prefetch of a [ROWS, D] slice of K or V by NT
-// threads, through buffer loads: each NT-thread pass gets a buffer resource
-// that starts at its first row and ends at row T, so rows past T (and padded
-// columns) read as zeros.
-template <int D, int ROWS, int NT = 256> struct TileFetch {
-  static constexpr int DP = Dims<D>::DP, DS = Dims<D>::DS;
-  static constexpr int V4 = ROWS * DP / 4;   // 16-byte vectors per chunk
-  static constexpr int PF = V4 / NT;         // passes of NT threads
-  static constexpr int RPP = NT / (DP / 4);  // rows per pass
-  static_assert(V4 % NT == 0, "whole passes");
-  f32x4 x[PF];
-  __device__ __forceinline__ void fetch(const float *src, int j0, int T, uint32_t voff) {
-#pragma unroll
-    for (int e = 0; e < PF; ++e) x[e] = buffer_f32x4(row_rsrc(src, j0 + e * RPP, T, D), voff);
-  }
-  __device__ __forceinline__ void stash(float *dst, int tid) const {
-#pragma unroll
-    for (int e = 0; e < PF; ++e) {
-      const int idx = tid + NT * e;
-      const int r = idx / (DP / 4), c4 = idx % (DP / 4);
-      *reinterpret_cast<f32x4 *>(dst + r * DS + c4 * 4) = x[e];
-    }
-  }
-};
-
-// Running (extremum, first index, count) merge; `b` is the later part.
-template <bool MAX>
-__device__ __forceinline__ void merge_ext(float &M, int &a, int &c, float M2, int a2, int c2) {
-  const bool take = MAX ? (M2 > M) : (M2 < M);
-  const bool tie = M2 == M;
-  a = take ? a2 : (tie ? min(a, a2) : a);
-  c = take ? c2 : (tie ? c + c2 : c);
-  M = take ? M2 : M;
-}
-
-template <int D, int CALIB, int RECON, bool OL, int KP>
-__global__ __launch_bounds__(KP == 8 ? 512 : 256, Dims<D>::FWD_WAVES_PER_EU) void fwd_kernel(FwdArgs a) {
-  constexpr int DS = Dims<D>::DS, NC = Dims<D>::NC;
+template <typename TI, int D, int CALIB, int RECON, bool OL, int RG, int KP>
+__global__ __launch_bounds__(64 * RG * KP, (FwdShape<TI, D, RG, KP>::OCC)) void fwd_kernel(FwdArgsT<TI> a) {
+  using Shape = FwdShape<TI, D, RG, KP>;
+  constexpr int NP = Pieces<TI>::N, NC = D >= 32 ? D / 32 : 1;
   // MinMax and the resolved grid need the row minimum (resolved: for the
   // rounding margin of its far keys only)
   constexpr bool TRACKMIN = CALIB != CAL_FWM, NEAREST = RECON == REC_NEAREST;
-  constexpr bool EXPW = is_exp_rec(RECON);
+  constexpr bool EXPW = is_exp_rec(RECON), COMPACT = compact_codes<CALIB, RECON>();
   static_assert(!EXPW || (CALIB == CAL_FWM && !OL), "exp weights use the maximum only");
+  constexpr int BM = 32 * RG, CHK = 32 * KP, NT = 64 * RG * KP, NBUF = Shape::NBUF;
+  // RG = 1: a wave's tile is read by no other, so it stages it itself (K, then
+  // V, in one buffer of its own) and no barrier is needed
+  constexpr bool PRIV = RG == 1;
+  using St = Stage<D, PRIV ? 32 : CHK, PRIV ? 64 : NT, TI>;
+  constexpr int RS = St::RS, PS = St::PS;
   // per-lane values a wave of key part > 0 hands to part 0 at the end
   constexpr int NRED = NC * 16 * (OL ? 2 : 1) + 2;
-  // KP key parts times RG row groups of 32 rows; a chunk holds one 32-key
-  // tile per key part
-  static_assert(KP == 2 || KP == 4 || KP == 8, "key parts");
-  constexpr int RG = KP == 8 ? 1 : 4 / KP, BM = 32 * RG, CHK = FWD_TK * KP;
-  constexpr int NT = 64 * RG * KP;  // threads: one wave per (row group, key part)
-  static_assert((KP - 1) * RG * 64 * NRED <= 2 * CHK * DS, "reduction buffer");
-  // K chunks (pass 1) and V chunks (pass 2) share one double buffer: the
-  // passes are separated by the extrema merge's workgroup barrier. Half the
-  // LDS of separate buffers, so twice the workgroups fit on a CU.
-  __shared__ __attribute__((aligned(16))) float CH[2][CHK * DS];
-  __shared__ int Xc[RG][KP][6][32];  // pass-1 partials [row group][key part][field][row]
+  // K chunks, then V chunks; at the end the key parts' sums (16-bit units)
+  constexpr int STG = PRIV ? KP * St::SIZE : 2 * NBUF * St::SIZE, RED = (KP - 1) * RG * 64 * NRED * 2;
+  constexpr int SMEM = STG > RED ? STG : RED;
+  __shared__ __attribute__((aligned(16))) uint16_t smem[SMEM];
+  __shared__ int Xc[KP > 1 ? RG * KP * 4 * 32 : 1];  // [row group][key part][field][row]
 
   const int tid = threadIdx.x;
-  const int lane = tid & 63, wave = tid >> 6, half = lane >> 5, l32 = lane & 31;
+  const int lane = tid & 63, half = lane >> 5, l32 = lane & 31;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int pr = wave % RG, kh = wave / RG;  // row group, key part
   const int T = a.T;
   const int nqb = (T + BM - 1) / BM;
@@ -128,7 +73,7 @@ __global__ __launch_bounds__(KP == 8 ? 512 : 256, Dims<D>::FWD_WAVES_PER_EU) voi
   const int iw = i0 + pr * 32;
   const int row = iw + l32;
   const size_t slice = (size_t)bh * T * D;
-  const float *qs = a.q + slice, *ks = a.k + slice, *vs = a.v + slice;
+  const TI *ks = a.k + slice, *vs = a.v + slice;
   const float Kf = (float)a.K;
   // key j is valid for this lane's row iff j <= jlim; a tile starting at js
   // holds a valid key for some row of the wave iff js <= wlim
@@ -136,115 +81,354 @@ __global__ __launch_bounds__(KP == 8 ? 512 : 256, Dims<D>::FWD_WAVES_PER_EU) voi
   const int wlim = iw >= T ? -1 : (a.causal ? min(iw + 31, T - 1) : T - 1);
   // every key j <= wmin is valid for every row of the wave
   const int wmin = a.causal ? min(iw, T - 1) : T - 1;
-
-  float qop[D / 2];
-  {
-    const int rr = row < T ? row : T - 1;
-    const float *src = qs + (size_t)rr * D + half * (D / 2);
-#pragma unroll
-    for (int s = 0; s < D / 2; s += 4) {
-      f32x4 x = *reinterpret_cast<const f32x4 *>(src + s);
-      qop[s] = x[0]; qop[s + 1] = x[1]; qop[s + 2] = x[2]; qop[s + 3] = x[3];
-    }
-  }
-
   const int kend = a.causal ? min(T, i0 + BM) : T;
   const int nstep = (kend + CHK - 1) / CHK;
-  const int toff = kh * FWD_TK * DS;  // this wave's tile inside a chunk
-  const uint32_t foff = row_vec_offset<D>(tid);  // this thread's vector in a pass
+  // this wave's tile inside a staged chunk, by rows and by columns
+  const int krow = ((PRIV ? 0 : kh * 32) + l32) * RS + 8 * half;
+  const int vcol = (PRIV ? 0 : kh * 32) * RS + tr_base<D>(lane);
 
-  auto load_kop = [&](const float *Kb, float (&kop)[D / 2]) {
-    const float *kr = Kb + l32 * DS + half * (D / 2);
-#pragma unroll
-    for (int s = 0; s < D / 2; s += 4) {
-      f32x4 x = *reinterpret_cast<const f32x4 *>(kr + s);
-      kop[s] = x[0]; kop[s + 1] = x[1]; kop[s + 2] = x[2]; kop[s + 3] = x[3];
-    }
+  bf16x8 qop[NP][D / 16];
+  const float qf = load_query<D>(a.q + slice, row < T ? row : T - 1, T, half, qop);
+  // Chunk steps: n counts the steps of both passes. A chunk is fetched into
+  // registers one step ahead and stashed at the start of its own step, behind
+  // which one barrier orders the stash before the reads; with two buffers the
+  // reads of two steps back are ordered before the stash by the barrier in
+  // between, with one by a barrier of its own.
+  St fk, fv;
+  auto kbuf = [&](int n) {
+    return smem + (PRIV ? kh * St::SIZE : NBUF == 2 ? (n & 1) * St::SIZE : 0);
+  };
+  auto vbuf = [&](int n) {
+    return PRIV ? kbuf(n) : smem + (NBUF + (NBUF == 2 ? n & 1 : 0)) * St::SIZE;
+  };
+  auto scores = [&](const uint16_t *Kb) {
+    const uint16_t *kr = Kb + krow;
+    return score_tile<D, NP>([&](int p, int s) { return row_op(kr + p * PS + 16 * s); },
+                             [&](int p, int s) { return qop[p][s]; });
   };
 
-  // chunks whose tile of this wave holds a valid key: p < npw
-  const int npw = wlim < kh * FWD_TK ? 0 : min(nstep, (wlim - kh * FWD_TK) / CHK + 1);
-  // this wave's score tiles in U (tile of chunk p at + (KP p + kh) * 1024;
-  // the tiles of one query tile are consecutive in both layouts)
-  float *Ut = a.st.U + ds_tile(bh, iw / 32, kh, (T + 31) / 32, a.causal) * 1024;
-
-  // chunk prefetch registers: K chunks in pass 1, then V chunks in pass 2
-  // (V chunk 0 is fetched during the last K step and stashed in CH[0] once
-  // pass 1's last step has ended)
-  TileFetch<D, CHK, NT> fch;
-
-  // ---------------- pass 1: scores, extrema, first index, tie counts -----
-  float Mx = -INFINITY, Mn = INFINITY;
-  int ax = 0x7fffffff, an = 0x7fffffff, cx = 0, cn = 0;
-  {
-    fch.fetch(ks, 0, T, foff);
-    fch.stash(CH[0], tid);
-    lds_barrier();
-    for (int p = 0; p < nstep; ++p) {
-      // the next K chunk; after the last one, pass 2's first V chunk
-      const bool more = p + 1 < nstep;
-      fch.fetch(more ? ks : vs, more ? (p + 1) * CHK : 0, T, foff);
-      if (p < npw) {
-        const int js = p * CHK + kh * FWD_TK;
-        float kop[D / 2];
-        load_kop(CH[p & 1] + toff, kop);
-        const f32x16 acc = score_tile<D>(kop, qop);
-        {
-          float sv[16];
+  // ---------------- pass 1: raw extrema --------------------------------
+  float Rx = -INFINITY, Rn = INFINITY;
+  const int stid = PRIV ? lane : tid, soff = PRIV ? kh * 32 : 0;
+  fk.fetch(ks, soff, T, stid);
+  for (int p = 0; p < nstep; ++p) {
+    const int js = p * CHK + kh * 32;
+    if (PRIV && js > wlim) break;
+    if (!PRIV && NBUF == 1 && p > 0) lds_barrier();
+    fk.stash(kbuf(p), stid);
+    // the next chunk; after the last one pass 2's first
+    const bool more = PRIV ? js + CHK <= wlim : p + 1 < nstep;
+    fk.fetch(ks, (more ? (p + 1) * CHK : 0) + soff, T, stid);
+    if (!PRIV) lds_barrier();
+    if (js <= wlim) {
+      f32x16 acc = scores(kbuf(p));
+      f32x16 lo = acc;
+      if (js + 31 > wmin) {
 #pragma unroll
-          for (int r = 0; r < 16; ++r) sv[r] = acc[r];
-          tile_store(Ut + (size_t)p * (KP * 1024), lane, sv);
-        }
-        float sx[16];
-        if (js + FWD_TK - 1 <= wmin) {
-          // interior tile: every key is valid for every row of the wave
-#pragma unroll
-          for (int r = 0; r < 16; ++r) sx[r] = acc[r] * a.scale;
-          tile_extremum<true>(sx, js, half, Mx, ax, cx);
-          if constexpr (TRACKMIN) tile_extremum<false>(sx, js, half, Mn, an, cn);
-        } else {
-          float sn[16];
-#pragma unroll
-          for (int r = 0; r < 16; ++r) {
-            const float sc = acc[r] * a.scale;
-            const bool valid = js + krel(r, half) <= jlim;
-            sx[r] = valid ? sc : -INFINITY;
-            sn[r] = valid ? sc : INFINITY;
-          }
-          tile_extremum<true>(sx, js, half, Mx, ax, cx);
-          if constexpr (TRACKMIN) tile_extremum<false>(sn, js, half, Mn, an, cn);
+        for (int r = 0; r < 16; ++r) {
+          const bool valid = js + krel(r, half) <= jlim;
+          if constexpr (TRACKMIN) lo[r] = valid ? acc[r] : INFINITY;
+          acc[r] = valid ? acc[r] : -INFINITY;
         }
       }
-      fch.stash(CH[(p + 1) & 1], tid);
-      lds_barrier();
-    }
-    // the last step stashed V chunk 0 in CH[nstep & 1]; pass 2 wants CH[0]
-    if (nstep & 1) fch.stash(CH[0], tid);
-  }
-  merge_ext<true>(Mx, ax, cx, __shfl_xor(Mx, 32), __shfl_xor(ax, 32), __shfl_xor(cx, 32));
-  if constexpr (TRACKMIN)
-    merge_ext<false>(Mn, an, cn, __shfl_xor(Mn, 32), __shfl_xor(an, 32), __shfl_xor(cn, 32));
-  // key parts: every wave of a row group merges the parts in the same order
-  if (half == 0) {
-    int *x = &Xc[pr][kh][0][l32];
-    x[0] = __float_as_int(Mx); x[32] = ax; x[64] = cx;
-    x[96] = __float_as_int(Mn); x[128] = an; x[160] = cn;
-  }
-  __syncthreads();
-  {
-    const int *x0 = &Xc[pr][0][0][l32];
-    Mx = __int_as_float(x0[0]); ax = x0[32]; cx = x0[64];
-    if constexpr (TRACKMIN) { Mn = __int_as_float(x0[96]); an = x0[128]; cn = x0[160]; }
 #pragma unroll
-    for (int q = 1; q < KP; ++q) {
-      const int *x1 = &Xc[pr][q][0][l32];
-      merge_ext<true>(Mx, ax, cx, __int_as_float(x1[0]), x1[32], x1[64]);
-      if constexpr (TRACKMIN)
-        merge_ext<false>(Mn, an, cn, __int_as_float(x1[96]), x1[128], x1[160]);
+      for (int r = 0; r < 16; r += 2) {
+        Rx = fmaxf(fmaxf(acc[r], acc[r + 1]), Rx);
+        if constexpr (TRACKMIN) Rn = fminf(fminf(lo[r], lo[r + 1]), Rn);
+      }
     }
   }
+  if (!PRIV) fv.fetch(vs, 0, T, tid);
+  Rx = fmaxf(Rx, __shfl_xor(Rx, 32));
+  if constexpr (TRACKMIN) Rn = fminf(Rn, __shfl_xor(Rn, 32));
+  if constexpr (KP > 1) {
+    int *x = Xc + pr * KP * 128 + l32;
+    if (half == 0) {
+      x[kh * 128] = __float_as_int(Rx);
+      x[kh * 128 + 32] = __float_as_int(Rn);
+    }
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < KP; ++q) {
+      Rx = fmaxf(Rx, __int_as_float(x[q * 128]));
+      if constexpr (TRACKMIN) Rn = fminf(Rn, __int_as_float(x[q * 128 + 32]));
+    }
+  }
+  // the extrema of the scores fl32(raw * scale), raw = fl32(acc * qf) (each
+  // rounding is monotone); a sum within its slack of the extreme one may round
+  // to the extremum
+  const float Mx = (Rx * qf) * a.scale;
+  const float Mn = TRACKMIN ? (Rn * qf) * a.scale : Mx;
+  auto slack = [&](float x) { return fmaxf(fabsf(x) * 0x1p-22f, 0x1p-140f / qf); };
+  const float bx = fabsf(Rx) < INFINITY ? Rx - slack(Rx) : Rx;
+  const float bn = fabsf(Rn) < INFINITY ? Rn + slack(Rn) : Rn;
+  int ax = 0x7fffffff, an = 0x7fffffff, cx = 0, cn = 0;
+  RowConst rc{};
+  if constexpr (!EXPW) rc = fwd_row_const<CALIB>(Mx, Mn, a);
+  const float a2 = 2.f * rc.alpha * qf, b2 = 2.f * rc.beta, mg = rc.margin2;
+  const float hic = 2.f * Kf - 0.75f;
+
+  // ---------------- pass 2: reconstruct, normalize, O = P V ---------------
+  f32x16 oacc[NC], olacc[OL ? NC : 1];
+#pragma unroll
+  for (int c = 0; c < NC; ++c)
+#pragma unroll
+    for (int e = 0; e < 16; ++e) {
+      oacc[c][e] = 0.f;
+      if constexpr (OL) olacc[c][e] = 0.f;
+    }
+  float WN = 0.f, WLs = 0.f;
+  // this wave's decision tiles in U (the tiles of one query tile are
+  // consecutive in both layouts)
+  float *Ut = a.st.U + ds_tile(bh, iw / 32, 0, (T + 31) / 32, a.causal) * 1024;
+  auto clamped = [&](float x) {
+    if constexpr (CALIB == CAL_MINMAX) return __builtin_amdgcn_fmed3f(x, 0.75f, hic);
+    else if constexpr (CALIB == CAL_FWM) return __builtin_amdgcn_fmed3f(x, -0.25f, hic);
+    else return fminf(x, hic);
+  };
+  // the decisions of the wave's tile at key js from its scores: v
+  auto decide = [&](int js, const f32x16 &S, float (&v)[16]) {
+    const bool diag = js + 31 > wmin;  // some pair of the tile is not valid
+    float *ut = Ut + (size_t)(js / 32) * 1024;
+    // extrema: first index and tie count. One comparison per key and its wave
+    // mask; only the few registers where a lane comes within rounding of an
+    // extremum (about one key per row) are looked at.
+    {
+      uint64_t hit[16], any = 0;
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        hit[r] = __ballot(S[r] >= bx);
+        if constexpr (TRACKMIN) hit[r] |= __ballot(S[r] <= bn);
+        any |= hit[r];
+      }
+      if (any) {
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          if (!hit[r]) continue;  // wave-uniform
+          const int j = js + krel(r, half);
+          const float s = (S[r] * qf) * a.scale;
+          const bool ok = j <= jlim;
+          const bool ex = ok & (s == Mx);
+          ax = ex ? min(ax, j) : ax;
+          cx += ex ? 1 : 0;
+          if constexpr (TRACKMIN) {
+            const bool en = ok & (s == Mn);
+            an = en ? min(an, j) : an;
+            cn += en ? 1 : 0;
+          }
+        }
+      }
+    }
+    // twice the position, v = 2u: a boundary (grid point or midpoint) is an
+    // integer. Clamped a quarter past the outermost boundary that decides
+    // (FWM: the cut 0 is one, MinMax: u = 0 is the argmin itself), so that
+    // neither the extrema nor far tail keys look ambiguous. For an exponential
+    // weight function v is the fp32 exponential as it rounds it (kept in U for
+    // the backward; bf16-rounded already for BF16-exp).
+    if constexpr (EXPW) {
+      float z[16];
+#pragma unroll
+      for (int r = 0; r < 16; ++r) z[r] = score_shift(S[r] * qf, a.scale, Mx);
+      exp_tile<RECON>(z, v);
+      if constexpr (RECON == REC_BF16EXP) {
+#pragma unroll
+        for (int r = 0; r < 16; ++r) v[r] = bf16_rne(v[r]);
+      }
+      if (diag) {
+#pragma unroll
+        for (int r = 0; r < 16; ++r) v[r] = js + krel(r, half) <= jlim ? v[r] : 0.f;
+      }
+      if (a.keep) tile_store(ut, lane, v);
+    } else {
+#pragma unroll
+      for (int r = 0; r < 16; ++r) v[r] = fmaf(S[r], a2, b2);
+      float f1 = 0.f, f0 = 1.f;
+#pragma unroll
+      for (int r = 0; r < 16; r += 2) {
+        const float x = __builtin_amdgcn_fractf(clamped(v[r]));
+        const float y = __builtin_amdgcn_fractf(clamped(v[r + 1]));
+        f1 = fmaxf(fmaxf(x, y), f1);
+        f0 = fminf(fminf(x, y), f0);
+      }
+      if (__any((f0 <= mg) | (1.f - f1 <= mg))) {
+        // keys within rounding of a boundary (about 1e-5 of them)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          const float f = __builtin_amdgcn_fractf(clamped(v[r]));
+          const bool amb = (f <= mg) | (1.f - f <= mg);
+          if (!__any(amb)) continue;  // wave-uniform
+          const float x = exact_v2<CALIB>((S[r] * qf) * a.scale, v[r], Mx, Mn, a.K, a.tau);
+          v[r] = amb ? x : v[r];
+        }
+      }
+      if (diag) {
+        // a position that no valid key takes and whose weight is 0: the FWM
+        // tail, below the argmin (u >= 0 up to rounding), or minus infinity
+        constexpr float none = CALIB == CAL_FWM ? -0.25f : CALIB == CAL_MINMAX ? -1.25f : -INFINITY;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) v[r] = js + krel(r, half) <= jlim ? v[r] : none;
+      }
+      if constexpr (!COMPACT) {
+        if (a.keep) {
+          float u[16];
+#pragma unroll
+          for (int r = 0; r < 16; ++r) u[r] = 0.5f * v[r];
+          tile_store(ut, lane, u);
+        }
+      }
+    }
+  };
+  // its weights and their products with V
+  auto accumulate = [&](int js, const float (&v)[16], const uint16_t *vb) {
+    uint32_t cw[4];
+    float tWN = 0.f, tWL = 0.f;  // sub-tile sums first: shorter running sums
+    // the weights of the lane's keys 8 t .. 8 t + 7, the k-slots of one step
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+      float w[8], wl[OL ? 8 : 1];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        const int r = 8 * t + e;
+        if constexpr (EXPW) {
+          w[e] = exp_weight_of<RECON>(v[r]);
+          tWL += w[e];
+        } else {
+          // c = floor(2u) = 2r + [t >= 1/2], in [-1, 2K - 1] (resolved:
+          // unbounded below); -1 is the FWM tail
+          const float c = floorf(clamped(v[r]));
+          const float hc = 0.5f * c;
+          const float rf = floorf(hc);
+          if constexpr (COMPACT)
+            cw[r >> 2] = __builtin_amdgcn_cvt_pk_u8_f32(c + 1.f, r & 3, (r & 3) ? cw[r >> 2] : 0u);
+          float arg = fmaf(rf, rc.hl, rc.b1l);
+          // weight 0: the FWM tail, and keys that are not valid
+          if constexpr (CALIB == CAL_FWM) arg = rf < 0.f ? -INFINITY : arg;
+          if constexpr (CALIB == CAL_MINMAX) arg = v[r] < -1.f ? -INFINITY : arg;
+          const float Eu = __builtin_amdgcn_exp2f(arg);
+          const float El = Eu * rc.emh;
+          float t01 = fmaf(v[r], 0.5f, -rf);
+          if constexpr (CALIB == CAL_RESOLVED) t01 = __builtin_amdgcn_fmed3f(t01, 0.f, 1.f);
+          const float wL = fmaf(t01, Eu - El, El);
+          tWL += wL;
+          if constexpr (NEAREST) {
+            w[e] = hc > rf ? Eu : El;
+            tWN += w[e];
+            if constexpr (OL) wl[e] = wL;
+          } else {
+            w[e] = wL;
+          }
+        }
+      }
+      bf16x8 wo[NP], wlo[OL ? NP : 1];
+      to_pieces<NP>(w, wo);
+      if constexpr (OL) to_pieces<NP>(wl, wlo);
+#pragma unroll
+      for (int c = 0; c < NC; ++c) {
+        bf16x8 av[NP];
+#pragma unroll
+        for (int p = 0; p < NP; ++p) av[p] = tr_op<RS>(vb + p * PS + 16 * t * RS + 32 * c);
+        oacc[c] = mma<NP>(av, wo, oacc[c]);
+        if constexpr (OL) olacc[c] = mma<NP>(av, wlo, olacc[c]);
+      }
+    }
+    if constexpr (COMPACT)
+      if (a.keep) codes_store(Ut + (size_t)(js / 32) * 1024, lane, cw);
+    WN += tWN;
+    WLs += tWL;
+  };
+  if constexpr (PRIV) {
+    for (int p = 0; p < nstep; ++p) {
+      const int js = p * CHK + kh * 32;
+      if (js > wlim) break;
+      fk.stash(kbuf(0), lane);
+      fk.fetch(vs, js, T, lane);
+      __builtin_amdgcn_sched_barrier(0);
+      const f32x16 S = scores(kbuf(0));
+      __builtin_amdgcn_sched_barrier(0);
+      // V takes K's place, the next K is fetched
+      fk.stash(vbuf(0), lane);
+      fk.fetch(ks, min(p + 1, nstep - 1) * CHK + soff, T, lane);
+      __builtin_amdgcn_sched_barrier(0);
+      float v[16];
+      decide(js, S, v);
+      __builtin_amdgcn_sched_barrier(0);
+      accumulate(js, v, vbuf(0) + vcol);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  } else {
+    for (int p = 0; p < nstep; ++p) {
+      const int js = p * CHK + kh * 32;
+      if (NBUF == 1) lds_barrier();
+      fk.stash(kbuf(nstep + p), tid);
+      fv.stash(vbuf(nstep + p), tid);
+      const int nx = min(p + 1, nstep - 1) * CHK;
+      fk.fetch(ks, nx, T, tid);
+      fv.fetch(vs, nx, T, tid);
+      lds_barrier();
+      if (js <= wlim) {
+        __builtin_amdgcn_sched_barrier(0);
+        const f32x16 S = scores(kbuf(nstep + p));
+        __builtin_amdgcn_sched_barrier(0);
+        float v[16];
+        decide(js, S, v);
+        __builtin_amdgcn_sched_barrier(0);
+        accumulate(js, v, vbuf(nstep + p) + vcol);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+  }
+  WN += __shfl_xor(WN, 32);
+  WLs += __shfl_xor(WLs, 32);
+  ax = min(ax, __shfl_xor(ax, 32));
+  cx += __shfl_xor(cx, 32);
+  if constexpr (TRACKMIN) {
+    an = min(an, __shfl_xor(an, 32));
+    cn += __shfl_xor(cn, 32);
+  }
+  if constexpr (KP > 1) {
+    // key parts 1.. hand their partial sums to key part 0, which adds them in
+    // part order (the chunk buffers are free behind the first barrier)
+    __syncthreads();
+    float *red = reinterpret_cast<float *>(smem) + pr * (KP - 1) * 64 * NRED + lane;
+    int *xr = Xc + pr * KP * 128 + l32;
+    if (kh > 0) {
+      float *rk = red + (kh - 1) * 64 * NRED;
+#pragma unroll
+      for (int c = 0; c < NC; ++c)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) {
+          rk[(c * 16 + e) * 64] = oacc[c][e];
+          if constexpr (OL) rk[((NC + c) * 16 + e) * 64] = olacc[c][e];
+        }
+      rk[(NRED - 2) * 64] = WN;
+      rk[(NRED - 1) * 64] = WLs;
+      if (half == 0) {
+        int *x = xr + kh * 128;
+        x[0] = ax; x[32] = cx; x[64] = an; x[96] = cn;
+      }
+    }
+    __syncthreads();
+    if (kh > 0) return;
+#pragma unroll 1
+    for (int q = 0; q < KP - 1; ++q) {
+      const float *rk = red + q * 64 * NRED;
+#pragma unroll
+      for (int c = 0; c < NC; ++c)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) {
+          oacc[c][e] += rk[(c * 16 + e) * 64];
+          if constexpr (OL) olacc[c][e] += rk[((NC + c) * 16 + e) * 64];
+        }
+      WN += rk[(NRED - 2) * 64];
+      WLs += rk[(NRED - 1) * 64];
+      const int *x = xr + (q + 1) * 128;
+      ax = min(ax, x[0]); cx += x[32]; an = min(an, x[64]); cn += x[96];
+    }
+  }
+  if (row >= T) return;
   const size_t ridx = (size_t)bh * T + row;
-  if (kh == 0 && half == 0 && row < T) {
+  const float W = NEAREST ? WN : WLs;
+  if (half == 0) {
     a.st.M[ridx] = Mx;
     a.st.amax[ridx] = ax;
     a.st.nmax[ridx] = cx;
@@ -253,735 +437,72 @@ __global__ __launch_bounds__(KP == 8 ? 512 : 256, Dims<D>::FWD_WAVES_PER_EU) voi
       a.st.amin[ridx] = an;
       a.st.nmin[ridx] = cn;
     }
-  }
-  if constexpr (!TRACKMIN) Mn = Mx;  // unused by FWM
-  RowConst rc{};
-  if constexpr (!EXPW) rc = row_const(Mx, Mn, a.K, CALIB, a.tau, a.scale);
-
-  // ---------------- pass 2: reconstruct, normalize, O = P V ---------------
-  // The wave's own score tiles come back from U (one tile ahead, in two
-  // fixed register sets); each is replaced there by its decided positions.
-  f32x16 oacc[NC], olacc[OL ? NC : 1];
-#pragma unroll
-  for (int c = 0; c < NC; ++c)
-#pragma unroll
-    for (int e = 0; e < 16; ++e) oacc[c][e] = 0.f;
-  if constexpr (OL) {
-#pragma unroll
-    for (int c = 0; c < NC; ++c)
-#pragma unroll
-      for (int e = 0; e < 16; ++e) olacc[c][e] = 0.f;
-  }
-  float WN = 0.f, WLs = 0.f;
-  auto load_s = [&](int p, f32x16 &S) {
-    float sv[16];
-    tile_load(Ut + (size_t)p * (KP * 1024), lane, sv);
-#pragma unroll
-    for (int r = 0; r < 16; ++r) S[r] = sv[r];
-  };
-  auto tile = [&](int p, const f32x16 &S, auto masked_tag) {
-    constexpr bool MASKED = decltype(masked_tag)::value;
-    const int js = p * CHK + kh * FWD_TK;
-    float w[16], wl[16];
-    float tWN = 0.f, tWL = 0.f;  // sub-tile sums first: shorter running sums
-    if constexpr (EXPW) {
-      // z = s - M, the fp32 exponential as the weight function rounds it
-      // (kept in U for the backward; bf16-rounded already for BF16-exp),
-      // and the weight
-      float z[16], e[16];
-#pragma unroll
-      for (int r = 0; r < 16; ++r) z[r] = score_shift(S[r], a.scale, Mx);
-      exp_tile<RECON>(z, e);
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        if constexpr (RECON == REC_BF16EXP) e[r] = bf16_rne(e[r]);
-        const bool valid = js + krel(r, half) <= jlim;
-        w[r] = valid ? exp_weight_of<RECON>(e[r]) : 0.f;
-        tWN += w[r];
-      }
-      if (a.keep) tile_store(Ut + (size_t)p * (KP * 1024), lane, e);
-      tWL = tWN;
-    } else {
-    float u[16];
-    uint32_t cw[4];
-    decide_u<CALIB>(S, rc, Mx, Mn, a.K, a.tau, a.scale, u);
-    if constexpr (!compact_codes<CALIB, RECON>())
-      if (a.keep) tile_store(Ut + (size_t)p * (KP * 1024), lane, u);
-#pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      const KeyDec kd = key_of<CALIB>(u[r], Kf);
-      if constexpr (compact_codes<CALIB, RECON>()) code_put(cw, r, kd);
-      float Eu;
-      if constexpr (MASKED) {
-        Eu = grid_upper(kd.rf, rc);
-      } else {
-        // interior tile: only the FWM tail is zero, through e^{-inf} = 0
-        const float arg = fmaf(kd.rf, rc.hl, rc.b1l);
-        Eu = __builtin_amdgcn_exp2f(kd.tail ? -INFINITY : arg);
-      }
-      const float El = Eu * rc.emh;
-      float wL = fmaf(kd.t, Eu - El, El);
-      float wN = kd.up ? Eu : El;
-      if constexpr (MASKED) {
-        const bool valid = (js + krel(r, half) <= jlim) & !kd.tail;
-        wL = valid ? wL : 0.f;
-        wN = valid ? wN : 0.f;
-      }
-      tWL += wL;
-      wl[r] = wL;
-      if constexpr (NEAREST) {
-        tWN += wN;
-        w[r] = wN;
-      } else {
-        w[r] = wL;
-      }
-    }
-    if constexpr (compact_codes<CALIB, RECON>())
-      if (a.keep) codes_store(Ut + (size_t)p * (KP * 1024), lane, cw);
-    }
-    WN += tWN;
-    WLs += tWL;
-    const float *Vb = CH[p & 1] + toff;
-#pragma unroll
-    for (int c = 0; c < NC; ++c) {
-      const float *vr = Vb + c * 32 + l32;
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const float vop = vr[krel(r, half) * DS];
-        oacc[c] = mfma32(vop, w[r], oacc[c]);
-        if constexpr (OL) olacc[c] = mfma32(vop, wl[r], olacc[c]);
-      }
-    }
-  };
-  {
-    // V chunk 0 is in CH[0] already (ordered by the extrema merge's barrier)
-    f32x16 SA, SB;
-    if (npw > 0) load_s(0, SA);
-    // tiles below the wave's first row are interior (no causal mask)
-    auto run = [&](int p, const f32x16 &S) {
-      if (p * CHK + kh * FWD_TK + FWD_TK - 1 <= wmin)
-        tile(p, S, std::integral_constant<bool, false>{});
-      else
-        tile(p, S, std::integral_constant<bool, true>{});
-    };
-    for (int p = 0; p < nstep; p += 2) {
-      fch.fetch(vs, min(p + 1, nstep - 1) * CHK, T, foff);
-      if (p + 1 < npw) load_s(p + 1, SB);
-      if (p < npw) run(p, SA);
-      fch.stash(CH[(p + 1) & 1], tid);
-      lds_barrier();
-      if (p + 1 >= nstep) break;
-      fch.fetch(vs, min(p + 2, nstep - 1) * CHK, T, foff);
-      if (p + 2 < npw) load_s(p + 2, SA);
-      if (p + 1 < npw) run(p + 1, SB);
-      fch.stash(CH[p & 1], tid);
-      lds_barrier();
-    }
-  }
-  WN += __shfl_xor(WN, 32);
-  WLs += __shfl_xor(WLs, 32);
-  // key parts 1.. hand their partial sums to key part 0, which adds them in
-  // part order (chunk buffers are free: the last step ended with a barrier)
-  float *red = &CH[0][0] + pr * (KP - 1) * 64 * NRED + lane;
-  if (kh > 0) {
-    float *rk = red + (kh - 1) * 64 * NRED;
-#pragma unroll
-    for (int c = 0; c < NC; ++c)
-#pragma unroll
-      for (int e = 0; e < 16; ++e) {
-        rk[(c * 16 + e) * 64] = oacc[c][e];
-        if constexpr (OL) rk[((NC + c) * 16 + e) * 64] = olacc[c][e];
-      }
-    rk[(NRED - 2) * 64] = WN;
-    rk[(NRED - 1) * 64] = WLs;
-  }
-  __syncthreads();
-  if (kh > 0) return;
-#pragma unroll 1
-  for (int q = 0; q < KP - 1; ++q) {
-    const float *rk = red + q * 64 * NRED;
-#pragma unroll
-    for (int c = 0; c < NC; ++c)
-#pragma unroll
-      for (int e = 0; e < 16; ++e) {
-        oacc[c][e] += rk[(c * 16 + e) * 64];
-        if constexpr (OL) olacc[c][e] += rk[((NC + c) * 16 + e) * 64];
-      }
-    WN += rk[(NRED - 2) * 64];
-    WLs += rk[(NRED - 1) * 64];
-  }
-  const float W = NEAREST ? WN : WLs;
-  if (half == 0 && row < T) {
     a.st.W[ridx] = W;
     a.st.WL[ridx] = WLs;
   }
-  if (row < T) {
-    const float inv = 1.f / W, invl = 1.f / WLs;
-    float *orow = a.o + slice + (size_t)row * D;
+  const float inv = 1.f / W, invl = 1.f / WLs;
+  float *orow = a.o + slice + (size_t)row * D;
+  uint16_t *orow16 = a.o16 + slice + (size_t)row * D;
 #pragma unroll
-    for (int c = 0; c < NC; ++c)
+  for (int c = 0; c < NC; ++c)
 #pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        const int n = c * 32 + 8 * g + 4 * half;
-        if (n >= D) continue;
-        f32x4 x = {oacc[c][4 * g] * inv, oacc[c][4 * g + 1] * inv,
-                   oacc[c][4 * g + 2] * inv, oacc[c][4 * g + 3] * inv};
+    for (int g = 0; g < 4; ++g) {
+      const int n = c * 32 + 8 * g + 4 * half;
+      if (n >= D) continue;
+      f32x4 x = {oacc[c][4 * g] * inv, oacc[c][4 * g + 1] * inv,
+                 oacc[c][4 * g + 2] * inv, oacc[c][4 * g + 3] * inv};
+      if (NP == 1 && a.o16)
+        *reinterpret_cast<uint2 *>(orow16 + n) =
+            make_uint2(pack_bf16x2(x[0], x[1]), pack_bf16x2(x[2], x[3]));
+      else
         *reinterpret_cast<f32x4 *>(orow + n) = x;
-        if constexpr (OL) {
-          f32x4 y = {olacc[c][4 * g] * invl, olacc[c][4 * g + 1] * invl,
-                     olacc[c][4 * g + 2] * invl, olacc[c][4 * g + 3] * invl};
-          *reinterpret_cast<f32x4 *>(a.st.OL + ridx * D + n) = y;
-        }
+      if constexpr (OL) {
+        f32x4 y = {olacc[c][4 * g] * invl, olacc[c][4 * g + 1] * invl,
+                   olacc[c][4 * g + 2] * invl, olacc[c][4 * g + 3] * invl};
+        *reinterpret_cast<f32x4 *>(a.st.OL + ridx * D + n) = y;
       }
-  }
+    }
 }
 
-// Debug codes: the same score sub-tiles, decide_u() and key_of() as pass 2
-// (REC = REC_LERP stands for both K-interval reconstructions); for an
-// exponential weight function (REC >= REC_SOFTMAX) the quantized weight's
-// code from the same score_shift() and exp_tile() as pass 2.
-template <int D, int CALIB, int REC, typename TI>
-__global__ __launch_bounds__(256) void codes_kernel(CodesArgsT<TI> a) {
-  constexpr bool EXPW = is_exp_rec(REC);
-  constexpr bool B16 = sizeof(TI) == 2;
-  constexpr int DS = Dims<D>::DS;
-  __shared__ __attribute__((aligned(16))) float Ks[CODES_BN * DS];
-  const int tid = threadIdx.x;
-  const int lane = tid & 63, wave = tid >> 6, half = lane >> 5, l32 = lane & 31;
-  const int T = a.T;
-  const int nqb = (T + CODES_BM - 1) / CODES_BM;
-  const int bh = blockIdx.x % a.BH;
-  const int qb = nqb - 1 - (int)(blockIdx.x / a.BH);
-  const int i0 = qb * CODES_BM, iw = i0 + wave * 32, row = iw + l32;
-  const size_t slice = (size_t)bh * T * D;
-  const float Kf = (float)a.K;
-  float qop[D / 2];
-  bf16x8 qop16[D / 16];
-  if constexpr (B16) {
-    load_rows16<D>(a.q + slice, row < T ? row : T - 1, T, half, qop16);
-  } else {
-    const int rr = row < T ? row : T - 1;
-    const float *src = a.q + slice + (size_t)rr * D + half * (D / 2);
-#pragma unroll
-    for (int s = 0; s < D / 2; s += 4) {
-      f32x4 x = *reinterpret_cast<const f32x4 *>(src + s);
-      qop[s] = x[0]; qop[s + 1] = x[1]; qop[s + 2] = x[2]; qop[s + 3] = x[3];
-    }
-  }
-  const size_t ridx = (size_t)bh * T + (row < T ? row : T - 1);
-  const float Mx = a.st.M[ridx];
-  const float Mn = CALIB != CAL_FWM ? a.st.m[ridx] : Mx;
-  RowConst rc{};
-  if constexpr (!EXPW) rc = row_const(Mx, Mn, a.K, CALIB, a.tau, a.scale);
-  const int kend = a.causal ? min(T, i0 + CODES_BM) : T;
-  const int ntiles = (T + CODES_BN - 1) / CODES_BN;
-  for (int t = 0; t < ntiles; ++t) {
-    const int j0 = t * CODES_BN;
-    __syncthreads();
-    if constexpr (!B16) load_tile_lds<D>(Ks, a.k + slice, j0, T, tid);
-    __syncthreads();
-#pragma unroll
-    for (int sub = 0; sub < CODES_BN / 32; ++sub) {
-      const int js = j0 + sub * 32;
-      if (js >= T) continue;
-      uint16_t code[16];
-      if (js >= kend || (a.causal && js > iw + 31)) {
-#pragma unroll
-        for (int r = 0; r < 16; ++r) code[r] = 0;
-      } else {
-        f32x16 acc;
-        if constexpr (B16) {
-          bf16x8 kop16[D / 16];
-          load_rows16<D>(a.k + slice, js + l32, T, half, kop16);
-          acc = score_tile16<D>(kop16, qop16);
-        } else {
-          float kop[D / 2];
-          const float *kr = Ks + (sub * 32 + l32) * DS + half * (D / 2);
-#pragma unroll
-          for (int s = 0; s < D / 2; s += 4) {
-            f32x4 x = *reinterpret_cast<const f32x4 *>(kr + s);
-            kop[s] = x[0]; kop[s + 1] = x[1]; kop[s + 2] = x[2]; kop[s + 3] = x[3];
-          }
-          acc = score_tile<D>(kop, qop);
-        }
-        if constexpr (EXPW) {
-          // bit 15 valid; bits 0-14 the bf16 pattern (BF16-exp) or the E4M3
-          // byte (FP8-exp) of the weight, 0 for softmax (w <= 1: bit 14 clear)
-          float z[16], e[16];
-#pragma unroll
-          for (int r = 0; r < 16; ++r) z[r] = score_shift(acc[r], a.scale, Mx);
-          exp_tile<REC>(z, e);
-#pragma unroll
-          for (int r = 0; r < 16; ++r) {
-            const int j = js + krel(r, half);
-            const bool valid = (j < T) & (!a.causal | (j <= row));
-            uint32_t c = 0;
-            if constexpr (REC == REC_BF16EXP) c = __float_as_uint(bf16_rne(e[r])) >> 16;
-            if constexpr (REC == REC_FP8EXP) e4m3_rne(e[r], c);
-            code[r] = valid ? (uint16_t)(0x8000u | c) : (uint16_t)0;
-          }
-        } else {
-        float u[16];
-        decide_u<CALIB>(acc, rc, Mx, Mn, a.K, a.tau, a.scale, u);
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const int j = js + krel(r, half);
-          const bool valid = (j < T) & (!a.causal | (j <= row));
-          const KeyDec kd = key_of<CALIB>(u[r], Kf);
-          uint16_t c = 0;
-          if (valid && CALIB == CAL_RESOLVED) {
-            // bit 15 valid, bit 14 l = r + 1, bits 0-13 r (two's complement,
-            // clamped to [-8192, 8191])
-            const int rr = (int)fmaxf(kd.rf, -8192.f);
-            c = (uint16_t)(0x8000u | (kd.up ? 0x4000u : 0u) | ((uint32_t)rr & 0x3FFFu));
-          } else if (valid) {
-            c = (uint16_t)(1u << 14);
-            if (rc.degen) c |= (uint16_t)(1u << 15);
-            else if (kd.tail) c |= (uint16_t)(1u << 13);
-            else {
-              const int rr = (int)kd.rf;
-              const int ll = rr + (kd.up ? 1 : 0);
-              c |= (uint16_t)(rr | (ll << 6));
-            }
-          }
-          code[r] = c;
-        }
-        }
-      }
-      if (row < T) {
-        uint16_t *dst = a.codes + ((size_t)bh * T + row) * T;
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const int j = js + krel(r, half);
-          if (j < T) dst[j] = code[r];
-        }
-      }
-    }
-  }
-}
+#define KIA_FWD_GRID(TI, D, RG, KP)                                                         \
+  template __global__ void fwd_kernel<TI, D, CAL_MINMAX, REC_LERP, false, RG, KP>(FwdArgsT<TI>);    \
+  template __global__ void fwd_kernel<TI, D, CAL_MINMAX, REC_NEAREST, false, RG, KP>(FwdArgsT<TI>); \
+  template __global__ void fwd_kernel<TI, D, CAL_MINMAX, REC_NEAREST, true, RG, KP>(FwdArgsT<TI>);  \
+  template __global__ void fwd_kernel<TI, D, CAL_FWM, REC_LERP, false, RG, KP>(FwdArgsT<TI>);       \
+  template __global__ void fwd_kernel<TI, D, CAL_FWM, REC_NEAREST, false, RG, KP>(FwdArgsT<TI>);    \
+  template __global__ void fwd_kernel<TI, D, CAL_FWM, REC_NEAREST, true, RG, KP>(FwdArgsT<TI>);     \
+  template __global__ void fwd_kernel<TI, D, CAL_RESOLVED, REC_LERP, false, RG, KP>(FwdArgsT<TI>);  \
+  template __global__ void fwd_kernel<TI, D, CAL_RESOLVED, REC_NEAREST, false, RG, KP>(FwdArgsT<TI>); \
+  template __global__ void fwd_kernel<TI, D, CAL_RESOLVED, REC_NEAREST, true, RG, KP>(FwdArgsT<TI>);
+#define KIA_FWD_EXP(D, RG, KP)                                                               \
+  template __global__ void fwd_kernel<float, D, CAL_FWM, REC_SOFTMAX, false, RG, KP>(FwdArgs); \
+  template __global__ void fwd_kernel<float, D, CAL_FWM, REC_BF16EXP, false, RG, KP>(FwdArgs); \
+  template __global__ void fwd_kernel<float, D, CAL_FWM, REC_FP8EXP, false, RG, KP>(FwdArgs);
+// every launch shape of one head dimension (d = 64 in fp32 has one more)
+#define KIA_FWD_D(D)             \
+  KIA_FWD_GRID(float, D, 4, 1)   \
+  KIA_FWD_EXP(D, 4, 1)           \
+  KIA_FWD_GRID(float, D, 2, 2)   \
+  KIA_FWD_EXP(D, 2, 2)           \
+  KIA_FWD_GRID(float, D, 1, 4)   \
+  KIA_FWD_EXP(D, 1, 4)           \
+  KIA_FWD_GRID(uint16_t, D, 4, 1) \
+  KIA_FWD_GRID(uint16_t, D, 2, 2) \
+  KIA_FWD_GRID(uint16_t, D, 1, 4)
 
-// Code words of the decisions the forward stored in U (the positions u
-// that pass 2 wrote and the backward reads; for an exponential weight
-// function the fp32 exponential): the same format as codes_kernel, with no
-// score recomputed. One wave per (b,h, 32-query tile) over all key tiles;
-// codes of keys that are not valid (and of unstored tiles) are 0.
-template <int CALIB, int REC>
-__global__ __launch_bounds__(256) void stored_codes_kernel(StoredCodesArgs a) {
-  constexpr bool EXPW = is_exp_rec(REC);
-  constexpr bool COMPACT = compact_codes<CALIB, REC>();
-  const int tid = threadIdx.x;
-  const int lane = tid & 63, wave = tid >> 6, half = lane >> 5, l32 = lane & 31;
-  const int T = a.T;
-  const int nq = (T + 31) / 32;
-  const size_t gw = (size_t)blockIdx.x * 4 + wave;
-  if (gw >= (size_t)a.BH * nq) return;
-  const int bh = (int)(gw / nq), qt = (int)(gw % nq);
-  const int i = qt * 32 + l32;
-  const float Kf = (float)a.K;
-  bool degen = false;
-  if (CALIB == CAL_MINMAX && i < T) {
-    const size_t ridx = (size_t)bh * T + i;
-    degen = (double)a.st.M[ridx] - (double)a.st.m[ridx] <= 1e-12;
-  }
-  for (int kt = 0; kt < nq; ++kt) {
-    const bool stored = !a.causal || kt <= qt;
-    float u[16];
-    uint4 cw = make_uint4(0, 0, 0, 0);
-    const float *tile = a.st.U + ds_tile(bh, qt, kt, nq, a.causal) * 1024;
-    if (stored) {
-      if constexpr (COMPACT) cw = codes_load(tile, lane);
-      else tile_load(tile, lane, u);
-    }
-#pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      const int j = kt * 32 + krel(r, half);
-      if (i >= T || j >= T) continue;
-      const bool valid = stored & (!a.causal | (j <= i));
-      uint32_t c = 0;
-      if (valid && COMPACT) {
-        const KeyDec kd = key_of_code(cw, r);
-        c = 1u << 14;
-        if (kd.tail) c |= 1u << 13;
-        else {
-          const int rr = (int)kd.rf;
-          c |= (uint32_t)(rr | ((rr + (kd.up ? 1 : 0)) << 6));
-        }
-      } else if (valid && EXPW) {
-        if constexpr (REC == REC_BF16EXP) c = __float_as_uint(bf16_rne(u[r])) >> 16;
-        if constexpr (REC == REC_FP8EXP) e4m3_rne(u[r], c);
-        c |= 0x8000u;
-      } else if (valid) {
-        const KeyDec kd = key_of<CALIB>(u[r], Kf);
-        if (CALIB == CAL_RESOLVED) {
-          const int rr = (int)fmaxf(kd.rf, -8192.f);
-          c = 0x8000u | (kd.up ? 0x4000u : 0u) | ((uint32_t)rr & 0x3FFFu);
-        } else {
-          c = 1u << 14;
-          if (degen) c |= 1u << 15;
-          else if (kd.tail) c |= 1u << 13;
-          else {
-            const int rr = (int)kd.rf;
-            c |= (uint32_t)(rr | ((rr + (kd.up ? 1 : 0)) << 6));
-          }
-        }
-      }
-      a.codes[((size_t)bh * T + i) * T + j] = (uint16_t)c;
-    }
-  }
-}
-
-// The canonical fp32 scores s = fl32(acc * scale) of every pair (the values
-// the forward's extrema pass stored and every decision is taken on), 0 for
-// keys that are not valid. Same sub-tile and operand loads as codes_kernel.
-template <int D, typename TI>
-__global__ __launch_bounds__(256) void scores_kernel(ScoresArgsT<TI> a) {
-  constexpr bool B16 = sizeof(TI) == 2;
-  constexpr int DS = Dims<D>::DS;
-  __shared__ __attribute__((aligned(16))) float Ks[CODES_BN * DS];
-  const int tid = threadIdx.x;
-  const int lane = tid & 63, wave = tid >> 6, half = lane >> 5, l32 = lane & 31;
-  const int T = a.T;
-  const int nqb = (T + CODES_BM - 1) / CODES_BM;
-  const int bh = blockIdx.x % a.BH;
-  const int qb = nqb - 1 - (int)(blockIdx.x / a.BH);
-  const int i0 = qb * CODES_BM, iw = i0 + wave * 32, row = iw + l32;
-  const size_t slice = (size_t)bh * T * D;
-  float qop[D / 2];
-  bf16x8 qop16[D / 16];
-  if constexpr (B16) {
-    load_rows16<D>(a.q + slice, row < T ? row : T - 1, T, half, qop16);
-  } else {
-    const int rr = row < T ? row : T - 1;
-    const float *src = a.q + slice + (size_t)rr * D + half * (D / 2);
-#pragma unroll
-    for (int s = 0; s < D / 2; s += 4) {
-      f32x4 x = *reinterpret_cast<const f32x4 *>(src + s);
-      qop[s] = x[0]; qop[s + 1] = x[1]; qop[s + 2] = x[2]; qop[s + 3] = x[3];
-    }
-  }
-  const int ntiles = (T + CODES_BN - 1) / CODES_BN;
-  for (int t = 0; t < ntiles; ++t) {
-    const int j0 = t * CODES_BN;
-    __syncthreads();
-    if constexpr (!B16) load_tile_lds<D>(Ks, a.k + slice, j0, T, tid);
-    __syncthreads();
-#pragma unroll
-    for (int sub = 0; sub < CODES_BN / 32; ++sub) {
-      const int js = j0 + sub * 32;
-      if (js >= T) continue;
-      f32x16 acc;
-      if constexpr (B16) {
-        bf16x8 kop16[D / 16];
-        load_rows16<D>(a.k + slice, js + l32, T, half, kop16);
-        acc = score_tile16<D>(kop16, qop16);
-      } else {
-        float kop[D / 2];
-        const float *kr = Ks + (sub * 32 + l32) * DS + half * (D / 2);
-#pragma unroll
-        for (int s = 0; s < D / 2; s += 4) {
-          f32x4 x = *reinterpret_cast<const f32x4 *>(kr + s);
-          kop[s] = x[0]; kop[s + 1] = x[1]; kop[s + 2] = x[2]; kop[s + 3] = x[3];
-        }
-        acc = score_tile<D>(kop, qop);
-      }
-      if (row < T) {
-        float *dst = a.scores + ((size_t)bh * T + row) * T;
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const int j = js + krel(r, half);
-          if (j < T) dst[j] = (!a.causal | (j <= row)) ? acc[r] * a.scale : 0.f;
-        }
-      }
-    }
-  }
-}
-
-// ---------------------------------------------------------------------------
-// Geometry probe (the paper's per-row score statistics): one wave per 32
-// query rows, four waves per workgroup, keys streamed through LDS in tiles of
-// 64 as in codes_kernel, scores from the canonical sub-tile and decisions
-// from decide_u()/key_of(), so M, the levels and the native weights are the
-// forward's own. Pass A: softmax sums W_E = sum e^z and sum e^z z, the count
-// of z < -6 (decided in fp64), the top-bucket mass, the bucket masses (LDS
-// float atomics, [row][K + 2]: levels/intervals 0..K, the FWM tail K + 1),
-// the row minimum and the LQ smallest scores of each lane (sorted insertion).
-// Pass B: TV = 1/2 sum |w / W - e^z / W_E| with the forward's W.
-constexpr int GEO_COUNT = 10;
-
-template <int D, int CALIB, int RECON, int LQ>
-__global__ __launch_bounds__(256) void geometry_kernel(GeoArgs a) {
-  constexpr int DS = Dims<D>::DS;
-  constexpr bool NEAREST = RECON == REC_NEAREST;
-  __shared__ __attribute__((aligned(16))) float Ks[CODES_BN * DS];
-  __shared__ float bucket[CODES_BM * 66];  // [row][K + 2], K <= 64
-  const int tid = threadIdx.x;
-  const int lane = tid & 63, wave = tid >> 6, half = lane >> 5, l32 = lane & 31;
-  const int T = a.T, K = a.K, NB = a.K + 2;
-  const int nqb = (T + CODES_BM - 1) / CODES_BM;
-  const int bh = blockIdx.x % a.BH;
-  const int qb = nqb - 1 - (int)(blockIdx.x / a.BH);
-  const int i0 = qb * CODES_BM, iw = i0 + wave * 32, row = iw + l32;
-  const int lrow = wave * 32 + l32;
-  const size_t slice = (size_t)bh * T * D;
-  const float Kf = (float)K;
-  for (int e = tid; e < CODES_BM * NB; e += 256) bucket[e] = 0.f;
-  float qop[D / 2];
-  float qss = 0.f, kss = 0.f;
-  {
-    const int rr = row < T ? row : T - 1;
-    const float *src = a.q + slice + (size_t)rr * D + half * (D / 2);
-    const float *ksrc = a.k + slice + (size_t)rr * D + half * (D / 2);
-#pragma unroll
-    for (int c = 0; c < D / 2; c += 4) {
-      const f32x4 x = *reinterpret_cast<const f32x4 *>(src + c);
-      const f32x4 y = *reinterpret_cast<const f32x4 *>(ksrc + c);
-      qop[c] = x[0]; qop[c + 1] = x[1]; qop[c + 2] = x[2]; qop[c + 3] = x[3];
-      qss += x[0] * x[0] + x[1] * x[1] + x[2] * x[2] + x[3] * x[3];
-      kss += y[0] * y[0] + y[1] * y[1] + y[2] * y[2] + y[3] * y[3];
-    }
-  }
-  const size_t ridx = (size_t)bh * T + (row < T ? row : T - 1);
-  const float M = a.st.M[ridx];
-  const float Mn = CALIB == CAL_MINMAX ? a.st.m[ridx] : M;
-  const float W = a.st.W[ridx];
-  const RowConst rc = row_const(M, Mn, K, CALIB, a.tau, a.scale);
-  const int kend = a.causal ? min(T, i0 + CODES_BM) : T;
-  const int ntiles = (kend + CODES_BN - 1) / CODES_BN;
-  const int jlim = row < T ? (a.causal ? row : T - 1) : -1;
-
-  // native weight and bucket of one key from its decided position
-  auto native = [&](float u, float &w, int &b, bool &top) {
-    const KeyDec kd = key_of<CALIB>(u, Kf);
-    const float Eu = grid_upper(kd.rf, rc);
-    const float El = Eu * rc.emh;
-    const float wl = fmaf(kd.t, Eu - El, El);
-    w = kd.tail ? 0.f : (NEAREST ? (kd.up ? Eu : El) : wl);
-    const int lev = (int)kd.rf + (NEAREST && kd.up ? 1 : 0);
-    b = kd.tail ? K + 1 : lev;
-    top = !kd.tail && (NEAREST ? lev == K : (int)kd.rf == K - 1);
-    if (rc.degen) { w = 1.f; b = 0; top = false; }  // App. A: weights 1, r = l = 0
-  };
-
-  float WE = 0.f, A = 0.f, topE = 0.f, smin = INFINITY, tv = 0.f;
-  int cnt6 = 0;
-  float low[LQ];
-#pragma unroll
-  for (int e = 0; e < LQ; ++e) low[e] = INFINITY;
-  for (int pass = 0; pass < 2; ++pass) {
-    float WEt = 0.f;
-    if (pass == 1) WEt = WE;
-    for (int t = 0; t < ntiles; ++t) {
-      const int j0 = t * CODES_BN;
-      __syncthreads();
-      load_tile_lds<D>(Ks, a.k + slice, j0, T, tid);
-      __syncthreads();
-#pragma unroll
-      for (int sub = 0; sub < CODES_BN / 32; ++sub) {
-        const int js = j0 + sub * 32;
-        if (js >= T || (a.causal && js > iw + 31)) continue;  // wave-uniform
-        float kop[D / 2];
-        const float *kr = Ks + (sub * 32 + l32) * DS + half * (D / 2);
-#pragma unroll
-        for (int c = 0; c < D / 2; c += 4) {
-          const f32x4 x = *reinterpret_cast<const f32x4 *>(kr + c);
-          kop[c] = x[0]; kop[c + 1] = x[1]; kop[c + 2] = x[2]; kop[c + 3] = x[3];
-        }
-        const f32x16 acc = score_tile<D>(kop, qop);
-        float u[16];
-        decide_u<CALIB>(acc, rc, M, Mn, K, a.tau, a.scale, u);
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const int j = js + krel(r, half);
-          const bool valid = j <= jlim;
-          const float sc = acc[r] * a.scale;
-          const float z = score_shift(acc[r], a.scale, M);
-          const float e = valid ? expf(z) : 0.f;
-          float w; int b; bool top;
-          native(u[r], w, b, top);
-          if (pass == 0) {
-            WE += e;
-            A += e * z;
-            topE += top ? e : 0.f;
-            cnt6 += (valid && (double)sc - (double)M < -6.0) ? 1 : 0;
-            if (valid) {
-              smin = fminf(smin, sc);
-              atomicAdd(&bucket[lrow * NB + b], e);
-              if (sc < low[LQ - 1]) {
-                float x = sc;
-#pragma unroll
-                for (int e2 = 0; e2 < LQ; ++e2) {
-                  const float lo = fminf(low[e2], x);
-                  x = fmaxf(low[e2], x);
-                  low[e2] = lo;
-                }
-              }
-            }
-          } else if (valid) {
-            tv += fabsf(w / W - e / WEt);
-          }
-        }
-      }
-    }
-    if (pass == 0) WE += __shfl_xor(WE, 32);
-  }
-  A += __shfl_xor(A, 32);
-  topE += __shfl_xor(topE, 32);
-  cnt6 += __shfl_xor(cnt6, 32);
-  smin = fminf(smin, __shfl_xor(smin, 32));
-  tv += __shfl_xor(tv, 32);
-  qss += __shfl_xor(qss, 32);
-  kss += __shfl_xor(kss, 32);
-  // the partner half's smallest scores merged into this lane's list (read
-  // in full first: both halves merge at once)
-  float other[LQ];
-#pragma unroll
-  for (int e = 0; e < LQ; ++e) other[e] = __shfl_xor(low[e], 32);
-#pragma unroll
-  for (int e = 0; e < LQ; ++e) {
-    float x = other[e];
-#pragma unroll
-    for (int e2 = 0; e2 < LQ; ++e2) {
-      const float lo = fminf(low[e2], x);
-      x = fmaxf(low[e2], x);
-      low[e2] = lo;
-    }
-  }
-  __syncthreads();
-  if (half == 1 || row >= T) return;
-  const int n = a.causal ? row + 1 : T;
-  float Hq = 0.f;
-  for (int b = 0; b < NB; ++b) {
-    const float mb = bucket[lrow * NB + b];
-    Hq += mb > 0.f ? mb * logf(mb) : 0.f;
-  }
-  const float lWE = logf(WE);
-  // 0.1% quantile of z: linear interpolation at (n - 1) * 0.001 between
-  // the order statistics lo and lo + 1 of the row's scores
-  const double pos = (double)(n - 1) * 0.001;
-  const int lo = (int)floor(pos), hi = lo + 1 < n ? lo + 1 : lo;
-  float slo = low[0], shi = low[0];
-#pragma unroll
-  for (int e = 1; e < LQ; ++e) {
-    slo = e == lo ? low[e] : slo;
-    shi = e == hi ? low[e] : shi;
-  }
-  const double zlo = (double)slo - (double)M, zhi = (double)shi - (double)M;
-  float *o = a.out + ((size_t)bh * T + row) * GEO_COUNT;
-  const float span = M - smin;
-  o[0] = span;
-  o[1] = CALIB == CAL_MINMAX ? span / Kf : a.tau / Kf;
-  o[2] = (float)(zlo + (pos - (double)lo) * (zhi - zlo));
-  o[3] = sqrtf(qss);
-  o[4] = sqrtf(kss);
-  o[5] = lWE - A / WE;
-  o[6] = (float)cnt6 / (float)n;
-  o[7] = topE / WE;
-  o[8] = expf(lWE - Hq / WE);
-  o[9] = 0.5f * tv;
-}
-
-#define KIA_GEO_INST(D)                                                        \
-  template __global__ void geometry_kernel<D, CAL_MINMAX, REC_LERP, 3>(GeoArgs);     \
-  template __global__ void geometry_kernel<D, CAL_MINMAX, REC_NEAREST, 3>(GeoArgs);  \
-  template __global__ void geometry_kernel<D, CAL_FWM, REC_LERP, 3>(GeoArgs);        \
-  template __global__ void geometry_kernel<D, CAL_FWM, REC_NEAREST, 3>(GeoArgs);     \
-  template __global__ void geometry_kernel<D, CAL_MINMAX, REC_LERP, 12>(GeoArgs);    \
-  template __global__ void geometry_kernel<D, CAL_MINMAX, REC_NEAREST, 12>(GeoArgs); \
-  template __global__ void geometry_kernel<D, CAL_FWM, REC_LERP, 12>(GeoArgs);       \
-  template __global__ void geometry_kernel<D, CAL_FWM, REC_NEAREST, 12>(GeoArgs);    \
-  template __global__ void geometry_kernel<D, CAL_MINMAX, REC_LERP, 67>(GeoArgs);    \
-  template __global__ void geometry_kernel<D, CAL_MINMAX, REC_NEAREST, 67>(GeoArgs); \
-  template __global__ void geometry_kernel<D, CAL_FWM, REC_LERP, 67>(GeoArgs);       \
-  template __global__ void geometry_kernel<D, CAL_FWM, REC_NEAREST, 67>(GeoArgs);
-KIA_GEO_INST(16)
-KIA_GEO_INST(32)
-KIA_GEO_INST(64)
-KIA_GEO_INST(128)
-
-// ---------------------------------------------------------------------------
-// Matrix-core peak probe (a measurement aid, not part of the operator): four
-// independent accumulator chains of v_mfma_f32_32x32x2_f32 on register
-// operands, `iters` rounds per wave. Workgroup 0's first wave records the
-// shader clock counter and the 100 MHz constant-rate counter around its loop.
-__global__ __launch_bounds__(256) void mfma_probe_kernel(unsigned long long *out, int iters) {
-  const int lane = threadIdx.x & 63;
-  const float x = 0.001f * (float)lane, y = 1.f - 0.0005f * (float)lane;
-  f32x16 c0, c1, c2, c3;
-#pragma unroll
-  for (int e = 0; e < 16; ++e) c0[e] = c1[e] = c2[e] = c3[e] = 0.f;
-  __builtin_amdgcn_sched_barrier(0);
-  const unsigned long long t0 = __builtin_amdgcn_s_memtime();
-  const unsigned long long r0 = __builtin_amdgcn_s_memrealtime();
-  __builtin_amdgcn_sched_barrier(0);
-  for (int i = 0; i < iters; ++i) {
-    c0 = mfma32(x, y, c0);
-    c1 = mfma32(y, x, c1);
-    c2 = mfma32(x, x, c2);
-    c3 = mfma32(y, y, c3);
-  }
-  __builtin_amdgcn_sched_barrier(0);
-  float sum = 0.f;
-#pragma unroll
-  for (int e = 0; e < 16; ++e) sum += c0[e] + c1[e] + c2[e] + c3[e];
-  const unsigned long long t1 = __builtin_amdgcn_s_memtime();
-  const unsigned long long r1 = __builtin_amdgcn_s_memrealtime();
-  if (blockIdx.x == 0 && threadIdx.x == 0) {
-    out[0] = t0; out[1] = t1; out[2] = r0; out[3] = r1;
-  }
-  if (sum == -1.f) out[0] = 0;  // never true (all products are >= 0): keeps the chains live
-}
-
-#define KIA_FWD_KP(D, KP)                                                        \
-  template __global__ void fwd_kernel<D, CAL_MINMAX, REC_LERP, false, KP>(FwdArgs);     \
-  template __global__ void fwd_kernel<D, CAL_MINMAX, REC_NEAREST, false, KP>(FwdArgs);  \
-  template __global__ void fwd_kernel<D, CAL_MINMAX, REC_NEAREST, true, KP>(FwdArgs);   \
-  template __global__ void fwd_kernel<D, CAL_FWM, REC_LERP, false, KP>(FwdArgs);        \
-  template __global__ void fwd_kernel<D, CAL_FWM, REC_NEAREST, false, KP>(FwdArgs);     \
-  template __global__ void fwd_kernel<D, CAL_FWM, REC_NEAREST, true, KP>(FwdArgs);      \
-  template __global__ void fwd_kernel<D, CAL_RESOLVED, REC_LERP, false, KP>(FwdArgs);   \
-  template __global__ void fwd_kernel<D, CAL_RESOLVED, REC_NEAREST, false, KP>(FwdArgs);\
-  template __global__ void fwd_kernel<D, CAL_RESOLVED, REC_NEAREST, true, KP>(FwdArgs); \
-  template __global__ void fwd_kernel<D, CAL_FWM, REC_SOFTMAX, false, KP>(FwdArgs);     \
-  template __global__ void fwd_kernel<D, CAL_FWM, REC_BF16EXP, false, KP>(FwdArgs);     \
-  template __global__ void fwd_kernel<D, CAL_FWM, REC_FP8EXP, false, KP>(FwdArgs);
-#define KIA_CODES_INST(D)                                                               \
-  template __global__ void codes_kernel<D, CAL_MINMAX, REC_LERP, float>(CodesArgs);     \
-  template __global__ void codes_kernel<D, CAL_FWM, REC_LERP, float>(CodesArgs);        \
-  template __global__ void codes_kernel<D, CAL_RESOLVED, REC_LERP, float>(CodesArgs);   \
-  template __global__ void codes_kernel<D, CAL_FWM, REC_SOFTMAX, float>(CodesArgs);     \
-  template __global__ void codes_kernel<D, CAL_FWM, REC_BF16EXP, float>(CodesArgs);     \
-  template __global__ void codes_kernel<D, CAL_FWM, REC_FP8EXP, float>(CodesArgs);      \
-  template __global__ void codes_kernel<D, CAL_MINMAX, REC_LERP, uint16_t>(CodesArgs16);\
-  template __global__ void codes_kernel<D, CAL_FWM, REC_LERP, uint16_t>(CodesArgs16);   \
-  template __global__ void codes_kernel<D, CAL_RESOLVED, REC_LERP, uint16_t>(CodesArgs16);
-KIA_FWD_KP(16, 2)
-KIA_FWD_KP(32, 2)
-KIA_FWD_KP(64, 2)
-KIA_FWD_KP(128, 2)
-// one row group and four (eight) key parts for grids too small to fill the chip
-KIA_FWD_KP(16, 4)
-KIA_FWD_KP(32, 4)
-KIA_FWD_KP(64, 4)
-KIA_FWD_KP(16, 8)
-KIA_FWD_KP(32, 8)
-KIA_FWD_KP(64, 8)
-KIA_CODES_INST(16)
-KIA_CODES_INST(32)
-KIA_CODES_INST(64)
-KIA_CODES_INST(128)
-template __global__ void stored_codes_kernel<CAL_MINMAX, REC_LERP>(StoredCodesArgs);
-template __global__ void stored_codes_kernel<CAL_FWM, REC_LERP>(StoredCodesArgs);
-template __global__ void stored_codes_kernel<CAL_FWM, REC_NEAREST>(StoredCodesArgs);
-template __global__ void stored_codes_kernel<CAL_RESOLVED, REC_LERP>(StoredCodesArgs);
-template __global__ void stored_codes_kernel<CAL_FWM, REC_SOFTMAX>(StoredCodesArgs);
-template __global__ void stored_codes_kernel<CAL_FWM, REC_BF16EXP>(StoredCodesArgs);
-template __global__ void stored_codes_kernel<CAL_FWM, REC_FP8EXP>(StoredCodesArgs);
-#define KIA_SCORES_INST(D)                                                  \
-  template __global__ void scores_kernel<D, float>(ScoresArgsT<float>);     \
-  template __global__ void scores_kernel<D, uint16_t>(ScoresArgsT<uint16_t>);
-KIA_SCORES_INST(16)
-KIA_SCORES_INST(32)
-KIA_SCORES_INST(64)
-KIA_SCORES_INST(128)
+// One head dimension per compilation (KIA_HEAD, set by the build).
+#if KIA_HEAD == 16
+KIA_FWD_D(16)
+#elif KIA_HEAD == 32
+KIA_FWD_D(32)
+#elif KIA_HEAD == 64
+KIA_FWD_D(64)
+KIA_FWD_GRID(float, 64, 1, 8)
+KIA_FWD_EXP(64, 1, 8)
+#elif KIA_HEAD == 128
+KIA_FWD_D(128)
+#else
+#error "KIA_HEAD must name a head dimension"
+#endif
 
 }  // namespace kia

@@ -15,11 +15,42 @@ template <typename TI> struct FwdArgsT {
   int BH, T, K, calib, recon, causal;
   float tau, scale;
   uint16_t *o16 = nullptr;  // bf16-output variant: O as bf16 here instead of o
-  // 0 (forward only): the fp32 second pass stores no decisions in U (the
-  // bf16 forward stores them regardless: the branch costs its d = 128
-  // instance ~500 B of spills per lane)
-  int keep = 1;
+  int keep = 1;  // 0 (forward only): pass 2 stores no decisions in U
+  // grid constants that do not depend on the row (FWM and resolved; see
+  // fwd_row_const): K / tau, and as RowConst alpha, hl, b1l, emh
+  double gc = 0.0;
+  float ga = 0.f, ghl = 0.f, gb1l = 0.f, gemh = 1.f;
 };
+
+// Launch shape of the forward: NBUF staging buffers per tensor, OCC waves per
+// SIMD. At d = 128 the three pieces of Q and two output accumulators take more
+// than half the registers of a SIMD, and large chunks more than half the LDS.
+template <typename TI, int D, int RG, int KP> struct FwdShape {
+  static constexpr int CHUNK = Pieces<TI>::N * 32 * KP * (D + 8) * 2;  // bytes of one staged tensor
+  static constexpr int WGS = RG * KP == 8 ? 1 : 2;  // workgroups that make two waves per SIMD
+  static constexpr int LDS = RG == 1 ? CHUNK : 2 * CHUNK;  // one buffer for each tensor, or one for both
+  static constexpr int OCC = (sizeof(TI) == 4 && D == 128) || LDS * WGS > 156 * 1024 ? 1 : 2;
+  static constexpr int NBUF = 4 * CHUNK * (OCC == 2 ? WGS : 1) <= 156 * 1024 ? 2 : 1;
+};
+
+// Row constants of the forward: as row_const(), with what FWM and the
+// resolved grid share across rows taken from the arguments.
+template <int CALIB, typename TI>
+__device__ __forceinline__ RowConst fwd_row_const(float M, float m, const FwdArgsT<TI> &a) {
+  if constexpr (CALIB == CAL_MINMAX) {
+    return row_const(M, m, a.K, CALIB, a.tau, a.scale);
+  } else {
+    RowConst rc{};
+    const double Kd = (double)a.K, t = (double)a.tau;
+    rc.alpha = a.ga; rc.hl = a.ghl; rc.b1l = a.gb1l; rc.emh = a.gemh;
+    rc.beta = (float)(Kd - (double)M * a.gc);
+    const double A = CALIB == CAL_RESOLVED
+                         ? fmax(fabs((double)M), fabs((double)m)) + t + ((double)M - (double)m)
+                         : fabs((double)M) + t;
+    rc.margin2 = (float)ldexp(3.0 * a.gc * A + 2.0 * Kd, -20);
+    return rc;
+  }
+}
 
 template <typename TI> struct CodesArgsT {
   const TI *q, *k;
@@ -61,7 +92,8 @@ using FwdArgs16 = FwdArgsT<uint16_t>;
 using CodesArgs16 = CodesArgsT<uint16_t>;
 using BwdArgs16 = BwdArgsT<uint16_t>;
 
-template <int D, int CALIB, int RECON, bool OL, int KP> __global__ void fwd_kernel(FwdArgs a);
+template <typename TI, int D, int CALIB, int RECON, bool OL, int RG, int KP>
+__global__ void fwd_kernel(FwdArgsT<TI> a);
 template <int D, int CALIB, int REC, typename TI> __global__ void codes_kernel(CodesArgsT<TI> a);
 // test exports: the code words of the decisions stored in U (no score
 // recomputation), and the canonical fp32 score sub-tiles
@@ -109,7 +141,6 @@ struct GeoArgs {
 template <int D, int CALIB, int RECON, int LQ> __global__ void geometry_kernel(GeoArgs a);
 __global__ void mfma_probe_kernel(unsigned long long *out, int iters);
 // bf16-input kernels (kia_bf16.hip)
-template <int D, int CALIB, int RECON, bool OL> __global__ void fwd16_kernel(FwdArgs16 a);
 template <int D, int CALIB, int RECON, bool SPLIT> __global__ void bwd16_main_kernel(BwdArgs16 a);
 template <int D> __global__ void bwd16_dq_kernel(BwdArgs16 a);
 
