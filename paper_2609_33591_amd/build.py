@@ -25,7 +25,7 @@ HEADS = (16, 32, 64, 128)
 OBJECTS = {
     "kia_abi.o": [("kia_abi.hip", [])],
     "kia_fwd.o": [("kia_fwd.hip", [f"-DKIA_HEAD={d}"]) for d in HEADS] + [("kia_debug.hip", [])],
-    "kia_bwd.o": [("kia_bwd.hip", [])],
+    "kia_bwd.o": [("kia_bwd.hip", [f"-DKIA_HEAD={d}"]) for d in HEADS],
     "kia_bf16.o": [("kia_bf16.hip", [])],
 }
 # (source, flags, object file) of every compilation

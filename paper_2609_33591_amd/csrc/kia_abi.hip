@@ -254,23 +254,14 @@ void launch_codes(const CodesArgsT<TI> &a, int recon, hipStream_t s) {
 }
 
 // ---- bf16 inputs ----------------------------------------------------------
-template <int D, int CALIB, int RECON>
-void launch_main16(const BwdArgs16 &a, int nkb, hipStream_t s) {
-  // the query-range split as its own instantiation: the unsplit kernel keeps
-  // plain stores in its epilogue
-  if (a.qsplit > 1)
-    hipLaunchKernelGGL((bwd16_main_kernel<D, CALIB, RECON, true>), dim3(a.BH * nkb), dim3(512), 0, s, a);
-  else
-    hipLaunchKernelGGL((bwd16_main_kernel<D, CALIB, RECON, false>), dim3(a.BH * nkb), dim3(512), 0, s, a);
+template <typename TI, int D, int CALIB, int RECON>
+void launch_main(const BwdArgsT<TI> &a, int nkb, hipStream_t s) {
+  hipLaunchKernelGGL((bwd_main_kernel<TI, D, CALIB, RECON>), dim3(a.BH * nkb), dim3(256), 0, s, a);
 }
-
-template <int D, int CALIB, int RECON>
-void launch_main(const BwdArgs &a, int nkb, hipStream_t s) {
-  // d <= 64: eight waves share one K/V block; d = 128: four waves, K/V in registers
-  if constexpr (D <= 64)
-    hipLaunchKernelGGL((bwd_main_shared_kernel<D, CALIB, RECON>), dim3(a.BH * nkb), dim3(512), 0, s, a);
-  else
-    hipLaunchKernelGGL((bwd_main_kernel<D, CALIB, RECON>), dim3(a.BH * nkb), dim3(256), 0, s, a);
+template <typename TI, int D, int CALIB>
+void launch_main_c(const BwdArgsT<TI> &a, int nkb, hipStream_t s) {
+  if (a.recon == KIA_RECON_LERP) launch_main<TI, D, CALIB, REC_LERP>(a, nkb, s);
+  else launch_main<TI, D, CALIB, REC_NEAREST>(a, nkb, s);
 }
 
 // The backward's four launches; TI selects the fp32 or the bf16-input
@@ -286,35 +277,14 @@ void launch_bwd(const BwdArgsT<TI> &a, hipStream_t s) {
   });
   const int nkb = (a.T + 127) / 128 * a.qsplit;
   timed("kia_bwd_main", s, [&] {
-    if constexpr (B16) {
-      if (a.calib == KIA_CALIB_MINMAX) {
-        if (a.recon == KIA_RECON_LERP) launch_main16<D, CAL_MINMAX, REC_LERP>(a, nkb, s);
-        else launch_main16<D, CAL_MINMAX, REC_NEAREST>(a, nkb, s);
-      } else if (a.calib == KIA_CALIB_RESOLVED) {
-        if (a.recon == KIA_RECON_LERP) launch_main16<D, CAL_RESOLVED, REC_LERP>(a, nkb, s);
-        else launch_main16<D, CAL_RESOLVED, REC_NEAREST>(a, nkb, s);
-      } else {
-        if (a.recon == KIA_RECON_LERP) launch_main16<D, CAL_FWM, REC_LERP>(a, nkb, s);
-        else launch_main16<D, CAL_FWM, REC_NEAREST>(a, nkb, s);
-      }
-    } else if (a.recon == KIA_RECON_SOFTMAX) {
-      launch_main<D, CAL_FWM, REC_SOFTMAX>(a, nkb, s);
-    } else if (a.recon == KIA_RECON_BF16EXP) {
-      launch_main<D, CAL_FWM, REC_BF16EXP>(a, nkb, s);
-    } else if (a.recon == KIA_RECON_FP8EXP) {
-      launch_main<D, CAL_FWM, REC_FP8EXP>(a, nkb, s);
-    } else {
-      if (a.calib == KIA_CALIB_MINMAX) {
-        if (a.recon == KIA_RECON_LERP) launch_main<D, CAL_MINMAX, REC_LERP>(a, nkb, s);
-        else launch_main<D, CAL_MINMAX, REC_NEAREST>(a, nkb, s);
-      } else if (a.calib == KIA_CALIB_RESOLVED) {
-        if (a.recon == KIA_RECON_LERP) launch_main<D, CAL_RESOLVED, REC_LERP>(a, nkb, s);
-        else launch_main<D, CAL_RESOLVED, REC_NEAREST>(a, nkb, s);
-      } else {
-        if (a.recon == KIA_RECON_LERP) launch_main<D, CAL_FWM, REC_LERP>(a, nkb, s);
-        else launch_main<D, CAL_FWM, REC_NEAREST>(a, nkb, s);
-      }
+    if constexpr (!B16) {
+      if (a.recon == KIA_RECON_SOFTMAX) return launch_main<TI, D, CAL_FWM, REC_SOFTMAX>(a, nkb, s);
+      if (a.recon == KIA_RECON_BF16EXP) return launch_main<TI, D, CAL_FWM, REC_BF16EXP>(a, nkb, s);
+      if (a.recon == KIA_RECON_FP8EXP) return launch_main<TI, D, CAL_FWM, REC_FP8EXP>(a, nkb, s);
     }
+    if (a.calib == KIA_CALIB_MINMAX) launch_main_c<TI, D, CAL_MINMAX>(a, nkb, s);
+    else if (a.calib == KIA_CALIB_RESOLVED) launch_main_c<TI, D, CAL_RESOLVED>(a, nkb, s);
+    else launch_main_c<TI, D, CAL_FWM>(a, nkb, s);
   });
   // deterministic backward: the key blocks' row-sum partials added up in
   // order (timed with the main kernel)
@@ -514,6 +484,11 @@ int attn_bwd(const TI *q, const TI *k, const TI *v, const float *o, const TI *dO
   a.tau = calib != KIA_CALIB_MINMAX ? tau : 0.f;
   if (is_exp_rec(recon)) { a.calib = CAL_FWM; a.tau = 0.f; a.K = 1; a.ste = STE_WEIGHT; }
   a.scale = softmax_scale(d);
+  if (a.calib != CAL_MINMAX && !is_exp_rec(recon)) {
+    const float h = a.tau / (float)K;
+    a.ghl = h * 1.44269504f;
+    a.gemh = expf(-h);
+  }
   hipStream_t s = static_cast<hipStream_t>(stream);
   switch (d) {
     case 16: launch_bwd<16, TI>(a, s); break;

@@ -112,249 +112,6 @@ template <int D, int ROWS, int NT> struct Blocks16 {
 };
 
 // ---------------------------------------------------------------------------
-// Backward main (bf16 inputs): KV-major as bwd_main_shared_kernel, 8 waves
-// in two groups of 4 taking alternate 32-query tiles; 128 keys per
-// workgroup with V row-major in LDS (dP^T A operand); per group the query
-// tile's dO row-major (dP^T B operand) and transposed (dV B operand) and Q
-// transposed (dK B operand).
-template <int D, int CALIB, int RECON, bool SPLIT>
-__global__ __launch_bounds__(512, 1) void bwd16_main_kernel(BwdArgs16 a) {
-  constexpr int NC = Dims16<D>::NC, RS = Dims16<D>::RS;
-  constexpr int VR = 128 * RS;           // bf16: V rows of the workgroup
-  constexpr int DOR = 32 * RS;           // bf16: dO rows of a query tile
-  constexpr int TT = D * H16_QT;         // bf16: a transposed query tile
-  constexpr int GRP = DOR + 2 * TT;      // bf16 per group: dO rows, dO^T, Q^T
-  constexpr int XW = 8 * 32 * H16_XS;    // bf16: wave-private transposes
-  constexpr int STAGE_B = 2 * (VR + 2 * GRP + XW);      // bytes
-  constexpr int RED_B = 4 * NC * 16 * 64 * 4;           // bytes: one of dV/dK of group 1
-  constexpr int SMB = STAGE_B > RED_B ? STAGE_B : RED_B;
-  __shared__ __attribute__((aligned(16))) unsigned char smem[SMB];
-  __shared__ __attribute__((aligned(16))) float Rec[2][32 * RR_COUNT];
-  __shared__ float Part[2][4 * 32 * 2];
-  uint16_t *Vr = reinterpret_cast<uint16_t *>(smem);
-  uint16_t *G0 = Vr + VR;
-  uint16_t *Xt = G0 + 2 * GRP;
-
-  const int tid = threadIdx.x;
-  const int lane = tid & 63, wave = tid >> 6, half = lane >> 5, l32 = lane & 31;
-  const int grp = wave >> 2, wk = wave & 3, gtid = tid & 255;
-  const int T = a.T;
-  const int nq = (T + 31) / 32;
-  // key block (ascending: the longest causal key blocks first) and the part
-  // of its query range (qsplit parts of nearly equal tile counts)
-  const int qsplit = SPLIT ? a.qsplit : 1;
-  const int kb = (int)(blockIdx.x / a.BH) / qsplit;
-  const int qpart = (int)(blockIdx.x / a.BH) % qsplit;
-  const int bh = blockIdx.x % a.BH;
-  const int j0 = kb * 128;
-  const int jw = j0 + 32 * wk;
-  const size_t slice = (size_t)bh * T * D;
-  const uint16_t *qs = a.q + slice, *vs = a.v + slice, *dos = a.dO + slice;
-  constexpr bool minmax = CALIB == CAL_MINMAX;
-  constexpr bool nearest = RECON == REC_NEAREST;
-  const bool want_cm = minmax & grad_channels(a.grad);
-  const float invK = 1.f / (float)a.K, Kf = (float)a.K;
-  uint16_t *dOr = G0 + grp * GRP, *dOt = dOr + DOR, *Qt = dOt + TT;
-
-  {
-    Blocks16<D, 128, 512> fvv;
-    fvv.fetch(vs, j0, T, tid);
-    fvv.template stash_rows<RS>(Vr, tid);
-  }
-
-  f32x16 dva[NC], dka[NC];
-#pragma unroll
-  for (int c = 0; c < NC; ++c)
-#pragma unroll
-    for (int e = 0; e < 16; ++e) { dva[c][e] = 0.f; dka[c][e] = 0.f; }
-
-  Blocks16<D, 32, 256> fq, fd;
-  f32x4 prr;
-  uint32_t prok;
-  auto fetch = [&](int i0) {
-    fq.fetch(qs, i0, T, gtid);
-    fd.fetch(dos, i0, T, gtid);
-    const int r = (gtid / (RR_COUNT / 4)) % 32, c4 = gtid % (RR_COUNT / 4);
-    const bool ok = (gtid < 32 * RR_COUNT / 4) & (i0 + r < T);
-    prok = ok ? 1u : 0u;
-    const size_t rix = (size_t)bh * T + (ok ? i0 + r : 0);
-    prr = *reinterpret_cast<const f32x4 *>(a.st.rowrec + rix * RR_COUNT + c4 * 4);
-  };
-  auto stash = [&]() {
-    fq.template stash_cols<H16_QT>(Qt, gtid);
-    fd.template stash_rows<RS>(dOr, gtid);
-    fd.template stash_cols<H16_QT>(dOt, gtid);
-    if (gtid < 32 * RR_COUNT / 4) {
-      const f32x4 pad = {0.f, (gtid % (RR_COUNT / 4)) == 0 ? (float)a.K : 0.f, 0.f, 0.f};
-      *reinterpret_cast<f32x4 *>(&Rec[grp][gtid * 4]) = prok ? prr : pad;
-    }
-  };
-
-  const int q0 = a.causal ? j0 : 0;
-  const int ntall = (T - q0 + 31) / 32;
-  const int tb = ntall * qpart / qsplit, te = ntall * (qpart + 1) / qsplit;
-  const int qstart = q0 + tb * 32;
-  const int nt = te - tb;
-  const int npair = (nt + 1) / 2;
-  uint16_t *Xw = Xt + wave * 32 * H16_XS;
-  if (grp < nt) fetch(qstart + grp * 32);
-  for (int it = 0; it < npair; ++it) {
-    const int t = 2 * it + grp;
-    const int i0 = qstart + t * 32;
-    if (t < nt) stash();
-    lds_barrier();
-    if (t + 2 < nt) fetch(i0 + 64);
-
-    float ps = 0.f, pm = 0.f;
-    const bool active = (t < nt) & (jw < T) & !(a.causal & (jw > i0 + 31));
-    if (active) {
-      // the forward's decided positions (one byte per key under FWM with
-      // Nearest)
-      constexpr bool COMPACT = compact_codes<CALIB, RECON>();
-      float u[16];
-      uint4 cw;
-      {
-        const float *ut = a.st.U + ds_tile(bh, i0 / 32, jw / 32, nq, a.causal) * 1024;
-        if constexpr (COMPACT) cw = codes_load(ut, lane);
-        else tile_load(ut, lane, u);
-      }
-      f32x16 G;
-#pragma unroll
-      for (int e = 0; e < 16; ++e) G[e] = 0.f;
-      {
-        const uint16_t *vr = Vr + (32 * wk + l32) * RS + 8 * half;
-        const uint16_t *dr = dOr + l32 * RS + 8 * half;
-#pragma unroll
-        for (int s = 0; s < D / 16; ++s)
-          G = mfma16(as_bf16x8(*reinterpret_cast<const uint4 *>(vr + 16 * s)),
-                     as_bf16x8(*reinterpret_cast<const uint4 *>(dr + 16 * s)), G);
-      }
-      const float *rr = Rec[grp] + l32 * RR_COUNT;
-      const f32x4 r0 = *reinterpret_cast<const f32x4 *>(rr);
-      const f32x4 r1 = *reinterpret_cast<const f32x4 *>(rr + 4);
-      const f32x4 r2 = *reinterpret_cast<const f32x4 *>(rr + 8);
-      const f32x4 r3 = *reinterpret_cast<const f32x4 *>(rr + 12);
-      RowConst rc;
-      rc.alpha = r0[0]; rc.beta = r0[1]; rc.margin2 = r0[2]; rc.hl = r0[3];
-      rc.b1l = r1[0]; rc.emh = r1[1]; rc.dcoef = r1[2];
-      rc.degen = r3[0] != 0.f;
-      const float invWf = r1[3], invWX = r2[0], negDXW = r2[1];
-      const int i = i0 + l32;
-      const int jlim = i < T ? (a.causal ? i : T - 1) : -1;
-      float P[16], dS[16];
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        KeyDec kd;
-        if constexpr (COMPACT) kd = key_of_code(cw, r);
-        else kd = key_of<CALIB>(u[r], Kf);
-        const bool valid = (jw + krel(r, half) <= jlim) & !kd.tail;
-        const float Eu = grid_upper(kd.rf, rc);
-        const float El = Eu * rc.emh;
-        const float wL = fmaf(kd.t, Eu - El, El);
-        const float wf = nearest ? (kd.up ? Eu : El) : wL;
-        const float gamma = fmaf(G[r], invWX, negDXW);
-        const float Delta = Eu * rc.dcoef;
-        P[r] = valid ? wf * invWf : 0.f;
-        dS[r] = valid ? gamma * Delta : 0.f;
-        ps += dS[r];
-        if (want_cm) {
-          const float uc = kd.rf + kd.t;
-          const float X = fmaf(kd.rf, wL, kd.t * Eu) * invK;
-          const float dM = X - wL - Delta * uc * invK;
-          pm += valid ? gamma * dM : 0.f;
-        }
-      }
-      {
-        // dS rounded to bf16 (the dQ product's operand), 2 KiB per tile:
-        // element (lane l, register r) at (r/8)*512 + 8l + r%8
-        uint16_t *dst = reinterpret_cast<uint16_t *>(a.st.dS) +
-                        ds_tile(bh, i0 / 32, jw / 32, nq, a.causal) * 1024 + 8 * lane;
-#pragma unroll
-        for (int t2 = 0; t2 < 2; ++t2)
-          *reinterpret_cast<bf16x8 *>(dst + 512 * t2) = to_bf16x8(&dS[8 * t2]);
-      }
-      // dV += P^T dO, dK += dS^T Q: k-slots are the queries 16t + 8h + e;
-      // the operand goes through the wave's private LDS tile rounded to bf16
-      auto transposed_product = [&](const float (&X)[16], const uint16_t *Bt, f32x16 (&acc)[NC]) {
-#pragma unroll
-        for (int r = 0; r < 16; ++r)
-          Xw[krel(r, half) * H16_XS + l32] = __builtin_bit_cast(uint16_t, (__bf16)X[r]);
-#pragma unroll
-        for (int t2 = 0; t2 < 2; ++t2) {
-          // read as a vector of the stored element type (a uint4 read may be
-          // moved above the 16-bit stores it does not alias by type)
-          const bf16x8 av = __builtin_bit_cast(
-              bf16x8, *reinterpret_cast<const u16x8 *>(Xw + l32 * H16_XS + 16 * t2 + 8 * half));
-#pragma unroll
-          for (int c = 0; c < NC; ++c) {
-            const int col = 32 * c + l32;
-            uint4 bv = *reinterpret_cast<const uint4 *>(Bt + (col < D ? col : 0) * H16_QT + 16 * t2 + 8 * half);
-            if (col >= D) bv = make_uint4(0, 0, 0, 0);
-            acc[c] = mfma16(av, as_bf16x8(bv), acc[c]);
-          }
-        }
-      };
-      transposed_product(P, dOt, dva);
-      transposed_product(dS, Qt, dka);
-    }
-    ps += __shfl_xor(ps, 32);
-    pm += __shfl_xor(pm, 32);
-    if (half == 0) {
-      Part[grp][(wk * 32 + l32) * 2] = ps;
-      Part[grp][(wk * 32 + l32) * 2 + 1] = pm;
-    }
-    lds_barrier();
-    if (a.grad != GRAD_DETACH && wk == 0 && lane < 32 && t < nt && i0 + lane < T) {
-      float sv = 0.f, mm = 0.f;
-#pragma unroll
-      for (int w = 0; w < 4; ++w) {
-        sv += Part[grp][(w * 32 + lane) * 2];
-        mm += Part[grp][(w * 32 + lane) * 2 + 1];
-      }
-      const size_t ridx = (size_t)bh * T + i0 + lane;
-      put_row_sums(a, kb, ridx, sv, mm, minmax);
-    }
-  }
-  // sum the two groups' dV, then dK (group 1 -> LDS -> group 0), and store;
-  // the buffer overlaps V and the tiles: a workgroup with an empty query
-  // part (only a split range has one) ran no iteration, whose barriers would
-  // have seen its V stash land, so it waits here
-  if (SPLIT && nt == 0) __syncthreads();
-  float *red = reinterpret_cast<float *>(smem) + (size_t)wk * (NC * 16 * 64) + lane;
-#pragma unroll
-  for (int which = 0; which < 2; ++which) {
-    f32x16 (&acc)[NC] = which == 0 ? dva : dka;
-    if (grp == 1) {
-#pragma unroll
-      for (int c = 0; c < NC; ++c)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) red[(c * 16 + r) * 64] = acc[c][r];
-    }
-    __syncthreads();
-    if (grp == 0) {
-#pragma unroll
-      for (int c = 0; c < NC; ++c)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const int j = jw + krel(r, half);
-          const int col = 32 * c + l32;
-          const float v = acc[c][r] + red[(c * 16 + r) * 64];
-          if (j < T && col < D) {
-            const size_t e = slice + (size_t)j * D + col;
-            if constexpr (SPLIT) {  // parts of the query range add up (zeroed by bwd_pre)
-              if (which == 1) atomicAdd(a.dk + e, a.scale * v);
-              else atomicAdd(a.dv + e, v);
-            } else if (which == 1) a.dk[e] = a.scale * v;
-            else if (a.dv16) a.dv16[e] = (uint16_t)(__float_as_uint(bf16_rne(v)) >> 16);
-            else a.dv[e] = v;
-          }
-        }
-    }
-    __syncthreads();
-  }
-}
-
-// ---------------------------------------------------------------------------
 // dQ (bf16 inputs) = scale * (dS K + calibration terms): as bwd_dq_kernel,
 // with each 64-key chunk of K staged transposed in bf16 and the fp32 dS
 // tiles (stored in bf16 by bwd16_main_kernel) as the A operand.
@@ -528,18 +285,6 @@ __global__ __launch_bounds__(512) void bwd16_dq_kernel(BwdArgs16 a) {
 }
 
 #define KIA_B16_INST(D)                                                                  \
-  template __global__ void bwd16_main_kernel<D, CAL_RESOLVED, REC_LERP, false>(BwdArgs16);    \
-  template __global__ void bwd16_main_kernel<D, CAL_RESOLVED, REC_LERP, true>(BwdArgs16);     \
-  template __global__ void bwd16_main_kernel<D, CAL_RESOLVED, REC_NEAREST, false>(BwdArgs16); \
-  template __global__ void bwd16_main_kernel<D, CAL_RESOLVED, REC_NEAREST, true>(BwdArgs16);  \
-  template __global__ void bwd16_main_kernel<D, CAL_MINMAX, REC_LERP, false>(BwdArgs16);      \
-  template __global__ void bwd16_main_kernel<D, CAL_MINMAX, REC_LERP, true>(BwdArgs16);       \
-  template __global__ void bwd16_main_kernel<D, CAL_MINMAX, REC_NEAREST, false>(BwdArgs16);   \
-  template __global__ void bwd16_main_kernel<D, CAL_MINMAX, REC_NEAREST, true>(BwdArgs16);    \
-  template __global__ void bwd16_main_kernel<D, CAL_FWM, REC_LERP, false>(BwdArgs16);         \
-  template __global__ void bwd16_main_kernel<D, CAL_FWM, REC_LERP, true>(BwdArgs16);          \
-  template __global__ void bwd16_main_kernel<D, CAL_FWM, REC_NEAREST, false>(BwdArgs16);      \
-  template __global__ void bwd16_main_kernel<D, CAL_FWM, REC_NEAREST, true>(BwdArgs16);       \
   template __global__ void bwd16_dq_kernel<D>(BwdArgs16);
 KIA_B16_INST(16)
 KIA_B16_INST(32)

@@ -36,7 +36,6 @@ namespace kia {
 
 constexpr int BKV = 128;  // keys per bwd_main workgroup
 constexpr int BQ = 32;    // queries per streamed tile
-constexpr int XS = 36;    // transpose buffer row stride (floats)
 
 // ---------------------------------------------------------------------------
 template <int D, typename TI>
@@ -100,19 +99,33 @@ __global__ __launch_bounds__(256) void bwd_pre_kernel(BwdArgsT<TI> a) {
 }
 
 // ---------------------------------------------------------------------------
-template <int D, int CALIB, int RECON>
-__global__ __launch_bounds__(256) void bwd_main_kernel(BwdArgs a) {
-  constexpr int NC = Dims<D>::NC, DS = Dims<D>::DS, DP = Dims<D>::DP;
-  constexpr int QV4 = BQ * DP / 4;         // float4 per Q (or dO) tile
-  constexpr int PF = (QV4 + 255) / 256;    // float4 per thread and tensor
-  __shared__ __attribute__((aligned(16))) float Qs[2][BQ * DS];
-  __shared__ __attribute__((aligned(16))) float dOs[2][BQ * DS];
-  __shared__ __attribute__((aligned(16))) float Rec[2][BQ * RR_COUNT];
-  __shared__ __attribute__((aligned(16))) float Xt[4 * 32 * XS];
+// Main kernel: one workgroup = 4 waves = 128 keys of one (b, h), a wave 32 of
+// them, streaming 32-query tiles of Q and dO (staged in LDS as bf16 pieces, two
+// buffers, one barrier per tile; both are read by rows or through transposing
+// reads as a product needs them). Per tile and wave:
+//   dP^T = V dO^T with the wave's V rows in registers (lane = query, register =
+//   key: the layout of the forward's decisions, and each row's constants are
+//   lane-local); P and dS per key; dS to its scratch tile; then P and dS go
+//   through a wave-private LDS tile as bf16 pieces, written by rows of 4 keys
+//   and read back transposed, as the A operands of dV += P^T dO and
+//   dK += dS^T Q.
+// Three products of 24 (d = 64, fp32) MFMAs each, about 700 VALU operations
+// and 60 KiB of LDS traffic per 32x32 tile: no single unit bounds it, so two
+// workgroups per CU (256 registers a wave) run out of phase; fp32 at d = 128
+// needs 512.
+template <typename TI, int D, int CALIB, int RECON>
+__global__ __launch_bounds__(256, (MainShape<TI, D>::OCC)) void bwd_main_kernel(BwdArgsT<TI> a) {
+  constexpr int NP = Pieces<TI>::N, NC = D >= 32 ? D / 32 : 1;
+  using St = Stage<D, BQ, 256, TI>;
+  constexpr int RS = St::RS, PS = St::PS;
+  constexpr int XT = NP * 32 * 32;  // a wave's transpose tile
+  __shared__ __attribute__((aligned(16))) uint16_t Tl[2][2 * St::SIZE];  // Q, dO
+  __shared__ __attribute__((aligned(16))) uint16_t Xt[4 * XT];
   __shared__ float Part[2][4 * 32 * 2];
 
   const int tid = threadIdx.x;
-  const int lane = tid & 63, wave = tid >> 6, half = lane >> 5, l32 = lane & 31;
+  const int lane = tid & 63, half = lane >> 5, l32 = lane & 31;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int T = a.T;
   const int nq = (T + 31) / 32;
   // key block (ascending: the longest causal key blocks first) and the part
@@ -123,8 +136,7 @@ __global__ __launch_bounds__(256) void bwd_main_kernel(BwdArgs a) {
   const int j0 = kb * BKV;
   const int jw = j0 + 32 * wave;
   const size_t slice = (size_t)bh * T * D;
-  const float *qs = a.q + slice, *vs = a.v + slice,
-              *dos = a.dO + slice;
+  const TI *qs = a.q + slice, *dos = a.dO + slice;
   constexpr bool minmax = CALIB == CAL_MINMAX;
   constexpr bool nearest = RECON == REC_NEAREST;
   constexpr bool EXPW = is_exp_rec(RECON);
@@ -132,19 +144,9 @@ __global__ __launch_bounds__(256) void bwd_main_kernel(BwdArgs a) {
   const bool want_cm = minmax & grad_channels(a.grad);
   const float invK = 1.f / (float)a.K, Kf = (float)a.K;
 
-  // this wave's 32 keys of V as A operands (canonical layout)
-  float vop[D / 2];
-  {
-    const int key = jw + l32;
-    const bool ok = key < T;
-    const float *vr = vs + (size_t)(ok ? key : 0) * D + half * (D / 2);
-#pragma unroll
-    for (int s = 0; s < D / 2; s += 4) {
-      f32x4 y = *reinterpret_cast<const f32x4 *>(vr + s);
-#pragma unroll
-      for (int e = 0; e < 4; ++e) vop[s + e] = ok ? y[e] : 0.f;
-    }
-  }
+  // this wave's 32 keys of V as A operands
+  bf16x8 vop[NP][D / 16];
+  load_rows<D>(a.v + slice, jw + l32, T, half, vop);
 
   f32x16 dva[NC], dka[NC];
 #pragma unroll
@@ -152,99 +154,120 @@ __global__ __launch_bounds__(256) void bwd_main_kernel(BwdArgs a) {
 #pragma unroll
     for (int e = 0; e < 16; ++e) { dva[c][e] = 0.f; dka[c][e] = 0.f; }
 
-  // next-tile prefetch registers: Q and dO rows through buffer loads (rows
-  // past T and padded columns read as zeros; no branch around a load, so
-  // the compiler does not wait for them before the compute); the row
-  // records of rows past T are replaced by padding when stashed
-  static_assert(QV4 % 256 == 0, "whole passes");
-  const uint32_t qoff = row_vec_offset<D>(tid);
-  f32x4 pq[PF], pd[PF], pr;
-  bool rok;
-  auto fetch = [&](int i0) {
-#pragma unroll
-    for (int e = 0; e < PF; ++e) {
-      const int rb = i0 + e * (1024 / DP);  // 256 threads cover 1024 / DP rows
-      pq[e] = buffer_f32x4(row_rsrc(qs, rb, T, D), qoff);
-      pd[e] = buffer_f32x4(row_rsrc(dos, rb, T, D), qoff);
-    }
-    {
-      const int r = (tid / (RR_COUNT / 4)) % BQ, c4 = tid % (RR_COUNT / 4);
-      rok = (tid < BQ * RR_COUNT / 4) & (i0 + r < T);
-      const size_t rix = (size_t)bh * T + (rok ? i0 + r : 0);
-      pr = *reinterpret_cast<const f32x4 *>(a.st.rowrec + rix * RR_COUNT + c4 * 4);
-    }
-  };
-  auto stash = [&](int buf) {
-#pragma unroll
-    for (int e = 0; e < PF; ++e) {
-      const int idx = tid + 256 * e;
-      const int r = idx / (DP / 4), c4 = idx % (DP / 4);
-      *reinterpret_cast<f32x4 *>(&Qs[buf][r * DS + c4 * 4]) = pq[e];
-      *reinterpret_cast<f32x4 *>(&dOs[buf][r * DS + c4 * 4]) = pd[e];
-    }
-    if (tid < BQ * RR_COUNT / 4) {
-      // padding rows: u = K (beta = K), never ambiguous
-      const f32x4 pad = {0.f, (tid % (RR_COUNT / 4)) == 0 ? (float)a.K : 0.f, 0.f, 0.f};
-      *reinterpret_cast<f32x4 *>(&Rec[buf][tid * 4]) = rok ? pr : pad;
-    }
-  };
-
   const int q0 = a.causal ? j0 : 0;
   const int ntall = (T - q0 + BQ - 1) / BQ;
   const int tb = ntall * qpart / a.qsplit, te = ntall * (qpart + 1) / a.qsplit;
   const int qstart = q0 + tb * BQ;
   const int nt = te - tb;
-  float *Xw = Xt + wave * 32 * XS;
-  fetch(qstart);
-  stash(0);
-  lds_barrier();
+
+  // next-tile prefetch: Q and dO rows, and what the tile needs of the lane's
+  // row record (a quad of it for FWM: the grid constants are the call's)
+  St fq, fd;
+  constexpr bool R012 = minmax && !EXPW, R12 = EXPW || R012;
+  f32x4 r0, r1, r2, r3;
+  auto fetch_rec = [&](int i0) {
+    const int i = i0 + l32;
+    const float *rr = a.st.rowrec + ((size_t)bh * T + (i < T ? i : T - 1)) * RR_COUNT;
+    if constexpr (R012) r0 = *reinterpret_cast<const f32x4 *>(rr);
+    if constexpr (R12) r1 = *reinterpret_cast<const f32x4 *>(rr + 4);
+    if constexpr (R12) r2 = *reinterpret_cast<const f32x4 *>(rr + 8);
+    if constexpr (!EXPW) r3 = *reinterpret_cast<const f32x4 *>(rr + 12);
+  };
+  // row sums of tile tp: the four waves' partials, then one atomic per row
+  auto flush = [&](int tp) {
+    const int ip = qstart + tp * BQ;
+    if (a.grad != GRAD_DETACH && tid < 32 && ip + tid < T) {
+      const float *pp = Part[tp & 1];
+      float sv = 0.f, mm = 0.f;
+#pragma unroll
+      for (int w = 0; w < 4; ++w) {
+        sv += pp[(w * 32 + tid) * 2];
+        mm += pp[(w * 32 + tid) * 2 + 1];
+      }
+      put_row_sums(a, kb, (size_t)bh * T + ip + tid, sv, mm, minmax);
+    }
+  };
+  // transpose tile [piece][query][key]: rows of eight 4-key units, permuted by
+  // the row's group of four, so that a wave's 8-byte writes and the
+  // transposing reads fall in distinct banks
+  uint16_t *Xw = Xt + wave * XT;
+  const int xw = l32 * 32, xs = (l32 >> 2) & 7;
+  const int xrow = 4 * half + ((lane & 15) >> 2), xunit = 4 * ((lane >> 4) & 1) + (lane & 3);
+  auto put_tile = [&](const float (&X)[16]) {
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+      bf16x8 w[NP];
+      to_pieces<NP>(reinterpret_cast<const float(&)[8]>(X[8 * t]), w);
+#pragma unroll
+      for (int p = 0; p < NP; ++p) {
+        const u32x4 q = __builtin_bit_cast(u32x4, w[p]);
+        uint16_t *x = Xw + p * 1024 + xw;
+        *reinterpret_cast<u32x2 *>(x + 4 * ((4 * t + half) ^ xs)) = u32x2{q[0], q[1]};
+        *reinterpret_cast<u32x2 *>(x + 4 * ((4 * t + 2 + half) ^ xs)) = u32x2{q[2], q[3]};
+      }
+    }
+  };
+  typedef s16x4 __attribute__((address_space(3))) *lds4;
+  typedef short s16x8 __attribute__((ext_vector_type(8)));
+  // lane = key, k-slots = queries krel(8 t + e, half)
+  auto get_op = [&](int t, bf16x8 (&op)[NP]) {
+    const int ra = 16 * t + xrow, rb = ra + 8;
+    const int oa = ra * 32 + 4 * (xunit ^ (ra >> 2)), ob = rb * 32 + 4 * (xunit ^ (rb >> 2));
+#pragma unroll
+    for (int p = 0; p < NP; ++p) {
+      const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds4)(Xw + p * 1024 + oa));
+      const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds4)(Xw + p * 1024 + ob));
+      op[p] = __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+    }
+  };
+  // acc += X^T B with B a staged [query][d] tile
+  auto product = [&](const uint16_t *B, f32x16 (&acc)[NC]) {
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+      bf16x8 av[NP];
+      get_op(t, av);
+#pragma unroll
+      for (int c = 0; c < NC; ++c) {
+        bf16x8 bv[NP];
+#pragma unroll
+        for (int p = 0; p < NP; ++p) bv[p] = tr_op<RS>(B + p * PS + 16 * t * RS + 32 * c);
+        acc[c] = mma<NP>(av, bv, acc[c]);
+      }
+    }
+  };
+
+  if (nt > 0) {
+    fq.fetch(qs, qstart, T, tid);
+    fd.fetch(dos, qstart, T, tid);
+    fetch_rec(qstart);
+  }
   for (int t = 0; t < nt; ++t) {
-    const int buf = t & 1;
     const int i0 = qstart + t * BQ;
-    if (t + 1 < nt) fetch(i0 + BQ);
+    uint16_t *Qb = Tl[t & 1], *dOb = Qb + St::SIZE;
+    fq.stash(Qb, tid);
+    fd.stash(dOb, tid);
+    lds_barrier();
+    if (t > 0) flush(t - 1);
+    fq.fetch(qs, i0 + BQ, T, tid);
+    fd.fetch(dos, i0 + BQ, T, tid);
 
     float ps = 0.f, pm = 0.f;
-    const bool active = (jw < T) & !(a.causal & (jw > i0 + 31));
-    if (active) {
-      const float *Qb = Qs[buf], *dOb = dOs[buf];
+    if ((jw < T) & !(a.causal & (jw > i0 + 31))) {
       // the forward's decided positions of this (query, key) tile (one byte
       // per key under FWM with Nearest)
+      const size_t tile = ds_tile(bh, i0 / 32, jw / 32, nq, a.causal) * 1024;
       float u[16];
       uint4 cw;
-      {
-        const float *ut = a.st.U + ds_tile(bh, i0 / 32, jw / 32, nq, a.causal) * 1024;
-        if constexpr (COMPACT) cw = codes_load(ut, lane);
-        else tile_load(ut, lane, u);
-      }
-      float dop[D / 2];
-      {
-        const float *dr = dOb + l32 * DS + half * (D / 2);
-#pragma unroll
-        for (int s = 0; s < D / 2; s += 4) {
-          f32x4 y = *reinterpret_cast<const f32x4 *>(dr + s);
-#pragma unroll
-          for (int e = 0; e < 4; ++e) dop[s + e] = y[e];
-        }
-      }
-      f32x16 G;
-#pragma unroll
-      for (int e = 0; e < 16; ++e) G[e] = 0.f;
-#pragma unroll
-      for (int s = 0; s < D / 2; ++s) G = mfma32(vop[s], dop[s], G);
-
-      const float *rr = Rec[buf] + l32 * RR_COUNT;
-      const f32x4 r0 = *reinterpret_cast<const f32x4 *>(rr);
-      const f32x4 r1 = *reinterpret_cast<const f32x4 *>(rr + 4);
-      const f32x4 r2 = *reinterpret_cast<const f32x4 *>(rr + 8);
-      const f32x4 r3 = *reinterpret_cast<const f32x4 *>(rr + 12);
-      RowConst rc;
-      rc.alpha = r0[0]; rc.beta = r0[1]; rc.margin2 = r0[2]; rc.hl = r0[3];
-      rc.b1l = r1[0]; rc.emh = r1[1]; rc.dcoef = r1[2];
-      rc.degen = r3[0] != 0.f;
-      const float invWf = r1[3], invWX = r2[0], negDXW = r2[1];
-
+      if constexpr (COMPACT) cw = codes_load(a.st.U + tile, lane);
+      else tile_load(a.st.U + tile, lane, u);
+      const uint16_t *dr = dOb + l32 * RS + 8 * half;
+      const f32x16 G = score_tile<D, NP>([&](int p, int s) { return row_op(dr + p * PS + 16 * s); },
+                                         [&](int p, int s) { return vop[p][s]; },
+                                         [](bf16x8 x, bf16x8 y, f32x16 c) { return mfma16(y, x, c); });
+      // some pair of the tile is not valid: key j is valid for this lane's
+      // query i iff j <= jlim
+      const bool edge = (a.causal & (jw + 31 > i0)) | (i0 + 32 > T) | (jw + 32 > T);
       const int i = i0 + l32;
-      // key j is valid for this lane's query i iff j <= jlim
       const int jlim = i < T ? (a.causal ? i : T - 1) : -1;
       float P[16], dS[16];
       if constexpr (EXPW) {
@@ -252,98 +275,99 @@ __global__ __launch_bounds__(256) void bwd_main_kernel(BwdArgs a) {
         // BF16-exp); dz = gamma e (softmax; FP8-exp: the fp32
         // exponential's derivative through an identity rounding), BF16-exp
         // the backward of its casts, bf16(bf16(gamma) w)
+        if (edge) {
+#pragma unroll
+          for (int r = 0; r < 16; ++r) u[r] = jw + krel(r, half) <= jlim ? u[r] : 0.f;
+        }
+        const float invWf = r1[3], invWX = r2[0], negDXW = r2[1];
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
-          const bool valid = jw + krel(r, half) <= jlim;
           const float e = u[r];
           const float wf = RECON == REC_FP8EXP ? exp_weight_of<RECON>(e) : e;
           const float gamma = fmaf(G[r], invWX, negDXW);
-          const float dz = RECON == REC_BF16EXP ? bf16_rne(bf16_rne(gamma) * e) : gamma * e;
-          P[r] = valid ? wf * invWf : 0.f;
-          dS[r] = valid ? dz : 0.f;
+          dS[r] = RECON == REC_BF16EXP ? bf16_rne(bf16_rne(gamma) * e) : gamma * e;
+          P[r] = wf * invWf;
           ps += dS[r];
         }
       } else {
+        // a position whose weight is 0 (the FWM tail; below the argmin; minus
+        // infinity) where the key is not valid
+        constexpr float none = CALIB == CAL_FWM ? -1.f : CALIB == CAL_MINMAX ? -2.f : -INFINITY;
+        if constexpr (COMPACT) {
+          const uint32_t word[4] = {cw.x, cw.y, cw.z, cw.w};
+#pragma unroll
+          for (int r = 0; r < 16; ++r)  // r + up / 2, the tail -1/2
+            u[r] = fmaf((float)((word[r >> 2] >> (8 * (r & 3))) & 0xFFu), 0.5f, -0.5f);
+        }
+        if (edge) {
+#pragma unroll
+          for (int r = 0; r < 16; ++r) u[r] = jw + krel(r, half) <= jlim ? u[r] : none;
+        }
         // e' = e^{b_{r+1}} / W from one exponential (RR_B1LW): P is e' or
         // e' e^{-h} (LERP: the chord between them), dS = (g c1 + c0) e'
         const float b1lw = r3[1], c1 = r3[2], c0 = r3[3];
-        const float Wf = 1.f / invWf;
+        const float hl = minmax ? r0[3] : a.ghl, emh = minmax ? r1[1] : a.gemh;
+        const float invWf = r1[3], invWX = r2[0], negDXW = r2[1], dcoef = r1[2];
+        const float Wf = minmax ? 1.f / invWf : 0.f;
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
-          KeyDec kd;
-          if constexpr (COMPACT) kd = key_of_code(cw, r);
-          else kd = key_of<CALIB>(u[r], Kf);
-          const float Ep = __builtin_amdgcn_exp2f(fmaf(kd.rf, rc.hl, b1lw));
-          const float Elp = Ep * rc.emh;
-          const float wLp = fmaf(kd.t, Ep - Elp, Elp);
-          const float Pr = nearest ? (kd.up ? Ep : Elp) : wLp;
-          const bool valid = (jw + krel(r, half) <= jlim) & !kd.tail;
-          P[r] = valid ? Pr : 0.f;
-          dS[r] = valid ? fmaf(G[r], c1, c0) * Ep : 0.f;
+          float rf = floorf(u[r]);
+          if constexpr (!COMPACT) rf = fminf(minmax ? fmaxf(rf, 0.f) : rf, Kf - 1.f);
+          float arg = fmaf(rf, hl, b1lw);
+          if constexpr (CALIB == CAL_FWM) arg = u[r] < 0.f ? -INFINITY : arg;
+          if constexpr (minmax) arg = u[r] < -1.f ? -INFINITY : arg;
+          const float Ep = __builtin_amdgcn_exp2f(arg);
+          const float Elp = Ep * emh;
+          float t01 = u[r] - rf;
+          if constexpr (CALIB == CAL_RESOLVED) t01 = __builtin_amdgcn_fmed3f(t01, 0.f, 1.f);
+          float wLp = 0.f;
+          if constexpr (!nearest || minmax) wLp = fmaf(t01, Ep - Elp, Elp);
+          P[r] = nearest ? (t01 >= 0.5f ? Ep : Elp) : wLp;
+          dS[r] = fmaf(G[r], c1, c0) * Ep;
           ps += dS[r];
           if (want_cm) {
             // dw^L/dM = X - w^L - Delta u / K, X = (r w^L + t e^{b_{r+1}}) / K,
             // on the unscaled weights
             const float Eu = Ep * Wf, wL = wLp * Wf;
             const float gamma = fmaf(G[r], invWX, negDXW);
-            const float Delta = Eu * rc.dcoef;
-            const float uc = kd.rf + kd.t;
-            const float X = fmaf(kd.rf, wL, kd.t * Eu) * invK;
-            const float dM = X - wL - Delta * uc * invK;
-            pm += valid ? gamma * dM : 0.f;
+            const float Delta = Eu * dcoef;
+            const float uc = rf + t01;
+            const float X = fmaf(rf, wL, t01 * Eu) * invK;
+            pm += gamma * (X - wL - Delta * uc * invK);
           }
         }
       }
-      // dS tile to the scratch, lane-major (the dQ kernel's A operand)
-      {
-        tile_store(a.st.dS + ds_tile(bh, i0 / 32, jw / 32, nq, a.causal) * 1024, lane, dS);
+      // dS to its scratch tile, in the dQ product's operand type
+      if constexpr (NP == 3) {
+        tile_store(a.st.dS + tile, lane, dS);
+      } else {
+        // 2 KiB: element (lane l, register r) at (r/8)*512 + 8l + r%8
+        uint16_t *dst = reinterpret_cast<uint16_t *>(a.st.dS) + tile + 8 * lane;
+#pragma unroll
+        for (int t2 = 0; t2 < 2; ++t2) {
+          bf16x8 w[1];
+          to_pieces<1>(reinterpret_cast<const float(&)[8]>(dS[8 * t2]), w);
+          *reinterpret_cast<u32x4 *>(dst + 512 * t2) = __builtin_bit_cast(u32x4, w[0]);
+        }
       }
-      // dV += P^T dO  (A = P transposed through LDS, B = dO rows)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) Xw[krel(r, half) * XS + l32] = P[r];
-      float at[16];
-#pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        const f32x4 x = *reinterpret_cast<const f32x4 *>(Xw + l32 * XS + 16 * half + 4 * g);
-        at[4 * g] = x[0]; at[4 * g + 1] = x[1]; at[4 * g + 2] = x[2]; at[4 * g + 3] = x[3];
-      }
-#pragma unroll
-      for (int c = 0; c < NC; ++c)
-#pragma unroll
-        for (int st = 0; st < 16; ++st)
-          dva[c] = mfma32(at[st], dOb[(16 * half + st) * DS + 32 * c + l32], dva[c]);
-      // dK += dS^T Q
-#pragma unroll
-      for (int r = 0; r < 16; ++r) Xw[krel(r, half) * XS + l32] = dS[r];
-#pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        const f32x4 x = *reinterpret_cast<const f32x4 *>(Xw + l32 * XS + 16 * half + 4 * g);
-        at[4 * g] = x[0]; at[4 * g + 1] = x[1]; at[4 * g + 2] = x[2]; at[4 * g + 3] = x[3];
-      }
-#pragma unroll
-      for (int c = 0; c < NC; ++c)
-#pragma unroll
-        for (int st = 0; st < 16; ++st)
-          dka[c] = mfma32(at[st], Qb[(16 * half + st) * DS + 32 * c + l32], dka[c]);
+      const int tb2 = tr_base<D>(lane);
+      put_tile(P);
+      product(dOb + tb2, dva);
+      put_tile(dS);
+      product(Qb + tb2, dka);
     }
+    fetch_rec(i0 + BQ);  // the next tile's (past the last row: clamped)
     ps += __shfl_xor(ps, 32);
     pm += __shfl_xor(pm, 32);
     if (half == 0) {
-      Part[buf][(wave * 32 + l32) * 2] = ps;
-      Part[buf][(wave * 32 + l32) * 2 + 1] = pm;
+      float *pp = Part[t & 1];
+      pp[(wave * 32 + l32) * 2] = ps;
+      pp[(wave * 32 + l32) * 2 + 1] = pm;
     }
-    if (t + 1 < nt) stash(buf ^ 1);
+  }
+  if (nt > 0) {
     lds_barrier();
-    if (a.grad != GRAD_DETACH && tid < 32 && i0 + tid < T) {
-      float s = 0.f, mm = 0.f;
-#pragma unroll
-      for (int w = 0; w < 4; ++w) {
-        s += Part[buf][(w * 32 + tid) * 2];
-        mm += Part[buf][(w * 32 + tid) * 2 + 1];
-      }
-      const size_t ridx = (size_t)bh * T + i0 + tid;
-      put_row_sums(a, kb, ridx, s, mm, minmax);
-    }
+    flush(nt - 1);
   }
   // write dV, dK (lane -> column, register -> key)
 #pragma unroll
@@ -352,337 +376,17 @@ __global__ __launch_bounds__(256) void bwd_main_kernel(BwdArgs a) {
     for (int r = 0; r < 16; ++r) {
       const int j = jw + krel(r, half);
       if (j < T && 32 * c + l32 < D) {
-        if (a.qsplit > 1) {
-          atomicAdd(a.dv + slice + (size_t)j * D + 32 * c + l32, dva[c][r]);
-          atomicAdd(a.dk + slice + (size_t)j * D + 32 * c + l32, a.scale * dka[c][r]);
+        const size_t e = slice + (size_t)j * D + 32 * c + l32;
+        if (a.qsplit > 1) {  // parts of the query range add up (zeroed by bwd_pre)
+          atomicAdd(a.dv + e, dva[c][r]);
+          atomicAdd(a.dk + e, a.scale * dka[c][r]);
         } else {
-          a.dv[slice + (size_t)j * D + 32 * c + l32] = dva[c][r];
-          a.dk[slice + (size_t)j * D + 32 * c + l32] = a.scale * dka[c][r];
+          if (NP == 1 && a.dv16) a.dv16[e] = (uint16_t)(__float_as_uint(bf16_rne(dva[c][r])) >> 16);
+          else a.dv[e] = dva[c][r];
+          a.dk[e] = a.scale * dka[c][r];
         }
       }
     }
-}
-
-// ---------------------------------------------------------------------------
-// bwd_main for d <= 64 at two waves per SIMD: 8 waves per workgroup in two
-// groups of 4. The workgroup's 128 keys have V in LDS (read as the MFMA A
-// operand), so a wave keeps only its dV/dK accumulators in registers.
-// Group g takes the query tiles t = g, g+2, ...; each group has its own
-// tile buffers, two of them (iteration parity), and prefetches its next tile
-// into registers, so one workgroup barrier per iteration orders the stash
-// before the reads and the reads of two iterations back before the stash.
-// The row sums of a tile's dS are added up (and sent out) one iteration
-// later, behind that same barrier. The two groups' partial dV/dK are summed
-// through LDS at the end.
-template <int D, int CALIB, int RECON>
-__global__ __launch_bounds__(512, 2) void bwd_main_shared_kernel(BwdArgs a) {
-  constexpr int NC = Dims<D>::NC, DS = Dims<D>::DS, DP = Dims<D>::DP;
-  constexpr int QV4 = BQ * DP / 4;         // float4 per Q (or dO) tile
-  constexpr int PF = (QV4 + 255) / 256;    // float4 per group thread and tensor
-  // One LDS block: V of the workgroup's keys, the Q / dO tiles and row
-  // records [group][parity], the wave-private transpose tiles and the row-sum
-  // partials [group][parity]. After the loop its start holds the second
-  // group's dV/dK for the final reduction (clear of the partials).
-  constexpr int KVF = BKV * DS, QT = BQ * DS, RT = BQ * RR_COUNT, PT = 4 * 32 * 2;
-  constexpr int OFF_Q = KVF, OFF_DO = OFF_Q + 4 * QT, OFF_REC = OFF_DO + 4 * QT;
-  constexpr int OFF_X = OFF_REC + 4 * RT, OFF_PART = OFF_X + 8 * 32 * XS;
-  constexpr int LDS_FLOATS = OFF_PART + 4 * PT;
-  static_assert(OFF_PART >= 4 * NC * 16 * 64 * 2, "reduction buffer");
-  __shared__ __attribute__((aligned(16))) float L[LDS_FLOATS];
-  float *Vb = L, *Xt = L + OFF_X;
-
-  const int tid = threadIdx.x;
-  const int lane = tid & 63, wave = tid >> 6, half = lane >> 5, l32 = lane & 31;
-  // key tile wk of the wave: group 1 takes the tiles in reverse order, so
-  // that the two waves sharing a SIMD (waves w and w + 4) own key tiles wk
-  // and 3 - wk, and the tiles idle on the causal diagonal (the high ones of a
-  // key block's first query tiles) never leave both waves of a SIMD idle
-  const int grp = wave >> 2, wk = grp ? 3 - (wave & 3) : (wave & 3), gtid = tid & 255;
-  const int T = a.T;
-  const int nq = (T + 31) / 32;
-  // key block (ascending: the longest causal key blocks first) and the part
-  // of its query range (qsplit parts of nearly equal tile counts)
-  const int kb = (int)(blockIdx.x / a.BH) / a.qsplit;
-  const int qpart = (int)(blockIdx.x / a.BH) % a.qsplit;
-  const int bh = blockIdx.x % a.BH;
-  const int j0 = kb * BKV;
-  const int jw = j0 + 32 * wk;
-  const size_t slice = (size_t)bh * T * D;
-  const float *qs = a.q + slice, *vs = a.v + slice,
-              *dos = a.dO + slice;
-  constexpr bool minmax = CALIB == CAL_MINMAX;
-  constexpr bool nearest = RECON == REC_NEAREST;
-  constexpr bool EXPW = is_exp_rec(RECON);
-  constexpr bool COMPACT = compact_codes<CALIB, RECON>();
-  const bool want_cm = minmax & grad_channels(a.grad);
-  const float invK = 1.f / (float)a.K, Kf = (float)a.K;
-
-  // V of the workgroup's keys: buffer loads issued first (keys past T and
-  // padded columns read as zeros), stashed after the first tile's fetch is
-  // in flight
-  constexpr int VL = BKV * DP / 4 / 512;  // 16-byte vectors per thread
-  static_assert(BKV * DP / 4 % 512 == 0, "whole passes");
-  f32x4 vpre[VL];
-  {
-    const uint32_t voff = row_vec_offset<D>(tid);
-#pragma unroll
-    for (int e = 0; e < VL; ++e)
-      vpre[e] = buffer_f32x4(row_rsrc(vs, j0 + e * (2048 / DP), T, D), voff);
-  }
-  auto stash_v = [&]() {
-#pragma unroll
-    for (int e = 0; e < VL; ++e) {
-      const int idx = tid + 512 * e;
-      const int r = idx / (DP / 4), c4 = idx % (DP / 4);
-      *reinterpret_cast<f32x4 *>(Vb + r * DS + c4 * 4) = vpre[e];
-    }
-  };
-
-  f32x16 dva[NC], dka[NC];
-#pragma unroll
-  for (int c = 0; c < NC; ++c)
-#pragma unroll
-    for (int e = 0; e < 16; ++e) { dva[c][e] = 0.f; dka[c][e] = 0.f; }
-
-  // Q and dO rows through buffer loads (rows past T and padded columns read
-  // as zeros); row records past T replaced by padding when stashed
-  static_assert(QV4 % 256 == 0, "whole passes");
-  const uint32_t qoff = row_vec_offset<D>(gtid);
-  f32x4 pq[PF], pd[PF], pr;
-  bool rok;
-  auto fetch = [&](int i0) {
-#pragma unroll
-    for (int e = 0; e < PF; ++e) {
-      const int rb = i0 + e * (1024 / DP);  // 256 threads cover 1024 / DP rows
-      pq[e] = buffer_f32x4(row_rsrc(qs, rb, T, D), qoff);
-      pd[e] = buffer_f32x4(row_rsrc(dos, rb, T, D), qoff);
-    }
-    {
-      const int r = (gtid / (RR_COUNT / 4)) % BQ, c4 = gtid % (RR_COUNT / 4);
-      rok = (gtid < BQ * RR_COUNT / 4) & (i0 + r < T);
-      const size_t rix = (size_t)bh * T + (rok ? i0 + r : 0);
-      pr = *reinterpret_cast<const f32x4 *>(a.st.rowrec + rix * RR_COUNT + c4 * 4);
-    }
-  };
-  auto stash = [&](int buf) {
-    float *Qd = L + OFF_Q + (2 * grp + buf) * QT, *dOd = L + OFF_DO + (2 * grp + buf) * QT;
-#pragma unroll
-    for (int e = 0; e < PF; ++e) {
-      const int idx = gtid + 256 * e;
-      const int r = idx / (DP / 4), c4 = idx % (DP / 4);
-      *reinterpret_cast<f32x4 *>(Qd + r * DS + c4 * 4) = pq[e];
-      *reinterpret_cast<f32x4 *>(dOd + r * DS + c4 * 4) = pd[e];
-    }
-    if (gtid < BQ * RR_COUNT / 4) {
-      // padding rows: u = K (beta = K), never ambiguous
-      const f32x4 pad = {0.f, (gtid % (RR_COUNT / 4)) == 0 ? (float)a.K : 0.f, 0.f, 0.f};
-      *reinterpret_cast<f32x4 *>(L + OFF_REC + (2 * grp + buf) * RT + gtid * 4) = rok ? pr : pad;
-    }
-  };
-
-  const int q0 = a.causal ? j0 : 0;
-  const int ntall = (T - q0 + BQ - 1) / BQ;
-  const int tb = ntall * qpart / a.qsplit, te = ntall * (qpart + 1) / a.qsplit;
-  const int qstart = q0 + tb * BQ;
-  const int nt = te - tb;
-  const int npair = (nt + 1) / 2;
-  float *Xw = Xt + wave * 32 * XS;
-  // row sums of iteration itp's tile: the four waves' partials, then one
-  // atomic per row
-  auto flush = [&](int itp) {
-    const int tp = 2 * itp + grp, ip = qstart + tp * BQ;
-    if (a.grad != GRAD_DETACH && wk == 0 && lane < 32 && tp < nt && ip + lane < T) {
-      const float *pp = L + OFF_PART + (2 * grp + (itp & 1)) * PT;
-      float sv = 0.f, mm = 0.f;
-#pragma unroll
-      for (int w = 0; w < 4; ++w) {
-        sv += pp[(w * 32 + lane) * 2];
-        mm += pp[(w * 32 + lane) * 2 + 1];
-      }
-      const size_t ridx = (size_t)bh * T + ip + lane;
-      put_row_sums(a, kb, ridx, sv, mm, minmax);
-    }
-  };
-  // the forward's decided positions of the wave's (query, key) tile, loaded
-  // at the end of the group's previous tile (behind its barrier wait and
-  // stash); the tile index is clamped into the stored tiles, so the load
-  // needs no branch (its data is unused for an inactive tile)
-  auto u_tile = [&](int tt) -> const float * {
-    const int qt = min((qstart + tt * BQ) / 32, nq - 1);
-    const int kt = min(jw / 32, a.causal ? qt : nq - 1);
-    return a.st.U + ds_tile(bh, qt, kt, nq, a.causal) * 1024;
-  };
-  float u[16];
-  uint4 cw;
-  auto load_u = [&](int tt) {
-    if constexpr (COMPACT) cw = codes_load(u_tile(tt), lane);
-    else tile_load(u_tile(tt), lane, u);
-  };
-  if (grp < nt) fetch(qstart + grp * BQ);
-  load_u(grp);  // behind the fetch, which the stash waits for
-  stash_v();
-  for (int it = 0; it < npair; ++it) {
-    const int t = 2 * it + grp, buf = it & 1;
-    const int i0 = qstart + t * BQ;
-    if (t < nt) stash(buf);
-    lds_barrier();
-    if (it > 0) flush(it - 1);
-    if (t + 2 < nt) fetch(i0 + 2 * BQ);
-
-    float ps = 0.f, pm = 0.f;
-    const bool active = (t < nt) & (jw < T) & !(a.causal & (jw > i0 + 31));
-    if (active) {
-      const float *Qb = L + OFF_Q + (2 * grp + buf) * QT;
-      const float *dOb = L + OFF_DO + (2 * grp + buf) * QT;
-      const float *vr = Vb + (32 * wk + l32) * DS + half * (D / 2);
-      const float *dr = dOb + l32 * DS + half * (D / 2);
-      f32x16 G;
-#pragma unroll
-      for (int e = 0; e < 16; ++e) G[e] = 0.f;
-#pragma unroll
-      for (int s = 0; s < D / 2; s += 4) {
-        const f32x4 x = *reinterpret_cast<const f32x4 *>(vr + s);
-        const f32x4 y = *reinterpret_cast<const f32x4 *>(dr + s);
-#pragma unroll
-        for (int e = 0; e < 4; ++e) G = mfma32(x[e], y[e], G);
-      }
-
-      const float *rr = L + OFF_REC + (2 * grp + buf) * RT + l32 * RR_COUNT;
-      const f32x4 r0 = *reinterpret_cast<const f32x4 *>(rr);
-      const f32x4 r1 = *reinterpret_cast<const f32x4 *>(rr + 4);
-      const f32x4 r2 = *reinterpret_cast<const f32x4 *>(rr + 8);
-      const f32x4 r3 = *reinterpret_cast<const f32x4 *>(rr + 12);
-      RowConst rc;
-      rc.alpha = r0[0]; rc.beta = r0[1]; rc.margin2 = r0[2]; rc.hl = r0[3];
-      rc.b1l = r1[0]; rc.emh = r1[1]; rc.dcoef = r1[2];
-      rc.degen = r3[0] != 0.f;
-      const float invWf = r1[3], invWX = r2[0], negDXW = r2[1];
-
-      const int i = i0 + l32;
-      // key j is valid for this lane's query i iff j <= jlim
-      const int jlim = i < T ? (a.causal ? i : T - 1) : -1;
-      float P[16], dS[16];
-      if constexpr (EXPW) {
-        // u holds the forward's fp32 exponential e (bf16-rounded for
-        // BF16-exp); dz = gamma e (softmax; FP8-exp: the fp32
-        // exponential's derivative through an identity rounding), BF16-exp
-        // the backward of its casts, bf16(bf16(gamma) w)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const bool valid = jw + krel(r, half) <= jlim;
-          const float e = u[r];
-          const float wf = RECON == REC_FP8EXP ? exp_weight_of<RECON>(e) : e;
-          const float gamma = fmaf(G[r], invWX, negDXW);
-          const float dz = RECON == REC_BF16EXP ? bf16_rne(bf16_rne(gamma) * e) : gamma * e;
-          P[r] = valid ? wf * invWf : 0.f;
-          dS[r] = valid ? dz : 0.f;
-          ps += dS[r];
-        }
-      } else {
-        // e' = e^{b_{r+1}} / W from one exponential (RR_B1LW): P is e' or
-        // e' e^{-h} (LERP: the chord between them), dS = (g c1 + c0) e'
-        const float b1lw = r3[1], c1 = r3[2], c0 = r3[3];
-        const float Wf = 1.f / invWf;
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          KeyDec kd;
-          if constexpr (COMPACT) kd = key_of_code(cw, r);
-          else kd = key_of<CALIB>(u[r], Kf);
-          const float Ep = __builtin_amdgcn_exp2f(fmaf(kd.rf, rc.hl, b1lw));
-          const float Elp = Ep * rc.emh;
-          const float wLp = fmaf(kd.t, Ep - Elp, Elp);
-          const float Pr = nearest ? (kd.up ? Ep : Elp) : wLp;
-          const bool valid = (jw + krel(r, half) <= jlim) & !kd.tail;
-          P[r] = valid ? Pr : 0.f;
-          dS[r] = valid ? fmaf(G[r], c1, c0) * Ep : 0.f;
-          ps += dS[r];
-          if (want_cm) {
-            // dw^L/dM = X - w^L - Delta u / K, X = (r w^L + t e^{b_{r+1}}) / K,
-            // on the unscaled weights
-            const float Eu = Ep * Wf, wL = wLp * Wf;
-            const float gamma = fmaf(G[r], invWX, negDXW);
-            const float Delta = Eu * rc.dcoef;
-            const float uc = kd.rf + kd.t;
-            const float X = fmaf(kd.rf, wL, kd.t * Eu) * invK;
-            const float dM = X - wL - Delta * uc * invK;
-            pm += valid ? gamma * dM : 0.f;
-          }
-        }
-      }
-      {
-        tile_store(a.st.dS + ds_tile(bh, i0 / 32, jw / 32, nq, a.causal) * 1024, lane, dS);
-      }
-#pragma unroll
-      for (int r = 0; r < 16; ++r) Xw[krel(r, half) * XS + l32] = P[r];
-      float at[16];
-#pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        const f32x4 x = *reinterpret_cast<const f32x4 *>(Xw + l32 * XS + 16 * half + 4 * g);
-        at[4 * g] = x[0]; at[4 * g + 1] = x[1]; at[4 * g + 2] = x[2]; at[4 * g + 3] = x[3];
-      }
-#pragma unroll
-      for (int c = 0; c < NC; ++c)
-#pragma unroll
-        for (int st = 0; st < 16; ++st)
-          dva[c] = mfma32(at[st], dOb[(16 * half + st) * DS + 32 * c + l32], dva[c]);
-#pragma unroll
-      for (int r = 0; r < 16; ++r) Xw[krel(r, half) * XS + l32] = dS[r];
-#pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        const f32x4 x = *reinterpret_cast<const f32x4 *>(Xw + l32 * XS + 16 * half + 4 * g);
-        at[4 * g] = x[0]; at[4 * g + 1] = x[1]; at[4 * g + 2] = x[2]; at[4 * g + 3] = x[3];
-      }
-#pragma unroll
-      for (int c = 0; c < NC; ++c)
-#pragma unroll
-        for (int st = 0; st < 16; ++st)
-          dka[c] = mfma32(at[st], Qb[(16 * half + st) * DS + 32 * c + l32], dka[c]);
-    }
-    load_u(t + 2);  // the group's next tile
-    ps += __shfl_xor(ps, 32);
-    pm += __shfl_xor(pm, 32);
-    if (half == 0) {
-      float *pp = L + OFF_PART + (2 * grp + buf) * PT;
-      pp[(wk * 32 + l32) * 2] = ps;
-      pp[(wk * 32 + l32) * 2 + 1] = pm;
-    }
-  }
-  // sum the two groups' dV/dK (group 1 -> LDS -> group 0) and store; the
-  // buffer overlaps V and the tiles, so wait for every wave (a workgroup
-  // with an empty query part runs no loop iteration and its V stash may
-  // still be landing); the last tile's row sums go out behind that barrier
-  float *red = L + (size_t)wk * (NC * 16 * 64 * 2);
-  lds_barrier();
-  if (npair > 0) flush(npair - 1);
-  if (grp == 1) {
-#pragma unroll
-    for (int c = 0; c < NC; ++c)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        red[((c * 16 + r) * 2) * 64 + lane] = dva[c][r];
-        red[((c * 16 + r) * 2 + 1) * 64 + lane] = dka[c][r];
-      }
-  }
-  lds_barrier();
-  if (grp == 0) {
-#pragma unroll
-    for (int c = 0; c < NC; ++c)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int j = jw + krel(r, half);
-        const float dvv = dva[c][r] + red[((c * 16 + r) * 2) * 64 + lane];
-        const float dkv = dka[c][r] + red[((c * 16 + r) * 2 + 1) * 64 + lane];
-        if (j < T && 32 * c + l32 < D) {
-          if (a.qsplit > 1) {
-            atomicAdd(a.dv + slice + (size_t)j * D + 32 * c + l32, dvv);
-            atomicAdd(a.dk + slice + (size_t)j * D + 32 * c + l32, a.scale * dkv);
-          } else {
-            a.dv[slice + (size_t)j * D + 32 * c + l32] = dvv;
-            a.dk[slice + (size_t)j * D + 32 * c + l32] = a.scale * dkv;
-          }
-        }
-      }
-  }
 }
 
 // ---------------------------------------------------------------------------
@@ -1246,6 +950,7 @@ __global__ __launch_bounds__(256) void bwd_p1_kernel(BwdArgsT<TI> a) {
   }
 }
 
+#if KIA_HEAD == 64  // no head dimension: once
 // ---------------------------------------------------------------------------
 // bf16-output variant: the fp32 dQ, dK accumulators rounded once to bf16
 // (nearest even), 8 elements per thread (n8 groups of 8).
@@ -1305,39 +1010,35 @@ __global__ __launch_bounds__(256) void score_grad_kernel(GradArgs a) {
   }
 }
 
-#define KIA_MAIN_INST(KERNEL, D)                                        \
-  template __global__ void KERNEL<D, CAL_MINMAX, REC_LERP>(BwdArgs);    \
-  template __global__ void KERNEL<D, CAL_MINMAX, REC_NEAREST>(BwdArgs); \
-  template __global__ void KERNEL<D, CAL_FWM, REC_LERP>(BwdArgs);       \
-  template __global__ void KERNEL<D, CAL_FWM, REC_NEAREST>(BwdArgs);    \
-  template __global__ void KERNEL<D, CAL_RESOLVED, REC_LERP>(BwdArgs);    \
-  template __global__ void KERNEL<D, CAL_RESOLVED, REC_NEAREST>(BwdArgs); \
-  template __global__ void KERNEL<D, CAL_FWM, REC_SOFTMAX>(BwdArgs);    \
-  template __global__ void KERNEL<D, CAL_FWM, REC_BF16EXP>(BwdArgs);    \
-  template __global__ void KERNEL<D, CAL_FWM, REC_FP8EXP>(BwdArgs);
-KIA_MAIN_INST(bwd_main_shared_kernel, 16)
-KIA_MAIN_INST(bwd_main_shared_kernel, 32)
-KIA_MAIN_INST(bwd_main_shared_kernel, 64)
-KIA_MAIN_INST(bwd_main_kernel, 128)
+#endif
 
-#define KIA_INST(D)                                                       \
-  template __global__ void bwd_pre_kernel<D, float>(BwdArgs);             \
-  template __global__ void bwd_pre_kernel<D, uint16_t>(BwdArgs16);        \
-  template __global__ void bwd_dq_kernel<D, dq_tiles(D)>(BwdArgs);        \
-  template __global__ void bwd_ties_kernel<D, float>(BwdArgs);            \
-  template __global__ void bwd_ties_kernel<D, uint16_t>(BwdArgs16);     \
-  template __global__ void bwd_p1_kernel<D, float>(BwdArgs);              \
-  template __global__ void bwd_p1_kernel<D, uint16_t>(BwdArgs16);        \
-  template __global__ void calib_gather_kernel<D, float, 1>(BwdArgs);     \
-  template __global__ void calib_gather_kernel<D, float, 4>(BwdArgs);     \
-  template __global__ void calib_gather_kernel<D, uint16_t, 1>(BwdArgs16); \
-  template __global__ void calib_gather_kernel<D, uint16_t, 4>(BwdArgs16);
-KIA_INST(16)
-KIA_INST(32)
-KIA_INST(64)
-KIA_INST(128)
+// One head dimension per compilation (KIA_HEAD, set by the build).
+#define KIA_MAIN_GRID(TI, D)                                                          \
+  template __global__ void bwd_main_kernel<TI, D, CAL_MINMAX, REC_LERP>(BwdArgsT<TI>);    \
+  template __global__ void bwd_main_kernel<TI, D, CAL_MINMAX, REC_NEAREST>(BwdArgsT<TI>); \
+  template __global__ void bwd_main_kernel<TI, D, CAL_FWM, REC_LERP>(BwdArgsT<TI>);       \
+  template __global__ void bwd_main_kernel<TI, D, CAL_FWM, REC_NEAREST>(BwdArgsT<TI>);    \
+  template __global__ void bwd_main_kernel<TI, D, CAL_RESOLVED, REC_LERP>(BwdArgsT<TI>);  \
+  template __global__ void bwd_main_kernel<TI, D, CAL_RESOLVED, REC_NEAREST>(BwdArgsT<TI>);
+#define KIA_BWD_TI(TI, D)                                              \
+  KIA_MAIN_GRID(TI, D)                                                 \
+  template __global__ void bwd_pre_kernel<D, TI>(BwdArgsT<TI>);        \
+  template __global__ void bwd_ties_kernel<D, TI>(BwdArgsT<TI>);       \
+  template __global__ void bwd_p1_kernel<D, TI>(BwdArgsT<TI>);         \
+  template __global__ void calib_gather_kernel<D, TI, 1>(BwdArgsT<TI>); \
+  template __global__ void calib_gather_kernel<D, TI, 4>(BwdArgsT<TI>);
+#define KIA_BWD(D)                                                                \
+  KIA_BWD_TI(float, D)                                                            \
+  KIA_BWD_TI(uint16_t, D)                                                         \
+  template __global__ void bwd_main_kernel<float, D, CAL_FWM, REC_SOFTMAX>(BwdArgs); \
+  template __global__ void bwd_main_kernel<float, D, CAL_FWM, REC_BF16EXP>(BwdArgs); \
+  template __global__ void bwd_main_kernel<float, D, CAL_FWM, REC_FP8EXP>(BwdArgs);  \
+  template __global__ void bwd_dq_kernel<D, dq_tiles(D)>(BwdArgs);
+KIA_BWD(KIA_HEAD)
 
+#if KIA_HEAD == 64  // no head dimension: once
 template __global__ void row_sums_kernel<float>(BwdArgs);
 template __global__ void row_sums_kernel<uint16_t>(BwdArgs16);
+#endif
 
 }  // namespace kia

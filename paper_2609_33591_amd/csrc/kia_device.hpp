@@ -681,26 +681,30 @@ __device__ __forceinline__ f32x16 mma(const bf16x8 (&a)[NP], const bf16x8 (&b)[N
   }
 }
 
-// A contraction over d (D / 16 k-steps): ap(piece, s) and bp(piece, s) give
-// the A and B operands of piece `piece` at k-step s. One piece of A is live at
-// a time; the products of full size come last, so that only they round at the
-// size of the result.
-template <int D, int NP, class FA, class FB>
-__device__ __forceinline__ f32x16 score_tile(FA ap, FB bp) {
+// A contraction over d (D / 16 k-steps): op(piece, s) gives an operand's
+// piece `piece` at k-step s, mm(x, y, c) multiplies one of the outer and one of
+// the inner operand. One piece of the outer one is live at a time; the products
+// of full size come last, so that only they round at the size of the result.
+template <int D, int NP, class FX, class FY, class FM>
+__device__ __forceinline__ f32x16 score_tile(FX outer, FY inner, FM mm) {
   f32x16 acc;
 #pragma unroll
   for (int e = 0; e < 16; ++e) acc[e] = 0.f;
 #pragma unroll
   for (int i = NP - 1; i >= 0; --i) {
-    bf16x8 a[D / 16];
+    bf16x8 x[D / 16];
 #pragma unroll
-    for (int s = 0; s < D / 16; ++s) a[s] = ap(i, s);
+    for (int s = 0; s < D / 16; ++s) x[s] = outer(i, s);
 #pragma unroll
     for (int j = NP - 1 - i; j >= 0; --j)
 #pragma unroll
-      for (int s = 0; s < D / 16; ++s) acc = mfma16(a[s], bp(j, s), acc);
+      for (int s = 0; s < D / 16; ++s) acc = mm(x[s], inner(j, s), acc);
   }
   return acc;
+}
+template <int D, int NP, class FA, class FB>
+__device__ __forceinline__ f32x16 score_tile(FA ap, FB bp) {
+  return score_tile<D, NP>(ap, bp, [](bf16x8 x, bf16x8 y, f32x16 c) { return mfma16(x, y, c); });
 }
 // both operands in registers
 template <int D, int NP>

@@ -83,6 +83,13 @@ template <typename TI> struct BwdArgsT {
   // at the fp32 accumulators in stats, which cast_bf16_kernel rounds at the end
   const uint16_t *o16 = nullptr;
   uint16_t *dv16 = nullptr;
+  float ghl = 0.f, gemh = 1.f;  // grid constants of FWM and resolved (as RowConst hl, emh)
+};
+
+// Waves per SIMD of the backward's main kernel: at d = 128 the three pieces of
+// V and the dV and dK accumulators take more than half the registers.
+template <typename TI, int D> struct MainShape {
+  static constexpr int OCC = sizeof(TI) == 4 && D == 128 ? 1 : 2;
 };
 
 using FwdArgs = FwdArgsT<float>;
@@ -111,8 +118,8 @@ template <typename TI> struct ScoresArgsT {
 };
 template <int D, typename TI> __global__ void scores_kernel(ScoresArgsT<TI> a);
 template <int D, typename TI> __global__ void bwd_pre_kernel(BwdArgsT<TI> a);
-template <int D, int CALIB, int RECON> __global__ void bwd_main_kernel(BwdArgs a);
-template <int D, int CALIB, int RECON> __global__ void bwd_main_shared_kernel(BwdArgs a);
+template <typename TI, int D, int CALIB, int RECON>
+__global__ void bwd_main_kernel(BwdArgsT<TI> a);
 // query tiles per bwd_dq workgroup (x 2 key halves = its waves): two for
 // d <= 64 (smaller workgroups, four per CU, balance the causal groups
 // better), four for d = 128 (where the larger K chunk per thread would cost)
@@ -140,8 +147,8 @@ struct GeoArgs {
 };
 template <int D, int CALIB, int RECON, int LQ> __global__ void geometry_kernel(GeoArgs a);
 __global__ void mfma_probe_kernel(unsigned long long *out, int iters);
+
 // bf16-input kernels (kia_bf16.hip)
-template <int D, int CALIB, int RECON, bool SPLIT> __global__ void bwd16_main_kernel(BwdArgs16 a);
 template <int D> __global__ void bwd16_dq_kernel(BwdArgs16 a);
 
 }  // namespace kia
