@@ -296,15 +296,11 @@ void launch_bwd(const BwdArgsT<TI> &a, hipStream_t s) {
   }
   const int nq = (a.T + 31) / 32;
   timed("kia_bwd_dq", s, [&] {
-    if constexpr (B16) {
-      hipLaunchKernelGGL(bwd16_dq_kernel<D>, dim3(a.BH * ((nq + 3) / 4)), dim3(512), 0, s, a);
-    } else {
-      constexpr int QG = dq_tiles(D);
-      int items = 0;
-      for (int g = 0; g < (nq + QG - 1) / QG; ++g)
-        items += dq_pieces(g, a.T, a.causal, a.dq_piece, QG);
-      hipLaunchKernelGGL((bwd_dq_kernel<D, QG>), dim3(a.BH * items), dim3(128 * QG), 0, s, a);
-    }
+    constexpr int QG = dq_tiles(D);
+    int items = 0;
+    for (int g = 0; g < (nq + QG - 1) / QG; ++g)
+      items += dq_pieces(g, a.T, a.causal, a.dq_piece, QG);
+    hipLaunchKernelGGL((bwd_dq_kernel<TI, D, QG>), dim3(a.BH * items), dim3(128 * QG), 0, s, a);
     // deterministic backward: the unique extrema's calibration terms
     // gathered onto dK per 32 keys (bwd_dq leaves them out)
     // (four waves per 32 keys when the scans are long or the grid is
@@ -463,10 +459,10 @@ int attn_bwd(const TI *q, const TI *k, const TI *v, const float *o, const TI *dO
     if (blocks < cus || force)
       a.qsplit = std::min(8, std::max(force ? 2 : 1, (3 * cus + blocks) / (2 * blocks)));
   }
-  if (sizeof(TI) == 4 && g_grid != KIA_GRID_WIDE) {
+  if (g_grid != KIA_GRID_WIDE) {
     const bool force = g_grid == KIA_GRID_SPLIT;
     const int cus = device_cus();
-    // dQ (fp32 inputs): groups of dq_tiles(d) query tiles; when they do not
+    // dQ: groups of dq_tiles(d) query tiles; when they do not
     // fill the chip, cut their keys into pieces so that there are about two
     // pieces per CU
     const int qg = dq_tiles(d);

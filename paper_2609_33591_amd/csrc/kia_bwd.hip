@@ -393,26 +393,24 @@ __global__ __launch_bounds__(256, (MainShape<TI, D>::OCC)) void bwd_main_kernel(
 // dQ = scale * (dS K + calibration terms). One workgroup = 2 QG waves = QG
 // consecutive 32-query tiles of one (b,h) times two key halves (QG = 2 for
 // d <= 64, 4 for d = 128): keys stream in chunks of 64 (one 32-key tile per
-// half), staged transposed in LDS (K^T, row stride DQ_KTS) so that the four
-// consecutive keys a lane needs for four MFMA steps are one 16-byte read.
-// Each wave streams its own dS tiles in two fixed register sets (loop
-// unrolled by two), one step ahead; a K chunk is fetched into the single K
-// register set right after the previous chunk's stash. The key halves'
-// partial sums are added through LDS before the calibration epilogue.
-constexpr int DQ_KTS = 68;
-
-template <int D, int QG>
-__global__ __launch_bounds__(128 * QG) void bwd_dq_kernel(BwdArgs a) {
-  constexpr int NC = Dims<D>::NC, DP = Dims<D>::DP;
-  constexpr int NT = 128 * QG;      // threads: QG query tiles x 2 key halves
-  constexpr int CV4 = 64 * DP / 4;  // float4 of one 64-key chunk
-  constexpr int KF = CV4 / NT;      // per thread
-  static_assert(KF * NT == CV4, "chunk split");
-  static_assert(QG * NC * 16 * 64 <= 2 * DP * DQ_KTS, "reduction buffer");
-  __shared__ __attribute__((aligned(16))) float KtT[2][DP * DQ_KTS];
+// half), staged row-major in bf16 pieces and read through transposing reads;
+// a lane's own dS values are the A operand (split into pieces, or the bf16
+// tile as it is). The kernel is bound by the latency and bandwidth of the dS
+// tiles: each wave fetches its own two steps ahead, in two fixed register sets
+// (loop unrolled by two), and one staging buffer leaves room for four
+// workgroups per CU. The key halves' partial sums are added through LDS before
+// the calibration epilogue.
+template <typename TI, int D, int QG>
+__global__ __launch_bounds__(128 * QG, (DqShape<TI, D>::OCC)) void bwd_dq_kernel(BwdArgsT<TI> a) {
+  constexpr int NP = Pieces<TI>::N, NC = D >= 32 ? D / 32 : 1;
+  constexpr int NT = 128 * QG;  // threads: QG query tiles x 2 key halves
+  using St = Stage<D, 64, NT, TI>;
+  constexpr int RS = St::RS, PS = St::PS, RED = QG * NC * 16 * 64 * 2;
+  __shared__ __attribute__((aligned(16))) uint16_t Ks[St::SIZE > RED ? St::SIZE : RED];
 
   const int tid = threadIdx.x;
-  const int lane = tid & 63, wave = tid >> 6, half = lane >> 5, l32 = lane & 31;
+  const int lane = tid & 63, half = lane >> 5, l32 = lane & 31;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   // query tile pq of the QG and key half kh; key half 1 takes the query
   // tiles in reverse order, so that (QG = 4) the two waves of a SIMD (w and
   // w + 4) own query tiles pq and 3 - pq and their causal key ranges add up
@@ -434,13 +432,12 @@ __global__ __launch_bounds__(128 * QG) void bwd_dq_kernel(BwdArgs a) {
   const bool live = qt < nq;
   const int qtc = live ? qt : nq - 1;
   const size_t slice = (size_t)bh * T * D;
-  const float *ks = a.k + slice + (size_t)c0 * 64 * D;  // the piece's first key
+  const TI *ks = a.k + slice;
   const int nstep = c1 - c0;  // chunks of the piece
   const int ktmine = a.causal ? qtc : nq - 1;  // this wave's last key tile
   // this wave's tile of the piece's chunk p is kt = 2 (c0 + p) + kh; it is
   // used iff p < npw
   const int npw = !live || ktmine < kh ? 0 : max(0, min(c1, (ktmine - kh) / 2 + 1) - c0);
-  const int Tp = T - c0 * 64;  // keys from the piece's first key on
   const bool minmax = a.calib == CAL_MINMAX;
 
   f32x16 acc[NC];
@@ -449,58 +446,46 @@ __global__ __launch_bounds__(128 * QG) void bwd_dq_kernel(BwdArgs a) {
 #pragma unroll
     for (int e = 0; e < 16; ++e) acc[c][e] = 0.f;
 
-  // K chunks through buffer loads: keys at or past Tp and padded columns
-  // read as zeros
-  // (one register set for K: a chunk is fetched right after the previous
-  // one is stashed, one MFMA step before its own stash)
-  f32x4 kX[KF], dA[4], dB[4];
-  const uint32_t koff = row_vec_offset<D>(tid);
-  auto fetch_k = [&](int p) {
+  St fk;
+  auto fetch_k = [&](int p) { fk.fetch(ks, (c0 + min(p, nstep - 1)) * 64, T, tid); };
+  // a dS tile: 16 fp32 per lane, or 16 bf16
+  constexpr int ND = NP == 3 ? 4 : 2;
+  u32x4 dA[ND], dB[ND];
+  auto fetch_d = [&](int p, u32x4 (&dx)[ND]) {
+    const int kt = min(2 * (c0 + min(p, nstep - 1)) + kh, ktmine);  // past this wave's row: unused
+    const float *tile = a.st.dS + ds_tile(bh, qtc, kt, nq, a.causal) * 1024;
 #pragma unroll
-    for (int e = 0; e < KF; ++e)
-      kX[e] = buffer_f32x4(row_rsrc(ks, p * 64 + e * (4 * NT / DP), Tp, D), koff);
+    for (int e = 0; e < ND; ++e)
+      dx[e] = NP == 3 ? *reinterpret_cast<const u32x4 *>(tile + 256 * e + 4 * lane)
+                      : *reinterpret_cast<const u32x4 *>(
+                            reinterpret_cast<const uint16_t *>(a.st.dS) + (tile - a.st.dS) +
+                            512 * e + 8 * lane);
   };
-  auto fetch_d = [&](int p, f32x4 (&dx)[4]) {
-    const int kt = min(2 * (c0 + p) + kh, ktmine);  // past this wave's row: unused
-    const float *src = a.st.dS + ds_tile(bh, qtc, kt, nq, a.causal) * 1024 + 4 * lane;
+  const uint16_t *kb = Ks + kh * 32 * RS + tr_base<D>(lane);
+  auto mma_step = [&](const u32x4 (&dx)[ND]) {
 #pragma unroll
-    for (int e = 0; e < 4; ++e) dx[e] = *reinterpret_cast<const f32x4 *>(src + 256 * e);
-  };
-  auto stash = [&](int buf) {
+    for (int t = 0; t < 2; ++t) {
+      bf16x8 av[NP];
+      if constexpr (NP == 3) {
+        float x[8];
 #pragma unroll
-    for (int e = 0; e < KF; ++e) {
-      const int idx = tid + NT * e;
-      const int r = idx / (DP / 4), c4 = idx % (DP / 4);
-      // row d = 4 c4 + i holds key r at column r ^ sw(d): the 4-key groups
-      // of a row are permuted by sw(d) = 4 ((d >> 3) & 7), so that the
-      // lanes of a stash (16 rows d, 4 keys) fall in distinct banks
-      float *dst = &KtT[buf][(4 * c4) * DQ_KTS + (r ^ (((c4 >> 1) & 7) << 2))];
+        for (int e = 0; e < 8; ++e) x[e] = __uint_as_float(dx[2 * t + e / 4][e % 4]);
+        to_pieces<3>(x, av);
+      } else {
+        av[0] = as_op(dx[t]);
+      }
 #pragma unroll
-      for (int i = 0; i < 4; ++i) dst[i * DQ_KTS] = kX[e][i];
+      for (int c = 0; c < NC; ++c) {
+        bf16x8 bv[NP];
+#pragma unroll
+        for (int p = 0; p < NP; ++p) bv[p] = tr_op<RS>(kb + p * PS + 16 * t * RS + 32 * c);
+        acc[c] = mma<NP>(av, bv, acc[c]);
+      }
     }
   };
-  auto mma = [&](int buf, const f32x4 (&dx)[4]) {
-    const float *kb = KtT[buf] + l32 * DQ_KTS;
-#pragma unroll
-    for (int c = 0; c < NC; ++c)
-#pragma unroll
-      for (int g4 = 0; g4 < 4; ++g4) {
-        // keys kh*32 + krel(4 g4 + i, half), i = 0..3: consecutive, the 4-key
-        // group 8 kh + 2 g4 + half of row d = 32 c + l32, permuted as stashed
-        const int grp4 = (8 * kh + 2 * g4 + half) ^ (((32 * c + l32) >> 3) & 7);
-        const f32x4 bk = *reinterpret_cast<const f32x4 *>(kb + c * 32 * DQ_KTS + 4 * grp4);
-#pragma unroll
-        for (int i = 0; i < 4; ++i) acc[c] = mfma32(dx[g4][i], bk[i], acc[c]);
-      }
-  };
-  // prologue: chunk 0 in LDS buffer 0 with dA; chunk 1's dS tile in dB and
-  // its K behind the first stash. Fetches and stashes run on every step
-  // (chunk index clamped; surplus chunks are never used) so that the number
-  // of loads in flight is the same on every path and the compiler's waits
-  // stay one step behind.
   fetch_k(0);
   fetch_d(0, dA);
-  fetch_d(min(1, nstep - 1), dB);
+  fetch_d(1, dB);
   // the calibration epilogue's row statistics (lanes 0..31: one row each)
   // and the q rows of its dK scatter, loaded behind the first two chunks'
   // fetches (so the first stash does not wait for them) and landing during
@@ -521,32 +506,29 @@ __global__ __launch_bounds__(128 * QG) void bwd_dq_kernel(BwdArgs a) {
 #pragma unroll
       for (int x = 0; x < NE; ++x) {
         const int n = lane + 64 * x;
-        qv[u][x] = a.q[slice + (size_t)qr * D + (n < D ? n : 0)];
+        qv[u][x] = load1(a.q + slice + (size_t)qr * D + (n < D ? n : 0));
       }
     }
   };
   // (d = 128: the 32 more registers would cost the key loop; loaded at the end)
   if constexpr (NE == 1) load_qv();
-  stash(0);
-  fetch_k(min(1, nstep - 1));
-  lds_barrier();
+  auto step = [&](int p, u32x4 (&dx)[ND]) {
+    if (p > 0) lds_barrier();
+    fk.stash(Ks, tid);
+    fetch_k(p + 1);
+    lds_barrier();
+    if (p < npw) mma_step(dx);
+    fetch_d(p + 2, dx);
+  };
   for (int p = 0; p < nstep; p += 2) {
-    if (p < npw) mma(0, dA);
-    stash(1);
-    fetch_k(min(p + 2, nstep - 1));
-    fetch_d(min(p + 2, nstep - 1), dA);
-    lds_barrier();
+    step(p, dA);
     if (p + 1 >= nstep) break;
-    if (p + 1 < npw) mma(1, dB);
-    stash(0);
-    fetch_k(min(p + 3, nstep - 1));
-    fetch_d(min(p + 3, nstep - 1), dB);
-    lds_barrier();
+    step(p + 1, dB);
   }
-  // key half 1 hands its partial sums to key half 0 (the chunk buffers are
-  // free: the last step ended with a barrier)
+  // key half 1 hands its partial sums to key half 0
+  __syncthreads();
   {
-    float *red = &KtT[0][0] + pq * (NC * 16 * 64) + lane;
+    float *red = reinterpret_cast<float *>(Ks) + pq * (NC * 16 * 64) + lane;
     if (kh == 1) {
 #pragma unroll
       for (int c = 0; c < NC; ++c)
@@ -596,8 +578,8 @@ __global__ __launch_bounds__(128 * QG) void bwd_dq_kernel(BwdArgs a) {
       for (int c = 0; c < NC; ++c) {
         const int n = 32 * c + l32;
         const int nn = n < D ? n : 0;
-        kM[b][c] = a.k[slice + (size_t)iam * D + nn];
-        km[b][c] = minmax ? a.k[slice + (size_t)ian * D + nn] : 0.f;
+        kM[b][c] = load1(ks + (size_t)iam * D + nn);
+        km[b][c] = minmax ? load1(ks + (size_t)ian * D + nn) : 0.f;
       }
     }
 #pragma unroll
@@ -952,20 +934,6 @@ __global__ __launch_bounds__(256) void bwd_p1_kernel(BwdArgsT<TI> a) {
 
 #if KIA_HEAD == 64  // no head dimension: once
 // ---------------------------------------------------------------------------
-// bf16-output variant: the fp32 dQ, dK accumulators rounded once to bf16
-// (nearest even), 8 elements per thread (n8 groups of 8).
-__global__ __launch_bounds__(256) void cast_bf16_kernel(const float *src, uint16_t *dst,
-                                                       size_t n8) {
-  const size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
-  if (i >= n8) return;
-  const f32x4 x = *reinterpret_cast<const f32x4 *>(src + 8 * i);
-  const f32x4 y = *reinterpret_cast<const f32x4 *>(src + 8 * i + 4);
-  *reinterpret_cast<uint4 *>(dst + 8 * i) =
-      make_uint4(pack_bf16x2(x[0], x[1]), pack_bf16x2(x[2], x[3]), pack_bf16x2(y[0], y[1]),
-                 pack_bf16x2(y[2], y[3]));
-}
-
-// ---------------------------------------------------------------------------
 // Score-gradient decomposition export: g_self dense from the dS scratch
 // (fp32 tiles, or bf16 tiles of the bf16 variant) and the row sums of the
 // two extremum channels. One wave per (b,h, 32-query tile).
@@ -1023,6 +991,7 @@ __global__ __launch_bounds__(256) void score_grad_kernel(GradArgs a) {
 #define KIA_BWD_TI(TI, D)                                              \
   KIA_MAIN_GRID(TI, D)                                                 \
   template __global__ void bwd_pre_kernel<D, TI>(BwdArgsT<TI>);        \
+  template __global__ void bwd_dq_kernel<TI, D, dq_tiles(D)>(BwdArgsT<TI>); \
   template __global__ void bwd_ties_kernel<D, TI>(BwdArgsT<TI>);       \
   template __global__ void bwd_p1_kernel<D, TI>(BwdArgsT<TI>);         \
   template __global__ void calib_gather_kernel<D, TI, 1>(BwdArgsT<TI>); \
@@ -1032,8 +1001,7 @@ __global__ __launch_bounds__(256) void score_grad_kernel(GradArgs a) {
   KIA_BWD_TI(uint16_t, D)                                                         \
   template __global__ void bwd_main_kernel<float, D, CAL_FWM, REC_SOFTMAX>(BwdArgs); \
   template __global__ void bwd_main_kernel<float, D, CAL_FWM, REC_BF16EXP>(BwdArgs); \
-  template __global__ void bwd_main_kernel<float, D, CAL_FWM, REC_FP8EXP>(BwdArgs);  \
-  template __global__ void bwd_dq_kernel<D, dq_tiles(D)>(BwdArgs);
+  template __global__ void bwd_main_kernel<float, D, CAL_FWM, REC_FP8EXP>(BwdArgs);
 KIA_BWD(KIA_HEAD)
 
 #if KIA_HEAD == 64  // no head dimension: once

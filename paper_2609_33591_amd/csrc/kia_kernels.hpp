@@ -92,6 +92,11 @@ template <typename TI, int D> struct MainShape {
   static constexpr int OCC = sizeof(TI) == 4 && D == 128 ? 1 : 2;
 };
 
+// Waves per SIMD of the dQ kernel.
+template <typename TI, int D> struct DqShape {
+  static constexpr int OCC = D == 128 ? (sizeof(TI) == 4 ? 2 : 3) : 4;
+};
+
 using FwdArgs = FwdArgsT<float>;
 using CodesArgs = CodesArgsT<float>;
 using BwdArgs = BwdArgsT<float>;
@@ -124,7 +129,7 @@ __global__ void bwd_main_kernel(BwdArgsT<TI> a);
 // d <= 64 (smaller workgroups, four per CU, balance the causal groups
 // better), four for d = 128 (where the larger K chunk per thread would cost)
 constexpr int dq_tiles(int d) { return d <= 64 ? 2 : 4; }
-template <int D, int QG> __global__ void bwd_dq_kernel(BwdArgs a);
+template <typename TI, int D, int QG> __global__ void bwd_dq_kernel(BwdArgsT<TI> a);
 template <int D, typename TI> __global__ void bwd_ties_kernel(BwdArgsT<TI> a);
 template <int D, typename TI> __global__ void bwd_p1_kernel(BwdArgsT<TI> a);
 // deterministic backward: row sums from the key blocks' partials; the
@@ -147,8 +152,5 @@ struct GeoArgs {
 };
 template <int D, int CALIB, int RECON, int LQ> __global__ void geometry_kernel(GeoArgs a);
 __global__ void mfma_probe_kernel(unsigned long long *out, int iters);
-
-// bf16-input kernels (kia_bf16.hip)
-template <int D> __global__ void bwd16_dq_kernel(BwdArgs16 a);
 
 }  // namespace kia
