@@ -114,7 +114,7 @@ def _ptr(t, dtypes):
 def _shape(q):
     if q.dim() != 4:
         raise KiaError(f"q must be [B,H,T,d], got shape {tuple(q.shape)}")
-    return tuple(int(x) for x in q.shape)
+    return tuple(map(int, q.shape))
 
 
 def _same(q, named):
@@ -122,12 +122,13 @@ def _same(q, named):
     of `dtypes` and a contiguous layout (the C ABI takes sizes from q only,
     so a short buffer would become an out-of-bounds device access)."""
     shape = _shape(q)
+    size, device = q.shape, q.device
     for name, t, dtypes in named:
-        if tuple(t.shape) != shape:
+        if t.shape != size:
             raise KiaError(f"{name} has shape {tuple(t.shape)}, q has {shape}")
         if t.dtype not in dtypes:
             raise KiaError(f"{name} has dtype {t.dtype}, expected one of {dtypes}")
-        if t.device != q.device:
+        if t.device != device:
             raise KiaError(f"{name} is on {t.device}, q on {q.device}")
         if not t.is_contiguous():
             raise KiaError(f"{name} must be contiguous")
@@ -171,8 +172,12 @@ def _op_flags(shape, K, calib, tau, recon, ste, causal, in_dtype, nograd=False):
                 ste=_enum(ste, STE) if r == RECON["nearest"] else None, nograd=bool(nograd))
 
 
+# the same by plain values: a training loop repeats them call after call
+_flags = functools.lru_cache(maxsize=256)(_op_flags)
+
+
 def _stats_key(stats):
-    return (str(stats.device), int(stats.data_ptr()))
+    return (stats.device, int(stats.data_ptr()))
 
 
 def _record_forward(stats, flags):
@@ -183,7 +188,7 @@ def _check_forward(stats, flags, keys=None):
     """Raise if the forward that filled `stats` ran with other flags (only
     the `keys` given, default all)."""
     have = _FWD_FLAGS.get(_stats_key(stats))
-    if have is None:
+    if have is None or have is flags:
         return
     keys = keys or flags.keys()
     if "nograd" in keys and have["nograd"] and not flags["nograd"]:
@@ -197,8 +202,8 @@ def _check_forward(stats, flags, keys=None):
 
 def _stream(stream):
     import torch
-    if stream is None:
-        stream = torch.cuda.current_stream()
+    if stream is None:  # the current device's current stream
+        return ctypes.c_void_p(torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice()))
     return ctypes.c_void_p(stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream))
 
 
@@ -211,6 +216,22 @@ def _grad(mode) -> int:
     if isinstance(mode, str):
         return GRAD[mode]
     return int(mode)
+
+
+@functools.lru_cache(maxsize=256, typed=True)
+def _op_codes(K, calib, tau, recon, ste, detach, causal):
+    return (int(K), _enum(calib, CALIB), float(tau), _enum(recon, RECON), _enum(ste, STE),
+            _grad(detach), int(bool(causal)))
+
+
+_PLAIN = {int, float, str, bool}
+
+
+def _op(*args):
+    """(K, calib, tau, recon, ste, detach, causal) as the C ABI takes them.
+    Plain values are looked up; anything else (such as a 0-d tensor) is
+    converted on every call."""
+    return (_op_codes if _PLAIN.issuperset(map(type, args)) else _op_codes.__wrapped__)(*args)
 
 
 def kia_strerror(code: int) -> str:
@@ -245,35 +266,31 @@ def kia_stats_offset(B, H, T, d, recon, ste, causal, field) -> int:
 
 def _fwd(fn, q, k, v, o, stats, K, calib, tau, recon, ste, detach, causal, stream,
          in_dtype, o_dtypes):
-    import torch
-    shape = _same(q, [("k", k, (in_dtype,)), ("v", v, (in_dtype,)), ("o", o, o_dtypes)])
-    _check_stats(stats, q, shape, _enum(recon, RECON), _enum(ste, STE), causal)
-    B, H, T, d = shape
     ip = (in_dtype,)
-    _check(fn(_ptr(q, ip), _ptr(k, ip), _ptr(v, ip), _ptr(o, o_dtypes),
-              _ptr(stats, (torch.uint8,)), B, H, T, d, int(K), _enum(calib, CALIB),
-              float(tau), _enum(recon, RECON), _enum(ste, STE), _grad(detach),
-              int(bool(causal)), _stream(stream)))
-    _record_forward(stats, _op_flags(shape, K, calib, tau, recon, ste, causal, in_dtype,
-                                     nograd=_grad(detach) == GRAD["none"]))
+    shape = _same(q, (("k", k, ip), ("v", v, ip), ("o", o, o_dtypes)))
+    op = _op(K, calib, tau, recon, ste, detach, causal)
+    K, calib, tau, recon, ste, detach, causal = op
+    _check_stats(stats, q, shape, recon, ste, causal)
+    # (every other tensor has q's device and was checked above)
+    _check(fn(_ptr(q, ip), k.data_ptr(), v.data_ptr(), o.data_ptr(), stats.data_ptr(), *shape,
+              *op, _stream(stream)))
+    _record_forward(stats, _flags(shape, K, calib, tau, recon, ste, causal, in_dtype,
+                                  detach == GRAD["none"]))
 
 
 def _bwd(fn, q, k, v, o, dO, stats, dq, dk, dv, K, calib, tau, recon, ste, detach, causal,
          stream, in_dtype, o_dtypes, nbytes=None):
-    import torch
-    shape = _same(q, [("k", k, (in_dtype,)), ("v", v, (in_dtype,)), ("o", o, o_dtypes),
-                      ("dO", dO, (in_dtype,)), ("dq", dq, o_dtypes), ("dk", dk, o_dtypes),
-                      ("dv", dv, o_dtypes)])
-    if nbytes is not None:
-        nbytes = nbytes(*shape, _enum(recon, RECON), _enum(ste, STE), causal)
-    _check_stats(stats, q, shape, _enum(recon, RECON), _enum(ste, STE), causal, nbytes)
-    _check_forward(stats, _op_flags(shape, K, calib, tau, recon, ste, causal, in_dtype))
-    B, H, T, d = shape
     ip = (in_dtype,)
-    _check(fn(_ptr(q, ip), _ptr(k, ip), _ptr(v, ip), _ptr(o, o_dtypes), _ptr(dO, ip),
-              _ptr(stats, (torch.uint8,)), _ptr(dq, o_dtypes), _ptr(dk, o_dtypes),
-              _ptr(dv, o_dtypes), B, H, T, d, int(K), _enum(calib, CALIB), float(tau),
-              _enum(recon, RECON), _enum(ste, STE), _grad(detach), int(bool(causal)),
+    shape = _same(q, (("k", k, ip), ("v", v, ip), ("o", o, o_dtypes), ("dO", dO, ip),
+                      ("dq", dq, o_dtypes), ("dk", dk, o_dtypes), ("dv", dv, o_dtypes)))
+    op = _op(K, calib, tau, recon, ste, detach, causal)
+    K, calib, tau, recon, ste, detach, causal = op
+    if nbytes is not None:
+        nbytes = nbytes(*shape, recon, ste, causal)
+    _check_stats(stats, q, shape, recon, ste, causal, nbytes)
+    _check_forward(stats, _flags(shape, K, calib, tau, recon, ste, causal, in_dtype, False))
+    _check(fn(_ptr(q, ip), k.data_ptr(), v.data_ptr(), o.data_ptr(), dO.data_ptr(),
+              stats.data_ptr(), dq.data_ptr(), dk.data_ptr(), dv.data_ptr(), *shape, *op,
               _stream(stream)))
 
 
