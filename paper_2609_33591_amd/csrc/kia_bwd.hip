@@ -220,19 +220,21 @@ __global__ __launch_bounds__(256, (MainShape<TI, D>::OCC)) void bwd_main_kernel(
       op[p] = __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
     }
   };
-  // acc += X^T B with B a staged [query][d] tile
-  auto product = [&](const uint16_t *B, f32x16 (&acc)[NC]) {
+  // acc += X^T B with B a staged [query][d] tile and av the two k-steps of X:
+  // the operands of a column block are read while the previous one's products
+  // run
+  auto product = [&](const bf16x8 (&av)[2][NP], const uint16_t *B, f32x16 (&acc)[NC]) {
+    bf16x8 bv[2][NP];
+    auto read = [&](int n) {
 #pragma unroll
-    for (int t = 0; t < 2; ++t) {
-      bf16x8 av[NP];
-      get_op(t, av);
+      for (int p = 0; p < NP; ++p)
+        bv[n & 1][p] = tr_op<RS>(B + p * PS + 16 * (n / NC) * RS + 32 * (n % NC));
+    };
+    read(0);
 #pragma unroll
-      for (int c = 0; c < NC; ++c) {
-        bf16x8 bv[NP];
-#pragma unroll
-        for (int p = 0; p < NP; ++p) bv[p] = tr_op<RS>(B + p * PS + 16 * t * RS + 32 * c);
-        acc[c] = mma<NP>(av, bv, acc[c]);
-      }
+    for (int n = 0; n < 2 * NC; ++n) {
+      if (n + 1 < 2 * NC) read(n + 1);
+      acc[n % NC] = mma<NP>(av[n / NC], bv[n & 1], acc[n % NC]);
     }
   };
 
@@ -351,10 +353,26 @@ __global__ __launch_bounds__(256, (MainShape<TI, D>::OCC)) void bwd_main_kernel(
         }
       }
       const int tb2 = tr_base<D>(lane);
+      // (one piece: dS takes P's place in LDS before the first product, whose
+      // MFMAs its reads then run under: B4 H16 T2048 d128 350 -> 335 us; with
+      // three pieces the 24 more registers cost more than that)
+      bf16x8 x[2][NP], xd[2][NP];
       put_tile(P);
-      product(dOb + tb2, dva);
-      put_tile(dS);
-      product(Qb + tb2, dka);
+      get_op(0, x[0]);
+      get_op(1, x[1]);
+      if constexpr (NP == 1) {
+        put_tile(dS);
+        get_op(0, xd[0]);
+        get_op(1, xd[1]);
+        product(x, dOb + tb2, dva);
+        product(xd, Qb + tb2, dka);
+      } else {
+        product(x, dOb + tb2, dva);
+        put_tile(dS);
+        get_op(0, x[0]);
+        get_op(1, x[1]);
+        product(x, Qb + tb2, dka);
+      }
     }
     fetch_rec(i0 + BQ);  // the next tile's (past the last row: clamped)
     ps += __shfl_xor(ps, 32);
