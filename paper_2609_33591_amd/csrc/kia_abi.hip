@@ -495,10 +495,8 @@ int attn_bwd(const TI *q, const TI *k, const TI *v, const float *o, const TI *dO
   if (bo) {
     const size_t n8 = (size_t)B * H * T * d / 8;
     timed("kia_cast_bf16", s, [&] {
-      const dim3 grid((unsigned)((n8 + 255) / 256)), block(256);
-      hipLaunchKernelGGL(cast_bf16_kernel, grid, block, 0, s, dq, bo->dq, n8);
-      hipLaunchKernelGGL(cast_bf16_kernel, grid, block, 0, s, dk, bo->dk, n8);
-      if (!a.dv16) hipLaunchKernelGGL(cast_bf16_kernel, grid, block, 0, s, dv, bo->dv, n8);
+      const dim3 grid((unsigned)((n8 + 255) / 256), a.dv16 ? 2 : 3), block(256);
+      hipLaunchKernelGGL(cast_bf16_kernel, grid, block, 0, s, dq, bo->dq, bo->dk, bo->dv, n8);
     });
   }
   return launched();

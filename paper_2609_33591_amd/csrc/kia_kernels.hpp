@@ -136,7 +136,8 @@ template <int D, typename TI> __global__ void bwd_p1_kernel(BwdArgsT<TI> a);
 // calibration terms of rows with unique extrema gathered onto dK per key
 template <typename TI> __global__ void row_sums_kernel(BwdArgsT<TI> a);
 template <int D, typename TI, int NW> __global__ void calib_gather_kernel(BwdArgsT<TI> a);
-__global__ void cast_bf16_kernel(const float *src, uint16_t *dst, size_t n8);
+__global__ void cast_bf16_kernel(const float *src, uint16_t *dq, uint16_t *dk, uint16_t *dv,
+                                 size_t n8);
 struct GradArgs {
   Stats st;
   float *g_self, *cM, *cm;
