@@ -6,6 +6,7 @@
 #include <string.h>
 
 #include <algorithm>
+#include <cmath>
 #include <mutex>
 #include <vector>
 
@@ -411,6 +412,28 @@ int attn_fwd(const TI *q, const TI *k, const TI *v, float *o, void *stats, int B
   return launched();
 }
 
+// Parts into which the main kernel splits each key block's query range. A
+// split shortens the longest workgroup (the causal key block 0, with L query
+// tiles) until the tiles are spread over the chip's slots, and each part adds
+// its dK and dV atomically: about 0.05 us a part over the whole chip at
+// d = 64, 0.02 of a tile's time with fp32 inputs and 0.035 with bf16. The
+// least of L / n + cost n blocks is n = sqrt(L / (cost blocks)). Measured (us;
+// 1 / 2 / 3 / 4 / 6 parts) at T = 1024, d = 64: fp32 96 blocks 99 / 55 / 44 /
+// 39 / 47, 192 blocks 100 / 63 / 55 / 67 / 86, 320 blocks 105 / 75 / 90; bf16
+// 96 blocks 50 / 30 / 25 / 28, 192 blocks 51 / 34 / 41; T = 4096, 256 blocks
+// 399 / 255 / 201 / 199 / 212; bf16 T = 8192 d = 128, 256 blocks 726 / 438 /
+// 336 / 326 / 349.
+int main_parts(int BH, int T, int d, bool f32, int causal) {
+  if (g_grid == KIA_GRID_WIDE) return 1;
+  const double blocks = (double)BH * ((T + 127) / 128), L = (T + 31) / 32;
+  const double slots = device_cus() * (f32 && d == 128 ? 1.0 : 2.0);
+  const double cost = (f32 ? 0.02 : 0.035) * std::min(d, 80) / 64.0;
+  // no further than the point where every slot is busy throughout
+  const double most = std::ceil((causal ? 2.0 : 1.0) * slots / blocks);
+  int n = (int)std::min(8.0, std::min(most, std::floor(std::sqrt(L / (cost * blocks)) + 0.5)));
+  return std::max(n, g_grid == KIA_GRID_SPLIT ? 2 : 1);
+}
+
 template <typename TI>
 int attn_bwd(const TI *q, const TI *k, const TI *v, const float *o, const TI *dO,
              void *stats, float *dq, float *dk, float *dv, int B, int H, int T, int d, int K,
@@ -446,19 +469,8 @@ int attn_bwd(const TI *q, const TI *k, const TI *v, const float *o, const TI *dO
   a.st = make_stats(stats, B, H, T, d, recon, ste, causal);
   a.BH = B * H; a.T = T; a.K = K; a.calib = calib; a.recon = recon;
   a.ste = ste; a.grad = detach; a.causal = causal;
-  // small grids (the paper's micro-batch-1 calls): split the query range of
-  // each key block of the main kernel into about 1.5 workgroups per CU
-  // (one fits per CU; measured best against 1, 2 and 3 per CU: the split
-  // parts pay their V load and their atomic dK/dV epilogue each)
-  a.qsplit = 1;
+  a.qsplit = main_parts(B * H, T, d, sizeof(TI) == 4, causal);
   a.dq_piece = 0;
-  if (g_grid != KIA_GRID_WIDE) {
-    const bool force = g_grid == KIA_GRID_SPLIT;
-    const int cus = device_cus();
-    const int blocks = B * H * ((T + 127) / 128);
-    if (blocks < cus || force)
-      a.qsplit = std::min(8, std::max(force ? 2 : 1, (3 * cus + blocks) / (2 * blocks)));
-  }
   if (g_grid != KIA_GRID_WIDE) {
     const bool force = g_grid == KIA_GRID_SPLIT;
     const int cus = device_cus();
