@@ -746,8 +746,10 @@ __device__ __forceinline__ void load_rows(const TI *slice, int row, int T, int h
 // The lane's operand of 32 query rows, and the factor that takes a product
 // with them back to q.k (1 for bf16 inputs). The pieces of a value below
 // 2^-109 would lose bits under bf16's smallest 2^-133, so a row that holds one
-// is scaled up by a power of two first (towards a maximum of 2^60), which is
-// exact; every other row has the factor 1.
+// is scaled up by a power of two first, which is exact: 2^24 takes fp32's last
+// bit, 2^-149, to a normal bf16, and is no larger because q.k has to stay
+// finite (and less where the row's maximum would pass 2^60); every other row
+// has the factor 1.
 template <int D, typename TI>
 __device__ __forceinline__ float load_query(const TI *slice, int row, int T, int half,
                                             bf16x8 (&op)[Pieces<TI>::N][D / 16]) {
@@ -773,7 +775,7 @@ __device__ __forceinline__ float load_query(const TI *slice, int row, int T, int
     big = fmaxf(big, __shfl_xor(big, 32));
     tiny = tiny | (__shfl_xor(tiny ? 1 : 0, 32) != 0);
     // exponent of the row's largest element (denormals: -127)
-    const int up = tiny ? min(max(60 - ((int)(__float_as_uint(big) >> 23) - 127), 0), 100) : 0;
+    const int up = tiny ? min(max(60 - ((int)(__float_as_uint(big) >> 23) - 127), 0), 24) : 0;
     const float f = ldexpf(1.f, up);
 #pragma unroll
     for (int s = 0; s < D / 16; ++s) {
