@@ -23,13 +23,18 @@
  *     fields) at most KIA_MAX_STATS_BYTES (else KIA_ERR_SHAPE, also from
  *     kia_stats_bytes). The softmax scale is fixed to fl32(1/sqrt(d)) and a
  *     score is fl32(fl32(q.k) * scale) (the fp32 scores of App. A).
+ *   - Products of fp32 operands are formed from three bf16 pieces each (an
+ *     exact sum) with fp32 accumulation; their error is below that of an
+ *     fp32 product. Inputs are finite: an infinite element, or one that
+ *     rounds to infinity in bf16 (above about 3.39e38), makes the results it
+ *     enters NaN.
  *   - Determinism: the forward is bitwise repeatable. By default the
  *     backward is not: the row sums of every key block's score gradients
  *     (S_self, and cM under MinMax) are accumulated with float atomics, and
  *     so are the calibration terms and tie splits scattered onto the
  *     argmax/argmin keys of dK, so dQ and dK can differ in their last bits
- *     from run to run (within fp32 rounding); dV is repeatable unless a
- *     small grid is split (KIA_GRID_*). kia_set_deterministic(1) makes
+ *     from run to run (within fp32 rounding); dV is repeatable unless the
+ *     query ranges are split (KIA_GRID_*). kia_set_deterministic(1) makes
  *     every backward reduction run in a fixed order, so that the backward
  *     too is bitwise repeatable.
  *   - calib: 0 MinMax, 1 FWM, 2 resolved (FWM and resolved need a finite
@@ -130,8 +135,8 @@ extern "C" {
 /* Forward only (the forward's gradient mode when no backward will read its
  * stats, e.g. an evaluation or inference pass): the forward leaves out what
  * only the backward reads, O^L = P^L V of Prob-STE with Nearest (a third of
- * that forward's matrix work) and, on the fp32 entry points, the per-key
- * decisions its second pass would store in U. O and every per-row statistic
+ * that forward's matrix work) and the per-key decisions its second pass
+ * would store in U. O and every per-row statistic
  * are the same as under the other modes. The backward entry points and
  * kia_attn_fwd_bwd_static reject it (KIA_ERR_ENUM, nothing enqueued); a
  * backward or kia_debug_codes_stored on stats that such a forward filled is
@@ -153,11 +158,10 @@ extern "C" {
  *   backward's dS scratch: B*H*n tiles of 32x32 f32 (4 KiB each) with
  *   n = q(q+1)/2 for causal and q*q otherwise, q = ceil(T/32) (about
  *   2*B*H*T^2 bytes causal, 4*B*H*T^2 otherwise); then U, tiles of the same
- *   shape and count: the forward's fp32 scores Q K^T of every (query, key)
- *   pair that its extrema pass computed, replaced by its second pass with
- *   the decided grid position u of the pair (the value the index decisions
- *   of the conventions above were taken from), so that the backward neither
- *   recomputes the scores nor the decisions; under FWM with Nearest, whose
+ *   shape and count: the decided grid position u of every (query, key) pair
+ *   (the value the index decisions of the conventions above were taken
+ *   from), written by the forward's second pass, so that the backward
+ *   neither recomputes the scores nor the decisions; under FWM with Nearest, whose
  *   backward needs only the interval, the level bit and the tail, by one
  *   byte per key instead (1 + 2r + [t >= 1/2], 0 for the tail) in the first
  *   KiB of each tile. Element order inside a tile is the kernels' register
@@ -445,17 +449,17 @@ int kia_timing_read(const char *name, double *total_ms, int *launches);
 
 /*
  * Launch-shape policy (process-wide, not thread-safe; affects later calls).
- * KIA_GRID_AUTO (default) picks per call: when a problem's natural grid
- * leaves the CUs short of work (micro-batch-1 shapes), the kernels split it
- * -- the fp32 forward takes one 32-row group with four key quarters per
- * workgroup (d <= 64; eight key parts in 8-wave workgroups when there are
- * fewer 64-row blocks than CUs) instead of two row groups with two key
- * halves, the backward's main kernel (fp32 and bf16 inputs) splits each key
- * block's query range over several workgroups (dK, dV added atomically) and
- * the fp32 dQ kernel each group of query tiles' keys over several pieces
- * (dQ added atomically). KIA_GRID_WIDE never splits;
- * KIA_GRID_SPLIT always does (the forward's four key quarters, the
- * backward's splits in at least two parts). The policies compute the same decisions,
+ * KIA_GRID_AUTO (default) picks per call. The forward takes workgroups of
+ * 128 rows where there are more than two such blocks per CU, of two 32-row
+ * groups with two key halves down to one per CU, and below that of one row
+ * group with four key quarters (fp32 inputs at d = 64 below half a block per
+ * CU: eight key parts). The backward's main kernel splits each key block's
+ * query range over several workgroups where that shortens the longest one by
+ * more than the added atomics cost (dK, dV added atomically), and where the
+ * dQ kernel's groups of query tiles do not fill the chip their keys are cut
+ * into pieces (dQ added atomically); both for fp32 and bf16 inputs.
+ * KIA_GRID_WIDE never splits; KIA_GRID_SPLIT always does (the forward's
+ * smallest row groups, the backward's splits in at least two parts). The policies compute the same decisions,
  * extrema and codes; O, W and the gradients differ only in fp32 summation
  * order (neither backward is bitwise repeatable: see Determinism above).
  * Returns KIA_ERR_ENUM for another value.

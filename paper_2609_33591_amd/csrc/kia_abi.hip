@@ -254,7 +254,7 @@ void launch_codes(const CodesArgsT<TI> &a, int recon, hipStream_t s) {
   });
 }
 
-// ---- bf16 inputs ----------------------------------------------------------
+// ---- backward ------------------------------------------------------------
 template <typename TI, int D, int CALIB, int RECON>
 void launch_main(const BwdArgsT<TI> &a, int nkb, hipStream_t s) {
   hipLaunchKernelGGL((bwd_main_kernel<TI, D, CALIB, RECON>), dim3(a.BH * nkb), dim3(256), 0, s, a);
@@ -265,8 +265,8 @@ void launch_main_c(const BwdArgsT<TI> &a, int nkb, hipStream_t s) {
   else launch_main<TI, D, CALIB, REC_NEAREST>(a, nkb, s);
 }
 
-// The backward's four launches; TI selects the fp32 or the bf16-input
-// main and dQ kernels (pre-pass and tie path are shared templates).
+// The backward's launches: pre-pass, main, dQ and, by gradient mode, ties or
+// the P1 projection. Every kernel is one template over the input type TI.
 template <int D, typename TI>
 void launch_bwd(const BwdArgsT<TI> &a, hipStream_t s) {
   constexpr bool B16 = sizeof(TI) == 2;
@@ -474,9 +474,8 @@ int attn_bwd(const TI *q, const TI *k, const TI *v, const float *o, const TI *dO
   if (g_grid != KIA_GRID_WIDE) {
     const bool force = g_grid == KIA_GRID_SPLIT;
     const int cus = device_cus();
-    // dQ: groups of dq_tiles(d) query tiles; when they do not
-    // fill the chip, cut their keys into pieces so that there are about two
-    // pieces per CU
+    // dQ: groups of dq_tiles(d) query tiles; when they do not fill the chip,
+    // their keys are cut into pieces so that there are about two per CU
     const int qg = dq_tiles(d);
     const int npq = (T + 32 * qg - 1) / (32 * qg);
     if (B * H * npq < cus || force) {

@@ -104,15 +104,6 @@ __device__ __forceinline__ f32x16 mfma32(float a, float b, f32x16 c) {
   return __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, c, 0, 0, 0);
 }
 
-// Column blocks of the PV-type products are 32 wide: d = 16 is padded to
-// 32 zero columns in LDS and never stored.
-template <int D> struct Dims {
-  static constexpr int DP = D < 32 ? 32 : D;  // padded width
-  static constexpr int NC = DP / 32;          // 32-wide column blocks
-  static constexpr int DS = DP + 4;           // LDS row stride (floats)
-  static constexpr int FWD_WAVES_PER_EU = D <= 64 ? 2 : 1;
-};
-
 __device__ __forceinline__ int krel(int r, int half) {
   return 8 * (r >> 2) + 4 * half + (r & 3);
 }
@@ -339,20 +330,6 @@ __host__ __device__ constexpr bool compact_codes() {
   return CALIB == CAL_FWM && RECON == REC_NEAREST;
 }
 
-// The byte of a decided key (exact small integer as a float): tail keys
-// (FWM: rf <= -1) give a value <= 0, stored as 0.
-__device__ __forceinline__ float code_value(const KeyDec &kd) {
-  return fmaxf(fmaf(kd.rf, 2.f, kd.up ? 2.f : 1.f), 0.f);
-}
-
-// Register r's byte into the lane's four code words (packed as the keys
-// are decided, so that only four words stay live).
-// v_cvt_pk_u8_f32 converts and inserts one byte; the values are exact
-// integers in [0, 2K], so its rounding and saturation do not matter.
-__device__ __forceinline__ void code_put(uint32_t (&w)[4], int r, const KeyDec &kd) {
-  w[r >> 2] = __builtin_amdgcn_cvt_pk_u8_f32(code_value(kd), r & 3, (r & 3) ? w[r >> 2] : 0u);
-}
-
 // The lane's 16 bytes of the tile (one 16-byte store).
 __device__ __forceinline__ void codes_store(float *tile, int lane, const uint32_t (&w)[4]) {
   *reinterpret_cast<uint4 *>(reinterpret_cast<char *>(tile) + 16 * lane) =
@@ -544,27 +521,6 @@ __device__ __forceinline__ void tile_store(float *tile, int lane, const float (&
 }
 
 // ---- buffer loads of row blocks ---------------------------------------------
-// A buffer resource over rows [r0, rend) of a row-major [*, D] fp32 array:
-// loads at byte offsets at or past its end read as zeros (the hardware's
-// range check), so ragged tails need no address clamping or masking on the
-// vector units.
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t row_rsrc(const float *base, int r0,
-                                                          int rend, int D) {
-  const int rb = min(r0, rend);
-  return __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(base) + (size_t)rb * D,
-                                           (short)0, (rend - rb) * D * 4, 0x00020000);
-}
-__device__ __forceinline__ f32x4 buffer_f32x4(__amdgpu_buffer_rsrc_t rs, uint32_t voff) {
-  return __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rs, voff, 0, 0));
-}
-// Byte offset of 16-byte vector idx of a row block (DP / 4 vectors a row);
-// padded columns (c >= D) point past the end of any buffer.
-template <int D> __device__ __forceinline__ uint32_t row_vec_offset(int idx) {
-  constexpr int DP = Dims<D>::DP;
-  const int r = idx / (DP / 4), c4 = idx % (DP / 4);
-  return c4 * 4 < D ? (uint32_t)(r * D + c4 * 4) * 4u : 0x80000000u;
-}
-
 // ---- gradient modes (the backward's `detach` argument) ---------------------
 // 0 full (Eq. full), 1 detach, 2 max_only / 3 min_only (one extremum
 // channel; appendix on the detached-gradient record), 4 detach with the P1
@@ -600,16 +556,6 @@ __device__ __forceinline__ float load1(const uint16_t *p) { return bf2f(*p); }
 __device__ __forceinline__ f32x16 mfma16(bf16x8 a, bf16x8 b, f32x16 c) {
   return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
 }
-__device__ __forceinline__ bf16x8 as_bf16x8(uint4 x) {
-  return __builtin_bit_cast(bf16x8, x);
-}
-__device__ __forceinline__ bf16x8 to_bf16x8(const float *v) {
-  bf16x8 r;
-#pragma unroll
-  for (int e = 0; e < 8; ++e) r[e] = (__bf16)v[e];
-  return r;
-}
-
 // ---- operand pieces --------------------------------------------------------
 // LDS and operand vectors that alias the element types they are staged as
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4), may_alias));
