@@ -672,13 +672,12 @@ __device__ __forceinline__ void tie_rows(const BwdArgsT<TI> &a, int bh, int rb, 
   }
   if (!__any(tierow)) return;
   // the row's scores with the canonical sub-tile of the input type
-  constexpr int NP = Pieces<TI>::N;
-  bf16x8 qop[NP][D / 16];
-  const float qf = load_query<D>(a.q + slice, i < T ? i : T - 1, T, half, qop);
+  ScoreOp<TI, D> qop;
+  const float qf = qop.load_q(a.q + slice, i < T ? i : T - 1, T, half);
   auto tile_scores = [&](int js) -> f32x16 {
-    bf16x8 kop[NP][D / 16];
-    load_rows<D>(a.k + slice, js + l32, T, half, kop);
-    return qf * score_tile<D, NP>(kop, qop);
+    ScoreOp<TI, D> kop;
+    kop.load(a.k + slice, js + l32, T, half);
+    return qf * ScoreOp<TI, D>::tile(kop, qop);
   };
   const int kend = a.causal ? min(T, rb * 32 + 32) : T;
   for (int js = 0; js < kend; js += 32) {

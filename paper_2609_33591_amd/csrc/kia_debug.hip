@@ -15,7 +15,6 @@ constexpr int CODES_BN = 64;
 template <int D, int CALIB, int REC, typename TI>
 __global__ __launch_bounds__(256) void codes_kernel(CodesArgsT<TI> a) {
   constexpr bool EXPW = is_exp_rec(REC);
-  constexpr int NP = Pieces<TI>::N;
   const int tid = threadIdx.x;
   const int lane = tid & 63, wave = tid >> 6, half = lane >> 5, l32 = lane & 31;
   const int T = a.T;
@@ -25,8 +24,8 @@ __global__ __launch_bounds__(256) void codes_kernel(CodesArgsT<TI> a) {
   const int i0 = qb * CODES_BM, iw = i0 + wave * 32, row = iw + l32;
   const size_t slice = (size_t)bh * T * D;
   const float Kf = (float)a.K;
-  bf16x8 qop[NP][D / 16];
-  const float qf = load_query<D>(a.q + slice, row < T ? row : T - 1, T, half, qop);
+  ScoreOp<TI, D> qop;
+  const float qf = qop.load_q(a.q + slice, row < T ? row : T - 1, T, half);
   const size_t ridx = (size_t)bh * T + (row < T ? row : T - 1);
   const float Mx = a.st.M[ridx];
   const float Mn = CALIB != CAL_FWM ? a.st.m[ridx] : Mx;
@@ -45,10 +44,9 @@ __global__ __launch_bounds__(256) void codes_kernel(CodesArgsT<TI> a) {
 #pragma unroll
         for (int r = 0; r < 16; ++r) code[r] = 0;
       } else {
-        bf16x8 kop[NP][D / 16];
-        load_rows<D>(a.k + slice, js + l32, T, half, kop);
-        const f32x16 acc =
-            qf * score_tile<D, NP>(kop, qop);
+        ScoreOp<TI, D> kop;
+        kop.load(a.k + slice, js + l32, T, half);
+        const f32x16 acc = qf * ScoreOp<TI, D>::tile(kop, qop);
         if constexpr (EXPW) {
           // bit 15 valid; bits 0-14 the bf16 pattern (BF16-exp) or the E4M3
           // byte (FP8-exp) of the weight, 0 for softmax (w <= 1: bit 14 clear)
@@ -180,7 +178,6 @@ __global__ __launch_bounds__(256) void stored_codes_kernel(StoredCodesArgs a) {
 // keys that are not valid. Same sub-tile and operand loads as codes_kernel.
 template <int D, typename TI>
 __global__ __launch_bounds__(256) void scores_kernel(ScoresArgsT<TI> a) {
-  constexpr int NP = Pieces<TI>::N;
   const int tid = threadIdx.x;
   const int lane = tid & 63, wave = tid >> 6, half = lane >> 5, l32 = lane & 31;
   const int T = a.T;
@@ -189,8 +186,8 @@ __global__ __launch_bounds__(256) void scores_kernel(ScoresArgsT<TI> a) {
   const int qb = nqb - 1 - (int)(blockIdx.x / a.BH);
   const int i0 = qb * CODES_BM, iw = i0 + wave * 32, row = iw + l32;
   const size_t slice = (size_t)bh * T * D;
-  bf16x8 qop[NP][D / 16];
-  const float qf = load_query<D>(a.q + slice, row < T ? row : T - 1, T, half, qop);
+  ScoreOp<TI, D> qop;
+  const float qf = qop.load_q(a.q + slice, row < T ? row : T - 1, T, half);
   const int ntiles = (T + CODES_BN - 1) / CODES_BN;
   for (int t = 0; t < ntiles; ++t) {
     const int j0 = t * CODES_BN;
@@ -198,10 +195,9 @@ __global__ __launch_bounds__(256) void scores_kernel(ScoresArgsT<TI> a) {
     for (int sub = 0; sub < CODES_BN / 32; ++sub) {
       const int js = j0 + sub * 32;
       if (js >= T) continue;
-      bf16x8 kop[NP][D / 16];
-        load_rows<D>(a.k + slice, js + l32, T, half, kop);
-        const f32x16 acc =
-            qf * score_tile<D, NP>(kop, qop);
+      ScoreOp<TI, D> kop;
+        kop.load(a.k + slice, js + l32, T, half);
+        const f32x16 acc = qf * ScoreOp<TI, D>::tile(kop, qop);
       if (row < T) {
         float *dst = a.scores + ((size_t)bh * T + row) * T;
 #pragma unroll
@@ -241,8 +237,8 @@ __global__ __launch_bounds__(256) void geometry_kernel(GeoArgs a) {
   const float Kf = (float)K;
   for (int e = tid; e < CODES_BM * NB; e += 256) bucket[e] = 0.f;
   __syncthreads();
-  bf16x8 qop[3][D / 16];
-  const float qf = load_query<D>(a.q + slice, row < T ? row : T - 1, T, half, qop);
+  ScoreOp<float, D> qop;
+  const float qf = qop.load_q(a.q + slice, row < T ? row : T - 1, T, half);
   float qss = 0.f, kss = 0.f;
   {
     const int rr = row < T ? row : T - 1;
@@ -292,10 +288,9 @@ __global__ __launch_bounds__(256) void geometry_kernel(GeoArgs a) {
       for (int sub = 0; sub < CODES_BN / 32; ++sub) {
         const int js = j0 + sub * 32;
         if (js >= T || (a.causal && js > iw + 31)) continue;  // wave-uniform
-        bf16x8 kop[3][D / 16];
-        load_rows<D>(a.k + slice, js + l32, T, half, kop);
-        const f32x16 acc =
-            qf * score_tile<D, 3>(kop, qop);
+        ScoreOp<float, D> kop;
+        kop.load(a.k + slice, js + l32, T, half);
+        const f32x16 acc = qf * ScoreOp<float, D>::tile(kop, qop);
         float u[16];
         decide_u<CALIB>(acc, rc, M, Mn, K, a.tau, a.scale, u);
 #pragma unroll

@@ -16,8 +16,9 @@
 // 4.1e-7 and 3.4e-7. bf16 inputs are one piece and one product.
 //
 // Canonical score sub-tile. Every kernel that needs a score s_ij computes it
-// with score_tile(): a 32-key x 32-query block of S^T accumulated by
-// v_mfma_f32_32x32x16_bf16 over d in one fixed order, with the key block and
+// with ScoreOp::tile(): a 32-key x 32-query block of S^T accumulated by
+// v_mfma_f32_32x32x16_bf16 (fp32 inputs at d = 128: by the fp32 MFMA, see
+// ScoreOp) over d in one fixed order, with the key block and
 // the query block aligned to multiples of 32. The A operand is K (rows =
 // keys), the B operand Q (columns = queries). Lane l (half h = l/32) feeds,
 // at k-step s, K[key0 + l%32][16 s + 8 h + e] and Q[query0 + l%32][16 s + 8 h
@@ -736,6 +737,63 @@ __device__ __forceinline__ float load_query(const TI *slice, int row, int T, int
   }
 }
 
+// ---- score operands ----------------------------------------------------------
+// fp32 scores at d = 128 stay on v_mfma_f32_32x32x2_f32, in one summation order:
+// lane l feeds, at k-step s, K[key0 + l%32][64 (l/32) + s] and the same of Q. An
+// index decision jumps where a score's rounding does, so this also leaves the
+// decisions at d = 128 where they were. Six piece products would take the
+// registers of a second wave per SIMD (Q and K in three pieces each); the fp32
+// operand takes half of that. Forward (us, piece products / this): B4 H16 T2048
+// MinMax LERP 803 / 690, FWM Nearest Prob-STE 928 / 909; B1 H40 T1024 196 / 148
+// and 231 / 202; B1 H12 T1024 77 / 68 and 90 / 79; B1 H16 T8192 MinMax LERP
+// 2747 / 2602.
+template <typename TI, int D> __host__ __device__ constexpr bool fp32_scores() {
+  return sizeof(TI) == 4 && D == 128;
+}
+template <typename TI, int D, bool EX = fp32_scores<TI, D>()> struct ScoreOp {
+  bf16x8 v[Pieces<TI>::N][D / 16];
+  // a row of a [T, D] slice (rows at or beyond T read as zero)
+  __device__ __forceinline__ void load(const TI *slice, int row, int T, int half) {
+    load_rows<D>(slice, row, T, half, v);
+  }
+  // the same of q, and the factor that takes a product with it back to q.k
+  __device__ __forceinline__ float load_q(const TI *slice, int row, int T, int half) {
+    return load_query<D>(slice, row, T, half, v);
+  }
+  static __device__ __forceinline__ f32x16 tile(const ScoreOp &k, const ScoreOp &q) {
+    return score_tile<D, Pieces<TI>::N>(k.v, q.v);
+  }
+};
+template <typename TI, int D> struct ScoreOp<TI, D, true> {
+  float v[D / 2];
+  __device__ __forceinline__ void read(const float *p) {
+#pragma unroll
+    for (int s = 0; s < D / 2; s += 4) {
+      const f32x4 x = *reinterpret_cast<const f32x4 *>(p + s);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) v[s + e] = x[e];
+    }
+  }
+  __device__ __forceinline__ void load(const float *slice, int row, int T, int half) {
+    const bool ok = row < T;
+    read(slice + (size_t)(ok ? row : 0) * D + half * (D / 2));
+#pragma unroll
+    for (int s = 0; s < D / 2; ++s) v[s] = ok ? v[s] : 0.f;
+  }
+  __device__ __forceinline__ float load_q(const float *slice, int row, int T, int half) {
+    load(slice, row, T, half);
+    return 1.f;
+  }
+  static __device__ __forceinline__ f32x16 tile(const ScoreOp &k, const ScoreOp &q) {
+    f32x16 acc;
+#pragma unroll
+    for (int e = 0; e < 16; ++e) acc[e] = 0.f;
+#pragma unroll
+    for (int s = 0; s < D / 2; ++s) acc = mfma32(k.v[s], q.v[s], acc);
+    return acc;
+  }
+};
+
 // ---- staging of row blocks in LDS ------------------------------------------
 // A [ROWS, D] block staged as bf16 pieces [piece][row][D + 8] (the row stride
 // of D / 2 + 4 dwords puts the 16-byte reads of eight consecutive rows in
@@ -779,6 +837,40 @@ template <int D, int ROWS, int NT, typename TI> struct Stage {
       } else {
         *reinterpret_cast<u32x4 *>(d) = x[e][0];
       }
+    }
+  }
+};
+
+// A buffer resource over rows [r0, rend) of a row-major [*, D] fp32 array:
+// loads at byte offsets at or past its end read as zeros (the hardware's
+// range check), so ragged tails need no address clamping or masking on the
+// vector units.
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t row_rsrc(const float *base, int r0,
+                                                          int rend, int D) {
+  const int rb = min(r0, rend);
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(base) + (size_t)rb * D,
+                                           (short)0, (rend - rb) * D * 4, 0x00020000);
+}
+__device__ __forceinline__ f32x4 buffer_f32x4(__amdgpu_buffer_rsrc_t rs, uint32_t voff) {
+  return __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rs, voff, 0, 0));
+}
+// A [ROWS, D] fp32 block staged as it is (row stride D + 4).
+template <int D, int ROWS, int NT> struct StageF32 {
+  static constexpr int RS = D + 4, SIZE = ROWS * RS;  // floats
+  static constexpr int V4 = ROWS * D / 4, PF = (V4 + NT - 1) / NT, RPP = NT * 4 / D;
+  static_assert(V4 % NT == 0 || PF == 1, "whole passes");
+  f32x4 x[PF];
+  __device__ __forceinline__ void fetch(const float *src, int j0, int T, int tid) {
+    const uint32_t voff = tid < V4 ? (uint32_t)tid * 16u : 0x80000000u;
+#pragma unroll
+    for (int e = 0; e < PF; ++e) x[e] = buffer_f32x4(row_rsrc(src, j0 + e * RPP, T, D), voff);
+  }
+  __device__ __forceinline__ void stash(float *dst, int tid) const {
+    if (V4 % NT != 0 && tid >= V4) return;
+#pragma unroll
+    for (int e = 0; e < PF; ++e) {
+      const int idx = tid + NT * e;
+      *reinterpret_cast<f32x4 *>(dst + (idx / (D / 4)) * RS + (idx % (D / 4)) * 4) = x[e];
     }
   }
 };

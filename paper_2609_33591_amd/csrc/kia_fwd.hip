@@ -17,6 +17,8 @@
 //   stored: pass 2 computes the same sub-tiles again. On the bf16 matrix unit
 //   that costs less than writing 4 bytes per pair and reading them back (at
 //   B8 H12 T1024 d64 2 x 208 MB, which alone take 80 us of the former 220).
+//   Only where the scores come from the fp32 MFMA (fp32 at d = 128) are they
+//   kept in U and read back.
 // Pass 2 (Sec. 3 reconstruction and normalization): per key the
 //   interval/level decision, kept in U for the backward (one byte, or the
 //   position u), w^L and w^N from e^{b_{r+1}} (one exp2 per key), the row sums
@@ -32,14 +34,16 @@
 //   the fp32 exponential as the weight function rounds it (kept in U) and the
 //   weight, with no grid.
 
+#include <type_traits>
+
 #include "kia_device.hpp"
 #include "kia_kernels.hpp"
 
 namespace kia {
 
 template <typename TI, int D, int CALIB, int RECON, bool OL, int RG, int KP>
-__global__ __launch_bounds__(64 * RG * KP, (FwdShape<TI, D, RG, KP>::OCC)) void fwd_kernel(FwdArgsT<TI> a) {
-  using Shape = FwdShape<TI, D, RG, KP>;
+__global__ __launch_bounds__(64 * RG * KP, (FwdShape<TI, D, RECON, RG, KP>::OCC)) void fwd_kernel(FwdArgsT<TI> a) {
+  using Shape = FwdShape<TI, D, RECON, RG, KP>;
   constexpr int NP = Pieces<TI>::N, NC = D >= 32 ? D / 32 : 1;
   // MinMax and the resolved grid need the row minimum (resolved: for the
   // rounding margin of its far keys only)
@@ -50,12 +54,17 @@ __global__ __launch_bounds__(64 * RG * KP, (FwdShape<TI, D, RG, KP>::OCC)) void 
   // RG = 1: a wave's tile is read by no other, so it stages it itself (K, then
   // V, in one buffer of its own) and no barrier is needed
   constexpr bool PRIV = RG == 1;
-  using St = Stage<D, PRIV ? 32 : CHK, PRIV ? 64 : NT, TI>;
+  constexpr bool EX = Shape::EX;  // fp32 scores, kept in U between the passes
+  constexpr int SROWS = PRIV ? 32 : CHK, SNT = PRIV ? 64 : NT;
+  using St = Stage<D, SROWS, SNT, TI>;
+  using StK = std::conditional_t<EX, StageF32<D, SROWS, SNT>, St>;
+  using Op = ScoreOp<TI, D>;
   constexpr int RS = St::RS, PS = St::PS;
   // per-lane values a wave of key part > 0 hands to part 0 at the end
   constexpr int NRED = NC * 16 * (OL ? 2 : 1) + 2;
   // K chunks, then V chunks; at the end the key parts' sums (16-bit units)
-  constexpr int STG = PRIV ? KP * St::SIZE : 2 * NBUF * St::SIZE, RED = (KP - 1) * RG * 64 * NRED * 2;
+  static_assert(!EX || StK::SIZE * 2 <= St::SIZE, "K in V's place");
+  constexpr int STG = (PRIV ? KP : (EX ? 1 : 2) * NBUF) * St::SIZE, RED = (KP - 1) * RG * 64 * NRED * 2;
   constexpr int SMEM = STG > RED ? STG : RED;
   __shared__ __attribute__((aligned(16))) uint16_t smem[SMEM];
   __shared__ int Xc[KP > 1 ? RG * KP * 4 * 32 : 1];  // [row group][key part][field][row]
@@ -84,28 +93,42 @@ __global__ __launch_bounds__(64 * RG * KP, (FwdShape<TI, D, RG, KP>::OCC)) void 
   const int kend = a.causal ? min(T, i0 + BM) : T;
   const int nstep = (kend + CHK - 1) / CHK;
   // this wave's tile inside a staged chunk, by rows and by columns
-  const int krow = ((PRIV ? 0 : kh * 32) + l32) * RS + 8 * half;
+  const int krow = ((PRIV ? 0 : kh * 32) + l32) * StK::RS + half * (EX ? D / 2 : 8);
   const int vcol = (PRIV ? 0 : kh * 32) * RS + tr_base<D>(lane);
 
-  bf16x8 qop[NP][D / 16];
-  const float qf = load_query<D>(a.q + slice, row < T ? row : T - 1, T, half, qop);
+  Op qop;
+  const float qf = qop.load_q(a.q + slice, row < T ? row : T - 1, T, half);
   // Chunk steps: n counts the steps of both passes. A chunk is fetched into
   // registers one step ahead and stashed at the start of its own step, behind
   // which one barrier orders the stash before the reads; with two buffers the
   // reads of two steps back are ordered before the stash by the barrier in
   // between, with one by a barrier of its own.
-  St fk, fv;
+  StK fk;
+  St fv;
   auto kbuf = [&](int n) {
     return smem + (PRIV ? kh * St::SIZE : NBUF == 2 ? (n & 1) * St::SIZE : 0);
   };
   auto vbuf = [&](int n) {
-    return PRIV ? kbuf(n) : smem + (NBUF + (NBUF == 2 ? n & 1 : 0)) * St::SIZE;
+    return PRIV || EX ? kbuf(n) : smem + (NBUF + (NBUF == 2 ? n & 1 : 0)) * St::SIZE;
+  };
+  auto stash_k = [&](int n, int t) {
+    if constexpr (EX) fk.stash(reinterpret_cast<float *>(kbuf(n)), t);
+    else fk.stash(kbuf(n), t);
   };
   auto scores = [&](const uint16_t *Kb) {
-    const uint16_t *kr = Kb + krow;
-    return score_tile<D, NP>([&](int p, int s) { return row_op(kr + p * PS + 16 * s); },
-                             [&](int p, int s) { return qop[p][s]; });
+    if constexpr (EX) {
+      Op kop;
+      kop.read(reinterpret_cast<const float *>(Kb) + krow);
+      return Op::tile(kop, qop);
+    } else {
+      const uint16_t *kr = Kb + krow;
+      return score_tile<D, NP>([&](int p, int s) { return row_op(kr + p * PS + 16 * s); },
+                               [&](int p, int s) { return qop.v[p][s]; });
+    }
   };
+  // this wave's tiles in U (the tiles of one query tile are consecutive in
+  // both layouts; a wave past the last row is kept inside the field)
+  float *Ut = a.st.U + ds_tile(bh, min(iw, T - 1) / 32, 0, (T + 31) / 32, a.causal) * 1024;
 
   // ---------------- pass 1: raw extrema --------------------------------
   float Rx = -INFINITY, Rn = INFINITY;
@@ -115,13 +138,19 @@ __global__ __launch_bounds__(64 * RG * KP, (FwdShape<TI, D, RG, KP>::OCC)) void 
     const int js = p * CHK + kh * 32;
     if (PRIV && js > wlim) break;
     if (!PRIV && NBUF == 1 && p > 0) lds_barrier();
-    fk.stash(kbuf(p), stid);
+    stash_k(p, stid);
     // the next chunk; after the last one pass 2's first
     const bool more = PRIV ? js + CHK <= wlim : p + 1 < nstep;
     fk.fetch(ks, (more ? (p + 1) * CHK : 0) + soff, T, stid);
     if (!PRIV) lds_barrier();
     if (js <= wlim) {
       f32x16 acc = scores(kbuf(p));
+      if constexpr (EX) {
+        float sv[16];
+#pragma unroll
+        for (int r = 0; r < 16; ++r) sv[r] = acc[r];
+        tile_store(Ut + (size_t)(js / 32) * 1024, lane, sv);
+      }
       f32x16 lo = acc;
       if (js + 31 > wmin) {
 #pragma unroll
@@ -138,7 +167,7 @@ __global__ __launch_bounds__(64 * RG * KP, (FwdShape<TI, D, RG, KP>::OCC)) void 
       }
     }
   }
-  if (!PRIV) fv.fetch(vs, 0, T, tid);
+  if (!PRIV || EX) fv.fetch(vs, soff, T, stid);
   Rx = fmaxf(Rx, __shfl_xor(Rx, 32));
   if constexpr (TRACKMIN) Rn = fminf(Rn, __shfl_xor(Rn, 32));
   if constexpr (KP > 1) {
@@ -178,9 +207,6 @@ __global__ __launch_bounds__(64 * RG * KP, (FwdShape<TI, D, RG, KP>::OCC)) void 
       if constexpr (OL) olacc[c][e] = 0.f;
     }
   float WN = 0.f, WLs = 0.f;
-  // this wave's decision tiles in U (the tiles of one query tile are
-  // consecutive in both layouts)
-  float *Ut = a.st.U + ds_tile(bh, iw / 32, 0, (T + 31) / 32, a.causal) * 1024;
   auto clamped = [&](float x) {
     if constexpr (CALIB == CAL_MINMAX) return __builtin_amdgcn_fmed3f(x, 0.75f, hic);
     else if constexpr (CALIB == CAL_FWM) return __builtin_amdgcn_fmed3f(x, -0.25f, hic);
@@ -342,7 +368,38 @@ __global__ __launch_bounds__(64 * RG * KP, (FwdShape<TI, D, RG, KP>::OCC)) void 
     WN += tWN;
     WLs += tWL;
   };
-  if constexpr (PRIV) {
+  if constexpr (EX) {
+    // the wave's scores come back from U one tile ahead (each lane reads what
+    // it wrote itself; a tile's decisions replace them after that)
+    auto load_s = [&](int js, f32x16 &S) {
+      float sv[16];
+      tile_load(Ut + (size_t)(min(js, max(wlim, 0)) / 32) * 1024, lane, sv);
+#pragma unroll
+      for (int r = 0; r < 16; ++r) S[r] = sv[r];
+    };
+    __syncthreads();
+    f32x16 S;
+    load_s(kh * 32, S);
+    for (int p = 0; p < nstep; ++p) {
+      const int js = p * CHK + kh * 32;
+      if (PRIV && js > wlim) break;
+      if (!PRIV && NBUF == 1 && p > 0) lds_barrier();
+      fv.stash(vbuf(p), stid);
+      fv.fetch(vs, min(p + 1, nstep - 1) * CHK + soff, T, stid);
+      f32x16 Sn;
+      load_s(js + CHK, Sn);
+      if (!PRIV) lds_barrier();
+      if (js <= wlim) {
+        __builtin_amdgcn_sched_barrier(0);
+        float v[16];
+        decide(js, S, v);
+        __builtin_amdgcn_sched_barrier(0);
+        accumulate(js, v, vbuf(p) + vcol);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      S = Sn;
+    }
+  } else if constexpr (PRIV) {
     for (int p = 0; p < nstep; ++p) {
       const int js = p * CHK + kh * 32;
       if (js > wlim) break;

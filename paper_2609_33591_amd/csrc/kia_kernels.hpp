@@ -23,14 +23,18 @@ template <typename TI> struct FwdArgsT {
 };
 
 // Launch shape of the forward: NBUF staging buffers per tensor, OCC waves per
-// SIMD. At d = 128 the three pieces of Q and two output accumulators take more
-// than half the registers of a SIMD, and large chunks more than half the LDS.
-template <typename TI, int D, int RG, int KP> struct FwdShape {
+// SIMD (one where large chunks take more than half the LDS; fp32 inputs at
+// d = 128 with Nearest: one as well, two spill). Where fp32 scores come from
+// the fp32 MFMA (EX), K is staged as it is in pass 1 and V in pieces in pass 2,
+// in the same place.
+template <typename TI, int D, int RECON, int RG, int KP> struct FwdShape {
+  static constexpr bool EX = fp32_scores<TI, D>();
   static constexpr int CHUNK = Pieces<TI>::N * 32 * KP * (D + 8) * 2;  // bytes of one staged tensor
   static constexpr int WGS = RG * KP == 8 ? 1 : 2;  // workgroups that make two waves per SIMD
-  static constexpr int LDS = RG == 1 ? CHUNK : 2 * CHUNK;  // one buffer for each tensor, or one for both
-  static constexpr int OCC = (sizeof(TI) == 4 && D == 128) || LDS * WGS > 156 * 1024 ? 1 : 2;
-  static constexpr int NBUF = 4 * CHUNK * (OCC == 2 ? WGS : 1) <= 156 * 1024 ? 2 : 1;
+  static constexpr int LDS = RG == 1 || EX ? CHUNK : 2 * CHUNK;  // one buffer for each tensor, or one for both
+  static constexpr int OCC =
+      LDS * WGS > 156 * 1024 || (EX && RECON == REC_NEAREST) ? 1 : 2;
+  static constexpr int NBUF = 2 * (EX ? CHUNK : 2 * CHUNK) * (OCC == 2 ? WGS : 1) <= 156 * 1024 ? 2 : 1;
 };
 
 // Row constants of the forward: as row_const(), with what FWM and the
