@@ -24,7 +24,7 @@
  *     kia_stats_bytes). The softmax scale is fixed to fl32(1/sqrt(d)) and a
  *     score is fl32(fl32(q.k) * scale) (the fp32 scores of App. A).
  *   - Products of fp32 operands are formed from three bf16 pieces each (an
- *     exact sum) with fp32 accumulation; their error is below that of an
+ *     exact sum; the scores at d = 128 as fp32 products) with fp32 accumulation; their error is below that of an
  *     fp32 product. Inputs are finite: an infinite element, or one that
  *     rounds to infinity in bf16 (above about 3.39e38), makes the results it
  *     enters NaN.
@@ -160,7 +160,8 @@ extern "C" {
  *   2*B*H*T^2 bytes causal, 4*B*H*T^2 otherwise); then U, tiles of the same
  *   shape and count: the decided grid position u of every (query, key) pair
  *   (the value the index decisions of the conventions above were taken
- *   from), written by the forward's second pass, so that the backward
+ *   from), written by the forward's second pass (in place of the scores,
+ *   which fp32 inputs at d = 128 keep there between the passes), so that the backward
  *   neither recomputes the scores nor the decisions; under FWM with Nearest, whose
  *   backward needs only the interval, the level bit and the tail, by one
  *   byte per key instead (1 + 2r + [t >= 1/2], 0 for the tail) in the first
