@@ -23,9 +23,11 @@
  *     fields) at most KIA_MAX_STATS_BYTES (else KIA_ERR_SHAPE, also from
  *     kia_stats_bytes). The softmax scale is fixed to fl32(1/sqrt(d)) and a
  *     score is fl32(fl32(q.k) * scale) (the fp32 scores of App. A).
- *   - Products of fp32 operands are formed from three bf16 pieces each (an
- *     exact sum; the scores at d = 128 as fp32 products) with fp32 accumulation; their error is below that of an
- *     fp32 product. Inputs are finite: an infinite element, or one that
+ *     With fp32 inputs q.k is one chain of fused multiply-adds, the terms s
+ *     and d/2 + s for s = 0 .. d/2 - 1.
+ *   - The other products of fp32 operands are formed from three bf16 pieces
+ *     each (an exact sum) with fp32 accumulation; their error is below that
+ *     of an fp32 product. Inputs are finite: an infinite element, or one that
  *     rounds to infinity in bf16 (above about 3.39e38), makes the results it
  *     enters NaN.
  *   - Determinism: the forward is bitwise repeatable. By default the
@@ -161,7 +163,7 @@ extern "C" {
  *   shape and count: the decided grid position u of every (query, key) pair
  *   (the value the index decisions of the conventions above were taken
  *   from), written by the forward's second pass (in place of the scores,
- *   which fp32 inputs at d = 128 keep there between the passes), so that the backward
+ *   which fp32 inputs keep there between the passes), so that the backward
  *   neither recomputes the scores nor the decisions; under FWM with Nearest, whose
  *   backward needs only the interval, the level bit and the tail, by one
  *   byte per key instead (1 + 2r + [t >= 1/2], 0 for the tail) in the first

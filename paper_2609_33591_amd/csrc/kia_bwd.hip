@@ -673,11 +673,11 @@ __device__ __forceinline__ void tie_rows(const BwdArgsT<TI> &a, int bh, int rb, 
   if (!__any(tierow)) return;
   // the row's scores with the canonical sub-tile of the input type
   ScoreOp<TI, D> qop;
-  const float qf = qop.load_q(a.q + slice, i < T ? i : T - 1, T, half);
+  qop.load(a.q + slice, i < T ? i : T - 1, T, half);
   auto tile_scores = [&](int js) -> f32x16 {
     ScoreOp<TI, D> kop;
     kop.load(a.k + slice, js + l32, T, half);
-    return qf * ScoreOp<TI, D>::tile(kop, qop);
+    return ScoreOp<TI, D>::tile(kop, qop);
   };
   const int kend = a.causal ? min(T, rb * 32 + 32) : T;
   for (int js = 0; js < kend; js += 32) {

@@ -25,7 +25,7 @@ __global__ __launch_bounds__(256) void codes_kernel(CodesArgsT<TI> a) {
   const size_t slice = (size_t)bh * T * D;
   const float Kf = (float)a.K;
   ScoreOp<TI, D> qop;
-  const float qf = qop.load_q(a.q + slice, row < T ? row : T - 1, T, half);
+  qop.load(a.q + slice, row < T ? row : T - 1, T, half);
   const size_t ridx = (size_t)bh * T + (row < T ? row : T - 1);
   const float Mx = a.st.M[ridx];
   const float Mn = CALIB != CAL_FWM ? a.st.m[ridx] : Mx;
@@ -46,7 +46,7 @@ __global__ __launch_bounds__(256) void codes_kernel(CodesArgsT<TI> a) {
       } else {
         ScoreOp<TI, D> kop;
         kop.load(a.k + slice, js + l32, T, half);
-        const f32x16 acc = qf * ScoreOp<TI, D>::tile(kop, qop);
+        const f32x16 acc = ScoreOp<TI, D>::tile(kop, qop);
         if constexpr (EXPW) {
           // bit 15 valid; bits 0-14 the bf16 pattern (BF16-exp) or the E4M3
           // byte (FP8-exp) of the weight, 0 for softmax (w <= 1: bit 14 clear)
@@ -187,7 +187,7 @@ __global__ __launch_bounds__(256) void scores_kernel(ScoresArgsT<TI> a) {
   const int i0 = qb * CODES_BM, iw = i0 + wave * 32, row = iw + l32;
   const size_t slice = (size_t)bh * T * D;
   ScoreOp<TI, D> qop;
-  const float qf = qop.load_q(a.q + slice, row < T ? row : T - 1, T, half);
+  qop.load(a.q + slice, row < T ? row : T - 1, T, half);
   const int ntiles = (T + CODES_BN - 1) / CODES_BN;
   for (int t = 0; t < ntiles; ++t) {
     const int j0 = t * CODES_BN;
@@ -197,7 +197,7 @@ __global__ __launch_bounds__(256) void scores_kernel(ScoresArgsT<TI> a) {
       if (js >= T) continue;
       ScoreOp<TI, D> kop;
         kop.load(a.k + slice, js + l32, T, half);
-        const f32x16 acc = qf * ScoreOp<TI, D>::tile(kop, qop);
+        const f32x16 acc = ScoreOp<TI, D>::tile(kop, qop);
       if (row < T) {
         float *dst = a.scores + ((size_t)bh * T + row) * T;
 #pragma unroll
@@ -238,7 +238,7 @@ __global__ __launch_bounds__(256) void geometry_kernel(GeoArgs a) {
   for (int e = tid; e < CODES_BM * NB; e += 256) bucket[e] = 0.f;
   __syncthreads();
   ScoreOp<float, D> qop;
-  const float qf = qop.load_q(a.q + slice, row < T ? row : T - 1, T, half);
+  qop.load(a.q + slice, row < T ? row : T - 1, T, half);
   float qss = 0.f, kss = 0.f;
   {
     const int rr = row < T ? row : T - 1;
@@ -290,7 +290,7 @@ __global__ __launch_bounds__(256) void geometry_kernel(GeoArgs a) {
         if (js >= T || (a.causal && js > iw + 31)) continue;  // wave-uniform
         ScoreOp<float, D> kop;
         kop.load(a.k + slice, js + l32, T, half);
-        const f32x16 acc = qf * ScoreOp<float, D>::tile(kop, qop);
+        const f32x16 acc = ScoreOp<float, D>::tile(kop, qop);
         float u[16];
         decide_u<CALIB>(acc, rc, M, Mn, K, a.tau, a.scale, u);
 #pragma unroll

@@ -1,6 +1,6 @@
 // kia_device.hpp -- device building blocks shared by every K-interval
 // attention kernel for gfx950 (CDNA4, wave64, bf16 MFMA 32x32x16 with fp32
-// accumulation).
+// accumulation; fp32 scores on the fp32 MFMA 32x32x2).
 //
 // fp32 operands on the bf16 matrix unit. An fp32 value is the exact sum of
 // three bf16 pieces x = x0 + x1 + x2, each the nearest bf16 of what is left
@@ -16,13 +16,13 @@
 // 4.1e-7 and 3.4e-7. bf16 inputs are one piece and one product.
 //
 // Canonical score sub-tile. Every kernel that needs a score s_ij computes it
-// with ScoreOp::tile(): a 32-key x 32-query block of S^T accumulated by
-// v_mfma_f32_32x32x16_bf16 (fp32 inputs at d = 128: by the fp32 MFMA, see
-// ScoreOp) over d in one fixed order, with the key block and
-// the query block aligned to multiples of 32. The A operand is K (rows =
-// keys), the B operand Q (columns = queries). Lane l (half h = l/32) feeds,
-// at k-step s, K[key0 + l%32][16 s + 8 h + e] and Q[query0 + l%32][16 s + 8 h
-// + e], e = 0..7. Output register r of lane l holds S^T[key0 + krel(r, h)]
+// with ScoreOp::tile(): a 32-key x 32-query block of S^T accumulated over d in
+// one fixed order, by v_mfma_f32_32x32x2_f32 for fp32 inputs (d/2 steps of the
+// terms s and d/2 + s, each a fused multiply-add) and v_mfma_f32_32x32x16_bf16
+// for bf16 inputs, with the key block and the query block aligned to multiples
+// of 32. The A operand is K (rows = keys), the B operand Q (columns = queries).
+// Lane l (half h = l/32) feeds, at k-step s, K[key0 + l%32][h d/2 + s] and the
+// same of Q (bf16: [16 s + 8 h + e], e = 0..7). Output register r of lane l holds S^T[key0 + krel(r, h)]
 // [query0 + l%32] with krel(r, h) = 8*(r/4) + 4*h + r%4. Same operands, same
 // instruction sequence, same lane/register position: the fp32 score of a pair
 // is bit-identical wherever it is computed (both passes of the forward, the
@@ -690,81 +690,24 @@ __device__ __forceinline__ void load_rows(const TI *slice, int row, int T, int h
   }
 }
 
-// The lane's operand of 32 query rows, and the factor that takes a product
-// with them back to q.k (1 for bf16 inputs). The pieces of a value below
-// 2^-109 would lose bits under bf16's smallest 2^-133, so a row that holds one
-// is scaled up by a power of two first, which is exact: 2^24 takes fp32's last
-// bit, 2^-149, to a normal bf16, and is no larger because q.k has to stay
-// finite (and less where the row's maximum would pass 2^60); every other row
-// has the factor 1.
-template <int D, typename TI>
-__device__ __forceinline__ float load_query(const TI *slice, int row, int T, int half,
-                                            bf16x8 (&op)[Pieces<TI>::N][D / 16]) {
-  if constexpr (sizeof(TI) == 2) {
-    load_rows<D>(slice, row, T, half, op);
-    return 1.f;
-  } else {
-    float x[D / 16][8], big = 0.f;
-    bool tiny = false;
-#pragma unroll
-    for (int s = 0; s < D / 16; ++s)
-#pragma unroll
-      for (int g = 0; g < 2; ++g) {
-        const f32x4 v =
-            *reinterpret_cast<const f32x4 *>(slice + (size_t)row * D + 16 * s + 8 * half + 4 * g);
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          x[s][4 * g + e] = v[e];
-          big = fmaxf(big, fabsf(v[e]));
-          tiny |= (fabsf(v[e]) < 0x1p-109f) & (v[e] != 0.f);
-        }
-      }
-    big = fmaxf(big, __shfl_xor(big, 32));
-    tiny = tiny | (__shfl_xor(tiny ? 1 : 0, 32) != 0);
-    // exponent of the row's largest element (denormals: -127)
-    const int up = tiny ? min(max(60 - ((int)(__float_as_uint(big) >> 23) - 127), 0), 24) : 0;
-    const float f = ldexpf(1.f, up);
-#pragma unroll
-    for (int s = 0; s < D / 16; ++s) {
-#pragma unroll
-      for (int e = 0; e < 8; ++e) x[s][e] *= f;
-      bf16x8 p[3];
-      to_pieces<3>(x[s], p);
-#pragma unroll
-      for (int i = 0; i < 3; ++i) op[i][s] = p[i];
-    }
-    return ldexpf(1.f, -up);
-  }
-}
-
 // ---- score operands ----------------------------------------------------------
-// fp32 scores at d = 128 stay on v_mfma_f32_32x32x2_f32, in one summation order:
-// lane l feeds, at k-step s, K[key0 + l%32][64 (l/32) + s] and the same of Q. An
-// index decision jumps where a score's rounding does, so this also leaves the
-// decisions at d = 128 where they were. Six piece products would take the
-// registers of a second wave per SIMD (Q and K in three pieces each); the fp32
-// operand takes half of that. Forward (us, piece products / this): B4 H16 T2048
-// MinMax LERP 803 / 690, FWM Nearest Prob-STE 928 / 909; B1 H40 T1024 196 / 148
-// and 231 / 202; B1 H12 T1024 77 / 68 and 90 / 79; B1 H16 T8192 MinMax LERP
-// 2747 / 2602.
-template <typename TI, int D> __host__ __device__ constexpr bool fp32_scores() {
-  return sizeof(TI) == 4 && D == 128;
-}
-template <typename TI, int D, bool EX = fp32_scores<TI, D>()> struct ScoreOp {
-  bf16x8 v[Pieces<TI>::N][D / 16];
+// fp32 scores stay on v_mfma_f32_32x32x2_f32, in one summation order: lane l
+// feeds, at k-step s, K[key0 + l%32][(d/2) (l/32) + s] and the same of Q. An
+// index decision jumps where a score's rounding does, so the order of a score's
+// sum is part of the operator's result; and every fp32 value keeps all its bits
+// here, whatever its size.
+template <typename TI> __host__ __device__ constexpr bool fp32_scores() { return sizeof(TI) == 4; }
+template <typename TI, int D> struct ScoreOp {
+  bf16x8 v[1][D / 16];
   // a row of a [T, D] slice (rows at or beyond T read as zero)
   __device__ __forceinline__ void load(const TI *slice, int row, int T, int half) {
     load_rows<D>(slice, row, T, half, v);
   }
-  // the same of q, and the factor that takes a product with it back to q.k
-  __device__ __forceinline__ float load_q(const TI *slice, int row, int T, int half) {
-    return load_query<D>(slice, row, T, half, v);
-  }
   static __device__ __forceinline__ f32x16 tile(const ScoreOp &k, const ScoreOp &q) {
-    return score_tile<D, Pieces<TI>::N>(k.v, q.v);
+    return score_tile<D, 1>(k.v, q.v);
   }
 };
-template <typename TI, int D> struct ScoreOp<TI, D, true> {
+template <int D> struct ScoreOp<float, D> {
   float v[D / 2];
   __device__ __forceinline__ void read(const float *p) {
 #pragma unroll
@@ -779,10 +722,6 @@ template <typename TI, int D> struct ScoreOp<TI, D, true> {
     read(slice + (size_t)(ok ? row : 0) * D + half * (D / 2));
 #pragma unroll
     for (int s = 0; s < D / 2; ++s) v[s] = ok ? v[s] : 0.f;
-  }
-  __device__ __forceinline__ float load_q(const float *slice, int row, int T, int half) {
-    load(slice, row, T, half);
-    return 1.f;
   }
   static __device__ __forceinline__ f32x16 tile(const ScoreOp &k, const ScoreOp &q) {
     f32x16 acc;

@@ -1,24 +1,24 @@
 // kia_fwd.hip -- forward of causal K-interval attention on gfx950, for fp32
-// inputs (three bf16 pieces per operand) and bf16 inputs (one piece).
+// inputs (fp32 scores; three bf16 pieces per operand of P V) and bf16 inputs
+// (one piece).
 //
 // One workgroup = RG row groups of 32 query rows of one (b, h) times KP key
 // parts, one wave each. Each wave keeps its 32 Q rows in registers as the B
 // operand of the canonical score sub-tile. Keys stream through LDS in chunks
-// of KP 32-key tiles, one per key part, staged row-major in bf16 pieces: K is
-// read by rows (the score sub-tile's A operand) and V through transposing
-// reads (the P V A operand). Large grids take RG = 4, KP = 1: 128 rows share
-// each staged tile, so splitting K and V into pieces costs 88 VALU operations
-// per thread and 32-key step against about 580 of a tile's weights. Grids too
+// of KP 32-key tiles, one per key part, staged row-major (V in bf16 pieces, K of
+// fp32 inputs as it is): K is read by rows (the score sub-tile's A operand) and
+// V through transposing reads (the P V A operand). Large grids take RG = 4, KP =
+// 1: 128 rows share each staged tile, so splitting V into pieces costs 44 VALU
+// operations per thread and 32-key step against about 580 of a tile's weights.
+// Grids too
 // small to fill the chip give up row groups for key parts.
 //
 // Pass 1 (row extrema, App. A: amax/amin over the valid keys): score
 //   sub-tiles and the raw row maximum (and minimum), merged across the two
-//   lanes that share a row and, through LDS, across the key parts. Nothing is
-//   stored: pass 2 computes the same sub-tiles again. On the bf16 matrix unit
-//   that costs less than writing 4 bytes per pair and reading them back (at
-//   B8 H12 T1024 d64 2 x 208 MB, which alone take 80 us of the former 220).
-//   Only where the scores come from the fp32 MFMA (fp32 at d = 128) are they
-//   kept in U and read back.
+//   lanes that share a row and, through LDS, across the key parts. bf16 scores
+//   are not stored: pass 2 computes the same sub-tiles again, which costs less
+//   than writing 4 bytes per pair and reading them back. fp32 scores take eight
+//   times the matrix work, and most shapes keep them in U (FwdShape::KEEP).
 // Pass 2 (Sec. 3 reconstruction and normalization): per key the
 //   interval/level decision, kept in U for the backward (one byte, or the
 //   position u), w^L and w^N from e^{b_{r+1}} (one exp2 per key), the row sums
@@ -54,7 +54,8 @@ __global__ __launch_bounds__(64 * RG * KP, (FwdShape<TI, D, RECON, RG, KP>::OCC)
   // RG = 1: a wave's tile is read by no other, so it stages it itself (K, then
   // V, in one buffer of its own) and no barrier is needed
   constexpr bool PRIV = RG == 1;
-  constexpr bool EX = Shape::EX;  // fp32 scores, kept in U between the passes
+  constexpr bool EX = Shape::EX;      // fp32 scores (K staged as it is)
+  constexpr bool KEEP = Shape::KEEP;  // kept in U between the passes
   constexpr int SROWS = PRIV ? 32 : CHK, SNT = PRIV ? 64 : NT;
   using St = Stage<D, SROWS, SNT, TI>;
   using StK = std::conditional_t<EX, StageF32<D, SROWS, SNT>, St>;
@@ -62,9 +63,12 @@ __global__ __launch_bounds__(64 * RG * KP, (FwdShape<TI, D, RECON, RG, KP>::OCC)
   constexpr int RS = St::RS, PS = St::PS;
   // per-lane values a wave of key part > 0 hands to part 0 at the end
   constexpr int NRED = NC * 16 * (OL ? 2 : 1) + 2;
-  // K chunks, then V chunks; at the end the key parts' sums (16-bit units)
-  static_assert(!EX || StK::SIZE * 2 <= St::SIZE, "K in V's place");
-  constexpr int STG = (PRIV ? KP : (EX ? 1 : 2) * NBUF) * St::SIZE, RED = (KP - 1) * RG * 64 * NRED * 2;
+  // K chunks, then V chunks; at the end the key parts' sums (16-bit units; a K
+  // block fits in a V block's place)
+  constexpr int KSIZE = EX ? 2 * StK::SIZE : St::SIZE;
+  static_assert(KSIZE <= St::SIZE, "K in V's place");
+  constexpr int STG = PRIV ? KP * St::SIZE : NBUF * (KEEP ? St::SIZE : KSIZE + St::SIZE);
+  constexpr int RED = (KP - 1) * RG * 64 * NRED * 2;
   constexpr int SMEM = STG > RED ? STG : RED;
   __shared__ __attribute__((aligned(16))) uint16_t smem[SMEM];
   __shared__ int Xc[KP > 1 ? RG * KP * 4 * 32 : 1];  // [row group][key part][field][row]
@@ -97,7 +101,7 @@ __global__ __launch_bounds__(64 * RG * KP, (FwdShape<TI, D, RECON, RG, KP>::OCC)
   const int vcol = (PRIV ? 0 : kh * 32) * RS + tr_base<D>(lane);
 
   Op qop;
-  const float qf = qop.load_q(a.q + slice, row < T ? row : T - 1, T, half);
+  qop.load(a.q + slice, row < T ? row : T - 1, T, half);
   // Chunk steps: n counts the steps of both passes. A chunk is fetched into
   // registers one step ahead and stashed at the start of its own step, behind
   // which one barrier orders the stash before the reads; with two buffers the
@@ -106,10 +110,10 @@ __global__ __launch_bounds__(64 * RG * KP, (FwdShape<TI, D, RECON, RG, KP>::OCC)
   StK fk;
   St fv;
   auto kbuf = [&](int n) {
-    return smem + (PRIV ? kh * St::SIZE : NBUF == 2 ? (n & 1) * St::SIZE : 0);
+    return smem + (PRIV ? kh * St::SIZE : NBUF == 2 ? (n & 1) * (KEEP ? St::SIZE : KSIZE) : 0);
   };
   auto vbuf = [&](int n) {
-    return PRIV || EX ? kbuf(n) : smem + (NBUF + (NBUF == 2 ? n & 1 : 0)) * St::SIZE;
+    return PRIV || KEEP ? kbuf(n) : smem + NBUF * KSIZE + (NBUF == 2 ? n & 1 : 0) * St::SIZE;
   };
   auto stash_k = [&](int n, int t) {
     if constexpr (EX) fk.stash(reinterpret_cast<float *>(kbuf(n)), t);
@@ -145,7 +149,7 @@ __global__ __launch_bounds__(64 * RG * KP, (FwdShape<TI, D, RECON, RG, KP>::OCC)
     if (!PRIV) lds_barrier();
     if (js <= wlim) {
       f32x16 acc = scores(kbuf(p));
-      if constexpr (EX) {
+      if constexpr (KEEP) {
         float sv[16];
 #pragma unroll
         for (int r = 0; r < 16; ++r) sv[r] = acc[r];
@@ -167,7 +171,7 @@ __global__ __launch_bounds__(64 * RG * KP, (FwdShape<TI, D, RECON, RG, KP>::OCC)
       }
     }
   }
-  if (!PRIV || EX) fv.fetch(vs, soff, T, stid);
+  if (!PRIV || KEEP) fv.fetch(vs, soff, T, stid);
   Rx = fmaxf(Rx, __shfl_xor(Rx, 32));
   if constexpr (TRACKMIN) Rn = fminf(Rn, __shfl_xor(Rn, 32));
   if constexpr (KP > 1) {
@@ -183,18 +187,17 @@ __global__ __launch_bounds__(64 * RG * KP, (FwdShape<TI, D, RECON, RG, KP>::OCC)
       if constexpr (TRACKMIN) Rn = fminf(Rn, __int_as_float(x[q * 128 + 32]));
     }
   }
-  // the extrema of the scores fl32(raw * scale), raw = fl32(acc * qf) (each
-  // rounding is monotone); a sum within its slack of the extreme one may round
-  // to the extremum
-  const float Mx = (Rx * qf) * a.scale;
-  const float Mn = TRACKMIN ? (Rn * qf) * a.scale : Mx;
-  auto slack = [&](float x) { return fmaxf(fabsf(x) * 0x1p-22f, 0x1p-140f / qf); };
+  // the extrema of the scores fl32(raw * scale) (the rounding is monotone); a
+  // sum within its slack of the extreme one may round to the extremum
+  const float Mx = Rx * a.scale;
+  const float Mn = TRACKMIN ? Rn * a.scale : Mx;
+  auto slack = [&](float x) { return fmaxf(fabsf(x) * 0x1p-22f, 0x1p-140f); };
   const float bx = fabsf(Rx) < INFINITY ? Rx - slack(Rx) : Rx;
   const float bn = fabsf(Rn) < INFINITY ? Rn + slack(Rn) : Rn;
   int ax = 0x7fffffff, an = 0x7fffffff, cx = 0, cn = 0;
   RowConst rc{};
   if constexpr (!EXPW) rc = fwd_row_const<CALIB>(Mx, Mn, a);
-  const float a2 = 2.f * rc.alpha * qf, b2 = 2.f * rc.beta, mg = rc.margin2;
+  const float a2 = 2.f * rc.alpha, b2 = 2.f * rc.beta, mg = rc.margin2;
   const float hic = 2.f * Kf - 0.75f;
 
   // ---------------- pass 2: reconstruct, normalize, O = P V ---------------
@@ -232,7 +235,7 @@ __global__ __launch_bounds__(64 * RG * KP, (FwdShape<TI, D, RECON, RG, KP>::OCC)
         for (int r = 0; r < 16; ++r) {
           if (!hit[r]) continue;  // wave-uniform
           const int j = js + krel(r, half);
-          const float s = (S[r] * qf) * a.scale;
+          const float s = S[r] * a.scale;
           const bool ok = j <= jlim;
           const bool ex = ok & (s == Mx);
           ax = ex ? min(ax, j) : ax;
@@ -254,7 +257,7 @@ __global__ __launch_bounds__(64 * RG * KP, (FwdShape<TI, D, RECON, RG, KP>::OCC)
     if constexpr (EXPW) {
       float z[16];
 #pragma unroll
-      for (int r = 0; r < 16; ++r) z[r] = score_shift(S[r] * qf, a.scale, Mx);
+      for (int r = 0; r < 16; ++r) z[r] = score_shift(S[r], a.scale, Mx);
       exp_tile<RECON>(z, v);
       if constexpr (RECON == REC_BF16EXP) {
 #pragma unroll
@@ -283,7 +286,7 @@ __global__ __launch_bounds__(64 * RG * KP, (FwdShape<TI, D, RECON, RG, KP>::OCC)
           const float f = __builtin_amdgcn_fractf(clamped(v[r]));
           const bool amb = (f <= mg) | (1.f - f <= mg);
           if (!__any(amb)) continue;  // wave-uniform
-          const float x = exact_v2<CALIB>((S[r] * qf) * a.scale, v[r], Mx, Mn, a.K, a.tau);
+          const float x = exact_v2<CALIB>(S[r] * a.scale, v[r], Mx, Mn, a.K, a.tau);
           v[r] = amb ? x : v[r];
         }
       }
@@ -368,7 +371,7 @@ __global__ __launch_bounds__(64 * RG * KP, (FwdShape<TI, D, RECON, RG, KP>::OCC)
     WN += tWN;
     WLs += tWL;
   };
-  if constexpr (EX) {
+  if constexpr (KEEP) {
     // the wave's scores come back from U one tile ahead (each lane reads what
     // it wrote itself; a tile's decisions replace them after that)
     auto load_s = [&](int js, f32x16 &S) {
@@ -403,13 +406,13 @@ __global__ __launch_bounds__(64 * RG * KP, (FwdShape<TI, D, RECON, RG, KP>::OCC)
     for (int p = 0; p < nstep; ++p) {
       const int js = p * CHK + kh * 32;
       if (js > wlim) break;
-      fk.stash(kbuf(0), lane);
-      fk.fetch(vs, js, T, lane);
+      stash_k(0, lane);
+      fv.fetch(vs, js, T, lane);
       __builtin_amdgcn_sched_barrier(0);
       const f32x16 S = scores(kbuf(0));
       __builtin_amdgcn_sched_barrier(0);
       // V takes K's place, the next K is fetched
-      fk.stash(vbuf(0), lane);
+      fv.stash(vbuf(0), lane);
       fk.fetch(ks, min(p + 1, nstep - 1) * CHK + soff, T, lane);
       __builtin_amdgcn_sched_barrier(0);
       float v[16];
@@ -422,7 +425,7 @@ __global__ __launch_bounds__(64 * RG * KP, (FwdShape<TI, D, RECON, RG, KP>::OCC)
     for (int p = 0; p < nstep; ++p) {
       const int js = p * CHK + kh * 32;
       if (NBUF == 1) lds_barrier();
-      fk.stash(kbuf(nstep + p), tid);
+      stash_k(nstep + p, tid);
       fv.stash(vbuf(nstep + p), tid);
       const int nx = min(p + 1, nstep - 1) * CHK;
       fk.fetch(ks, nx, T, tid);

@@ -24,17 +24,25 @@ template <typename TI> struct FwdArgsT {
 
 // Launch shape of the forward: NBUF staging buffers per tensor, OCC waves per
 // SIMD (one where large chunks take more than half the LDS; fp32 inputs at
-// d = 128 with Nearest: one as well, two spill). Where fp32 scores come from
-// the fp32 MFMA (EX), K is staged as it is in pass 1 and V in pieces in pass 2,
-// in the same place.
+// d = 128 with Nearest: one as well, two spill). fp32 scores come from the fp32
+// MFMA (EX) and K is staged as it is. KEEP: the scores are kept in U between the
+// passes, and V takes K's place in LDS in the second. Computing them again
+// instead grows with d, the trip through U does not, and small grids have the
+// bandwidth to spare. Measured (us, kept / again), B8 H12 T1024 (4 x 1), MinMax
+// LERP: d = 16 117 / 99, d = 32 145 / 130, d = 64 175 / 213; B1 H12 T1024 (1 x 4),
+// FWM Nearest Prob-STE: d = 16 27.3 / 28.3, d = 32 31.8 / 34.7.
 template <typename TI, int D, int RECON, int RG, int KP> struct FwdShape {
-  static constexpr bool EX = fp32_scores<TI, D>();
-  static constexpr int CHUNK = Pieces<TI>::N * 32 * KP * (D + 8) * 2;  // bytes of one staged tensor
+  static constexpr bool EX = fp32_scores<TI>();
+  static constexpr bool KEEP = EX && (D >= 64 || RG < 4);
+  // bytes of one staged block of V and of K
+  static constexpr int VB = Pieces<TI>::N * 32 * KP * (D + 8) * 2;
+  static constexpr int KB = EX ? 32 * KP * (D + 4) * 4 : VB;
   static constexpr int WGS = RG * KP == 8 ? 1 : 2;  // workgroups that make two waves per SIMD
-  static constexpr int LDS = RG == 1 || EX ? CHUNK : 2 * CHUNK;  // one buffer for each tensor, or one for both
+  static constexpr int LDS = RG == 1 || KEEP ? VB : VB + KB;  // a buffer for each tensor, or one for both
   static constexpr int OCC =
-      LDS * WGS > 156 * 1024 || (EX && RECON == REC_NEAREST) ? 1 : 2;
-  static constexpr int NBUF = 2 * (EX ? CHUNK : 2 * CHUNK) * (OCC == 2 ? WGS : 1) <= 156 * 1024 ? 2 : 1;
+      LDS * WGS > 156 * 1024 || (EX && D == 128 && RECON == REC_NEAREST) ? 1 : 2;
+  static constexpr int NBUF =
+      2 * (KEEP ? VB : VB + KB) * (OCC == 2 ? WGS : 1) <= 156 * 1024 ? 2 : 1;
 };
 
 // Row constants of the forward: as row_const(), with what FWM and the
