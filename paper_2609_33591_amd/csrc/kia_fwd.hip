@@ -348,6 +348,9 @@ __global__ __launch_bounds__(64 * RG * KP, (FwdShape<TI, D, RECON, RG, KP>::OCC)
           }
         }
       }
+      // (the bytes are made here: only the store below needs them, and left to
+      // it they would keep the 16 positions live through the products)
+      if constexpr (COMPACT) asm volatile("" : "+v"(cw[2 * t]), "+v"(cw[2 * t + 1]));
       bf16x8 wo[NP], wlo[OL ? NP : 1];
       to_pieces<NP>(w, wo);
       if constexpr (OL) to_pieces<NP>(wl, wlo);
