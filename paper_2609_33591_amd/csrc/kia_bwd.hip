@@ -3,7 +3,8 @@
 // Four launches on the caller's stream (App. B):
 //  1. bwd_pre   per row: D^X = dO . O^X (O^X = O, or O^L for Prob-STE with
 //               Nearest) and the row record (grid constants, 1/W, 1/W^X,
-//               -D^X/W^X); zeroes the two row sums.
+//               -D^X/W^X; with fp32 inputs whether dO or q leave the range of
+//               the pieces, see PieceCheck); zeroes the two row sums.
 //  2. bwd_main  KV-major: one workgroup per 128 keys, waves of 32 keys
 //               stream 32-query tiles (staged in LDS, prefetched into
 //               registers one tile ahead). The scores are not recomputed:
@@ -29,6 +30,8 @@
 // fp32 exponential, dS = dz of the weight function, and the maximum's
 // channel cM = -S_self lands on the argmax keys (z = s - M keeps M on the
 // gradient path).
+#include <type_traits>
+
 #include "kia_device.hpp"
 #include "kia_kernels.hpp"
 
@@ -66,13 +69,24 @@ __global__ __launch_bounds__(256) void bwd_pre_kernel(BwdArgsT<TI> a) {
   const f32x4 x = (a.o16 && !probN) ? load4(a.o16 + rr * D + sub * 4)
                                     : *reinterpret_cast<const f32x4 *>(ox + sub * 4);
   const f32x4 y = load4(a.dO + rr * D + sub * 4);
+  // (fp32: rows of dO or q that hold a value out of range of the pieces take the
+  // main kernel's products on the fp32 MFMA)
+  bool out = false;
+  if constexpr (sizeof(TI) == 4) {
+    const f32x4 z = load4(a.q + rr * D + sub * 4);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) out |= out_of_pieces(y[e]) | out_of_pieces(z[e]);
+  }
   const float M = a.st.M[rr];
   const float m = a.calib != CAL_FWM && a.recon < REC_SOFTMAX ? a.st.m[rr] : M;
   const float W = a.st.W[rr];
   const float WX = probN ? a.st.WL[rr] : W;
   if (live) dot = x[0] * y[0] + x[1] * y[1] + x[2] * y[2] + x[3] * y[3];
 #pragma unroll
-  for (int off = L / 2; off > 0; off >>= 1) dot += __shfl_xor(dot, off);
+  for (int off = L / 2; off > 0; off >>= 1) {
+    dot += __shfl_xor(dot, off);
+    if constexpr (sizeof(TI) == 4) out = out | (__shfl_xor(out ? 1 : 0, off) != 0);
+  }
   if (live && sub == 0) {
     // the grid constants (the decision constants alpha, beta, margin are not
     // needed: the backward reads the forward's decided positions)
@@ -85,7 +99,8 @@ __global__ __launch_bounds__(256) void bwd_pre_kernel(BwdArgsT<TI> a) {
     const f32x4 r0 = {rc.alpha, rc.beta, rc.margin2, rc.hl};
     const f32x4 r1 = {rc.b1l, rc.emh, rc.dcoef, 1.f / W};
     const f32x4 r2 = {invWX, -dot * invWX, M, m};
-    f32x4 r3 = {rc.degen ? 1.f : 0.f, 0.f, 0.f, 0.f};
+    // (the sign of the flag marks a row out of range of the pieces)
+    f32x4 r3 = {copysignf(rc.degen ? 1.f : 0.f, out ? -1.f : 1.f), 0.f, 0.f, 0.f};
     if (a.recon < REC_SOFTMAX) {
       const float dW = rc.dcoef * W;
       r3[1] = rc.b1l - __log2f(W);
@@ -146,7 +161,7 @@ __global__ __launch_bounds__(256, (MainShape<TI, D>::OCC)) void bwd_main_kernel(
 
   // this wave's 32 keys of V as A operands
   bf16x8 vop[NP][D / 16];
-  load_rows<D>(a.v + slice, jw + l32, T, half, vop);
+  const bool vout = __any(load_rows<D>(a.v + slice, jw + l32, T, half, vop));
 
   f32x16 dva[NC], dka[NC];
 #pragma unroll
@@ -171,7 +186,7 @@ __global__ __launch_bounds__(256, (MainShape<TI, D>::OCC)) void bwd_main_kernel(
     if constexpr (R012) r0 = *reinterpret_cast<const f32x4 *>(rr);
     if constexpr (R12) r1 = *reinterpret_cast<const f32x4 *>(rr + 4);
     if constexpr (R12) r2 = *reinterpret_cast<const f32x4 *>(rr + 8);
-    if constexpr (!EXPW) r3 = *reinterpret_cast<const f32x4 *>(rr + 12);
+    if constexpr (!EXPW || NP == 3) r3 = *reinterpret_cast<const f32x4 *>(rr + 12);
   };
   // row sums of tile tp: the four waves' partials, then one atomic per row
   auto flush = [&](int tp) {
@@ -238,6 +253,175 @@ __global__ __launch_bounds__(256, (MainShape<TI, D>::OCC)) void bwd_main_kernel(
     }
   };
 
+  // the same on the fp32 MFMA, for operands out of range of the pieces: X (lane =
+  // query, register = key) through LDS as it is, B's rows from memory
+  auto product32 = [&](const float (&X)[16], const TI *B, int i0, f32x16 (&acc)[NC]) {
+    typedef float f32a __attribute__((may_alias));
+    f32a *x = reinterpret_cast<f32a *>(Xw);
+#pragma unroll
+    for (int r = 0; r < 16; ++r) x[l32 * 32 + krel(r, half)] = X[r];
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    const RowRead<D> rb(B, i0, T, half, l32);
+#pragma unroll 1
+    for (int e = 0; e < 16; ++e) {
+      const float xv = x[(2 * e + half) * 32 + l32];
+#pragma unroll
+      for (int c = 0; c < NC; ++c) acc[c] = mfma32(xv, rb.at(2 * e, 32 * c), acc[c]);
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+  };
+
+  bool dsout = false;  // some dS of this lane is out of range of the pieces
+  // one 32-query tile (EXACT: its products on the fp32 MFMA)
+  auto tile_as = [&](int i0, const uint16_t *Qb, const uint16_t *dOb, float &ps, float &pm,
+                     auto tag) {
+    constexpr bool EXACT = decltype(tag)::value;
+    // the forward's decided positions of this (query, key) tile (one byte
+    // per key under FWM with Nearest)
+    const size_t tile = ds_tile(bh, i0 / 32, jw / 32, nq, a.causal) * 1024;
+    float u[16];
+    uint4 cw;
+    if constexpr (COMPACT) cw = codes_load(a.st.U + tile, lane);
+    else tile_load(a.st.U + tile, lane, u);
+    // (nothing of the two forms is shared: it would stay live across both)
+    if constexpr (EXACT && !COMPACT) {
+#pragma unroll
+      for (int r = 0; r < 16; ++r) asm volatile("" : "+v"(u[r]));
+    }
+    if constexpr (EXACT && COMPACT)
+      asm volatile("" : "+v"(cw.x), "+v"(cw.y), "+v"(cw.z), "+v"(cw.w));
+    const uint16_t *dr = dOb + l32 * RS + 8 * half;
+    f32x16 G;
+    if constexpr (!EXACT) {
+      G = score_tile<D, NP>([&](int p, int s) { return row_op(dr + p * PS + 16 * s); },
+                            [&](int p, int s) { return vop[p][s]; },
+                            [](bf16x8 x, bf16x8 y, f32x16 c) { return mfma16(y, x, c); });
+    } else {
+#pragma unroll
+      for (int e = 0; e < 16; ++e) G[e] = 0.f;
+      const RowRead<D> rv(a.v + slice, jw, T, l32, half * (D / 2));
+      const RowRead<D> rd(dos, i0, T, l32, half * (D / 2));
+#pragma unroll 4
+      for (int s = 0; s < D / 2; ++s) G = mfma32(rv.at(0, s), rd.at(0, s), G);
+    }
+    // some pair of the tile is not valid: key j is valid for this lane's
+    // query i iff j <= jlim
+    const bool edge = (a.causal & (jw + 31 > i0)) | (i0 + 32 > T) | (jw + 32 > T);
+    const int i = i0 + l32;
+    const int jlim = i < T ? (a.causal ? i : T - 1) : -1;
+    float P[16], dS[16];
+    if constexpr (EXPW) {
+      // u holds the forward's fp32 exponential e (bf16-rounded for
+      // BF16-exp); dz = gamma e (softmax; FP8-exp: the fp32
+      // exponential's derivative through an identity rounding), BF16-exp
+      // the backward of its casts, bf16(bf16(gamma) w)
+      if (edge) {
+#pragma unroll
+        for (int r = 0; r < 16; ++r) u[r] = jw + krel(r, half) <= jlim ? u[r] : 0.f;
+      }
+      const float invWf = r1[3], invWX = r2[0], negDXW = r2[1];
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        const float e = u[r];
+        const float wf = RECON == REC_FP8EXP ? exp_weight_of<RECON>(e) : e;
+        const float gamma = fmaf(G[r], invWX, negDXW);
+        dS[r] = RECON == REC_BF16EXP ? bf16_rne(bf16_rne(gamma) * e) : gamma * e;
+        P[r] = wf * invWf;
+        ps += dS[r];
+      }
+    } else {
+      // a position whose weight is 0 (the FWM tail; below the argmin; minus
+      // infinity) where the key is not valid
+      constexpr float none = CALIB == CAL_FWM ? -1.f : CALIB == CAL_MINMAX ? -2.f : -INFINITY;
+      if constexpr (COMPACT) {
+        const uint32_t word[4] = {cw.x, cw.y, cw.z, cw.w};
+#pragma unroll
+        for (int r = 0; r < 16; ++r)  // r + up / 2, the tail -1/2
+          u[r] = fmaf((float)((word[r >> 2] >> (8 * (r & 3))) & 0xFFu), 0.5f, -0.5f);
+      }
+      if (edge) {
+#pragma unroll
+        for (int r = 0; r < 16; ++r) u[r] = jw + krel(r, half) <= jlim ? u[r] : none;
+      }
+      // e' = e^{b_{r+1}} / W from one exponential (RR_B1LW): P is e' or
+      // e' e^{-h} (LERP: the chord between them), dS = (g c1 + c0) e'
+      const float b1lw = r3[1], c1 = r3[2], c0 = r3[3];
+      const float hl = minmax ? r0[3] : a.ghl, emh = minmax ? r1[1] : a.gemh;
+      const float invWf = r1[3], invWX = r2[0], negDXW = r2[1], dcoef = r1[2];
+      const float Wf = minmax ? 1.f / invWf : 0.f;
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        float rf = floorf(u[r]);
+        if constexpr (!COMPACT) rf = fminf(minmax ? fmaxf(rf, 0.f) : rf, Kf - 1.f);
+        float arg = fmaf(rf, hl, b1lw);
+        if constexpr (CALIB == CAL_FWM) arg = u[r] < 0.f ? -INFINITY : arg;
+        if constexpr (minmax) arg = u[r] < -1.f ? -INFINITY : arg;
+        const float Ep = __builtin_amdgcn_exp2f(arg);
+        const float Elp = Ep * emh;
+        float t01 = u[r] - rf;
+        if constexpr (CALIB == CAL_RESOLVED) t01 = __builtin_amdgcn_fmed3f(t01, 0.f, 1.f);
+        float wLp = 0.f;
+        if constexpr (!nearest || minmax) wLp = fmaf(t01, Ep - Elp, Elp);
+        P[r] = nearest ? (t01 >= 0.5f ? Ep : Elp) : wLp;
+        dS[r] = fmaf(G[r], c1, c0) * Ep;
+        ps += dS[r];
+        if (want_cm) {
+          // dw^L/dM = X - w^L - Delta u / K, X = (r w^L + t e^{b_{r+1}}) / K,
+          // on the unscaled weights
+          const float Eu = Ep * Wf, wL = wLp * Wf;
+          const float gamma = fmaf(G[r], invWX, negDXW);
+          const float Delta = Eu * dcoef;
+          const float uc = rf + t01;
+          const float X = fmaf(rf, wL, t01 * Eu) * invK;
+          pm += gamma * (X - wL - Delta * uc * invK);
+        }
+      }
+    }
+    // dS to its scratch tile, in the dQ product's operand type
+    if constexpr (NP == 3) {
+      tile_store(a.st.dS + tile, lane, dS);
+    } else {
+      // 2 KiB: element (lane l, register r) at (r/8)*512 + 8l + r%8
+      uint16_t *dst = reinterpret_cast<uint16_t *>(a.st.dS) + tile + 8 * lane;
+#pragma unroll
+      for (int t2 = 0; t2 < 2; ++t2) {
+        bf16x8 w[1];
+        to_pieces<1>(reinterpret_cast<const float(&)[8]>(dS[8 * t2]), w);
+        *reinterpret_cast<u32x4 *>(dst + 512 * t2) = __builtin_bit_cast(u32x4, w[0]);
+      }
+    }
+    const int tb2 = tr_base<D>(lane);
+    // (one piece: dS takes P's place in LDS before the first product, whose
+    // MFMAs its reads then run under: B4 H16 T2048 d128 350 -> 335 us; with
+    // three pieces the 24 more registers cost more than that)
+    bf16x8 x[2][NP], xd[2][NP];
+    if constexpr (EXACT) {
+      product32(P, dos, i0, dva);
+      product32(dS, qs, i0, dka);
+    } else if constexpr (NP == 1) {
+      put_tile(P);
+      get_op(0, x[0]);
+      get_op(1, x[1]);
+      put_tile(dS);
+      get_op(0, xd[0]);
+      get_op(1, xd[1]);
+      product(x, dOb + tb2, dva);
+      product(xd, Qb + tb2, dka);
+    } else {
+      put_tile(P);
+      get_op(0, x[0]);
+      get_op(1, x[1]);
+      product(x, dOb + tb2, dva);
+      put_tile(dS);
+      get_op(0, x[0]);
+      get_op(1, x[1]);
+      product(x, Qb + tb2, dka);
+      dsout = dsout | row_out_of_pieces(dS);
+    }
+  };
+
   if (nt > 0) {
     fq.fetch(qs, qstart, T, tid);
     fd.fetch(dos, qstart, T, tid);
@@ -255,124 +439,12 @@ __global__ __launch_bounds__(256, (MainShape<TI, D>::OCC)) void bwd_main_kernel(
 
     float ps = 0.f, pm = 0.f;
     if ((jw < T) & !(a.causal & (jw > i0 + 31))) {
-      // the forward's decided positions of this (query, key) tile (one byte
-      // per key under FWM with Nearest)
-      const size_t tile = ds_tile(bh, i0 / 32, jw / 32, nq, a.causal) * 1024;
-      float u[16];
-      uint4 cw;
-      if constexpr (COMPACT) cw = codes_load(a.st.U + tile, lane);
-      else tile_load(a.st.U + tile, lane, u);
-      const uint16_t *dr = dOb + l32 * RS + 8 * half;
-      const f32x16 G = score_tile<D, NP>([&](int p, int s) { return row_op(dr + p * PS + 16 * s); },
-                                         [&](int p, int s) { return vop[p][s]; },
-                                         [](bf16x8 x, bf16x8 y, f32x16 c) { return mfma16(y, x, c); });
-      // some pair of the tile is not valid: key j is valid for this lane's
-      // query i iff j <= jlim
-      const bool edge = (a.causal & (jw + 31 > i0)) | (i0 + 32 > T) | (jw + 32 > T);
-      const int i = i0 + l32;
-      const int jlim = i < T ? (a.causal ? i : T - 1) : -1;
-      float P[16], dS[16];
-      if constexpr (EXPW) {
-        // u holds the forward's fp32 exponential e (bf16-rounded for
-        // BF16-exp); dz = gamma e (softmax; FP8-exp: the fp32
-        // exponential's derivative through an identity rounding), BF16-exp
-        // the backward of its casts, bf16(bf16(gamma) w)
-        if (edge) {
-#pragma unroll
-          for (int r = 0; r < 16; ++r) u[r] = jw + krel(r, half) <= jlim ? u[r] : 0.f;
-        }
-        const float invWf = r1[3], invWX = r2[0], negDXW = r2[1];
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const float e = u[r];
-          const float wf = RECON == REC_FP8EXP ? exp_weight_of<RECON>(e) : e;
-          const float gamma = fmaf(G[r], invWX, negDXW);
-          dS[r] = RECON == REC_BF16EXP ? bf16_rne(bf16_rne(gamma) * e) : gamma * e;
-          P[r] = wf * invWf;
-          ps += dS[r];
-        }
-      } else {
-        // a position whose weight is 0 (the FWM tail; below the argmin; minus
-        // infinity) where the key is not valid
-        constexpr float none = CALIB == CAL_FWM ? -1.f : CALIB == CAL_MINMAX ? -2.f : -INFINITY;
-        if constexpr (COMPACT) {
-          const uint32_t word[4] = {cw.x, cw.y, cw.z, cw.w};
-#pragma unroll
-          for (int r = 0; r < 16; ++r)  // r + up / 2, the tail -1/2
-            u[r] = fmaf((float)((word[r >> 2] >> (8 * (r & 3))) & 0xFFu), 0.5f, -0.5f);
-        }
-        if (edge) {
-#pragma unroll
-          for (int r = 0; r < 16; ++r) u[r] = jw + krel(r, half) <= jlim ? u[r] : none;
-        }
-        // e' = e^{b_{r+1}} / W from one exponential (RR_B1LW): P is e' or
-        // e' e^{-h} (LERP: the chord between them), dS = (g c1 + c0) e'
-        const float b1lw = r3[1], c1 = r3[2], c0 = r3[3];
-        const float hl = minmax ? r0[3] : a.ghl, emh = minmax ? r1[1] : a.gemh;
-        const float invWf = r1[3], invWX = r2[0], negDXW = r2[1], dcoef = r1[2];
-        const float Wf = minmax ? 1.f / invWf : 0.f;
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          float rf = floorf(u[r]);
-          if constexpr (!COMPACT) rf = fminf(minmax ? fmaxf(rf, 0.f) : rf, Kf - 1.f);
-          float arg = fmaf(rf, hl, b1lw);
-          if constexpr (CALIB == CAL_FWM) arg = u[r] < 0.f ? -INFINITY : arg;
-          if constexpr (minmax) arg = u[r] < -1.f ? -INFINITY : arg;
-          const float Ep = __builtin_amdgcn_exp2f(arg);
-          const float Elp = Ep * emh;
-          float t01 = u[r] - rf;
-          if constexpr (CALIB == CAL_RESOLVED) t01 = __builtin_amdgcn_fmed3f(t01, 0.f, 1.f);
-          float wLp = 0.f;
-          if constexpr (!nearest || minmax) wLp = fmaf(t01, Ep - Elp, Elp);
-          P[r] = nearest ? (t01 >= 0.5f ? Ep : Elp) : wLp;
-          dS[r] = fmaf(G[r], c1, c0) * Ep;
-          ps += dS[r];
-          if (want_cm) {
-            // dw^L/dM = X - w^L - Delta u / K, X = (r w^L + t e^{b_{r+1}}) / K,
-            // on the unscaled weights
-            const float Eu = Ep * Wf, wL = wLp * Wf;
-            const float gamma = fmaf(G[r], invWX, negDXW);
-            const float Delta = Eu * dcoef;
-            const float uc = rf + t01;
-            const float X = fmaf(rf, wL, t01 * Eu) * invK;
-            pm += gamma * (X - wL - Delta * uc * invK);
-          }
-        }
-      }
-      // dS to its scratch tile, in the dQ product's operand type
-      if constexpr (NP == 3) {
-        tile_store(a.st.dS + tile, lane, dS);
-      } else {
-        // 2 KiB: element (lane l, register r) at (r/8)*512 + 8l + r%8
-        uint16_t *dst = reinterpret_cast<uint16_t *>(a.st.dS) + tile + 8 * lane;
-#pragma unroll
-        for (int t2 = 0; t2 < 2; ++t2) {
-          bf16x8 w[1];
-          to_pieces<1>(reinterpret_cast<const float(&)[8]>(dS[8 * t2]), w);
-          *reinterpret_cast<u32x4 *>(dst + 512 * t2) = __builtin_bit_cast(u32x4, w[0]);
-        }
-      }
-      const int tb2 = tr_base<D>(lane);
-      // (one piece: dS takes P's place in LDS before the first product, whose
-      // MFMAs its reads then run under: B4 H16 T2048 d128 350 -> 335 us; with
-      // three pieces the 24 more registers cost more than that)
-      bf16x8 x[2][NP], xd[2][NP];
-      put_tile(P);
-      get_op(0, x[0]);
-      get_op(1, x[1]);
-      if constexpr (NP == 1) {
-        put_tile(dS);
-        get_op(0, xd[0]);
-        get_op(1, xd[1]);
-        product(x, dOb + tb2, dva);
-        product(xd, Qb + tb2, dka);
-      } else {
-        product(x, dOb + tb2, dva);
-        put_tile(dS);
-        get_op(0, x[0]);
-        get_op(1, x[1]);
-        product(x, Qb + tb2, dka);
-      }
+      // (padding lanes of the last tile hold row T - 1's record)
+      bool exact = false;
+      if constexpr (NP == 3) exact = vout || __any(signbit(r3[0]));
+      if constexpr (NP == 3)
+        if (exact) tile_as(i0, Qb, dOb, ps, pm, std::true_type{});
+      if (!exact) tile_as(i0, Qb, dOb, ps, pm, std::false_type{});
     }
     fetch_rec(i0 + BQ);  // the next tile's (past the last row: clamped)
     ps += __shfl_xor(ps, 32);
@@ -386,6 +458,30 @@ __global__ __launch_bounds__(256, (MainShape<TI, D>::OCC)) void bwd_main_kernel(
   if (nt > 0) {
     lds_barrier();
     flush(nt - 1);
+  }
+  if constexpr (NP == 3) {
+    // a dS out of range of the pieces: the wave's dK again on the fp32 MFMA, from
+    // the dS tiles it stored
+    if (__any(dsout)) {
+      __threadfence();
+#pragma unroll
+      for (int c = 0; c < NC; ++c)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) dka[c][e] = 0.f;
+      const int key = 256 * (l32 >> 3) + 128 * ((l32 >> 2) & 1) + (l32 & 3);
+#pragma unroll 1
+      for (int i0 = qstart; i0 < qstart + nt * BQ; i0 += BQ) {
+        if (a.causal & (jw > i0 + 31)) continue;
+        const float *x = a.st.dS + ds_tile(bh, i0 / 32, jw / 32, nq, a.causal) * 1024 + key;
+        const RowRead<D> rq(qs, i0, T, half, l32);
+#pragma unroll 1
+        for (int e = 0; e < 16; ++e) {
+          const float xv = x[4 * (2 * e + half)];
+#pragma unroll
+          for (int c = 0; c < NC; ++c) dka[c] = mfma32(xv, rq.at(2 * e, 32 * c), dka[c]);
+        }
+      }
+    }
   }
   // write dV, dK (lane -> column, register -> key)
 #pragma unroll
@@ -425,6 +521,7 @@ __global__ __launch_bounds__(128 * QG, (DqShape<TI, D>::OCC)) void bwd_dq_kernel
   using St = Stage<D, 64, NT, TI>;
   constexpr int RS = St::RS, PS = St::PS, RED = QG * NC * 16 * 64 * 2;
   __shared__ __attribute__((aligned(16))) uint16_t Ks[St::SIZE > RED ? St::SIZE : RED];
+  __shared__ int Bad[2 * QG];
 
   const int tid = threadIdx.x;
   const int lane = tid & 63, half = lane >> 5, l32 = lane & 31;
@@ -480,7 +577,15 @@ __global__ __launch_bounds__(128 * QG, (DqShape<TI, D>::OCC)) void bwd_dq_kernel
                             512 * e + 8 * lane);
   };
   const uint16_t *kb = Ks + kh * 32 * RS + tr_base<D>(lane);
+  PieceCheck check;  // of the K values that this thread staged
+  bool dout = false;  // some dS tile of this lane is out of range of the pieces
   auto mma_step = [&](const u32x4 (&dx)[ND]) {
+    if constexpr (NP == 3) {
+      float x[16];
+#pragma unroll
+      for (int r = 0; r < 16; ++r) x[r] = __uint_as_float(dx[r / 4][r % 4]);
+      dout = dout | row_out_of_pieces(x);
+    }
 #pragma unroll
     for (int t = 0; t < 2; ++t) {
       bf16x8 av[NP];
@@ -532,7 +637,7 @@ __global__ __launch_bounds__(128 * QG, (DqShape<TI, D>::OCC)) void bwd_dq_kernel
   if constexpr (NE == 1) load_qv();
   auto step = [&](int p, u32x4 (&dx)[ND]) {
     if (p > 0) lds_barrier();
-    fk.stash(Ks, tid);
+    fk.stash(Ks, tid, &check);
     fetch_k(p + 1);
     lds_barrier();
     if (p < npw) mma_step(dx);
@@ -543,8 +648,34 @@ __global__ __launch_bounds__(128 * QG, (DqShape<TI, D>::OCC)) void bwd_dq_kernel
     if (p + 1 >= nstep) break;
     step(p + 1, dB);
   }
+  if constexpr (NP == 3) {
+    const bool out = __any(check.bad());
+    if (lane == 0) Bad[wave] = out;
+  }
   // key half 1 hands its partial sums to key half 0
   __syncthreads();
+  if constexpr (NP == 3) {
+    // a value out of range of the pieces in the K chunks or in this wave's dS:
+    // the wave's product again on the fp32 MFMA, its operands from memory
+    if (any_flag<2 * QG>(Bad) || __any(dout)) {
+#pragma unroll
+      for (int c = 0; c < NC; ++c)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) acc[c][e] = 0.f;
+#pragma unroll 1
+      for (int p = 0; p < npw; ++p) {
+        const int kt = 2 * (c0 + p) + kh;
+        const RowRead<D> rk(ks, kt * 32, T, 4 * half, l32);
+        const float *x = a.st.dS + ds_tile(bh, qtc, kt, nq, a.causal) * 1024 + 4 * lane;
+#pragma unroll 1
+        for (int r = 0; r < 16; ++r) {
+          const float xv = x[256 * (r >> 2) + (r & 3)];
+#pragma unroll
+          for (int c = 0; c < NC; ++c) acc[c] = mfma32(xv, rk.at(krel0(r), 32 * c), acc[c]);
+        }
+      }
+    }
+  }
   {
     float *red = reinterpret_cast<float *>(Ks) + pq * (NC * 16 * 64) + lane;
     if (kh == 1) {

@@ -2,9 +2,10 @@
 // attention kernel for gfx950 (CDNA4, wave64, bf16 MFMA 32x32x16 with fp32
 // accumulation; fp32 scores on the fp32 MFMA 32x32x2).
 //
-// fp32 operands on the bf16 matrix unit. An fp32 value is the exact sum of
-// three bf16 pieces x = x0 + x1 + x2, each the nearest bf16 of what is left
-// (|x1| <= 2^-9 |x|, |x2| <= 2^-18 |x|), and a product x y is taken as the six
+// fp32 operands on the bf16 matrix unit. An fp32 value of 2^-100 to 2^126, or 0,
+// is the exact sum of three bf16 pieces x = x0 + x1 + x2, each the nearest bf16
+// of what is left (|x1| <= 2^-9 |x|, |x2| <= 2^-18 |x|; for other values see
+// PieceCheck), and a product x y is taken as the six
 // piece products down to 2^-18: x2 y0, x1 y1, x0 y2, x1 y0, x0 y1, x0 y0. The
 // three that are left out are at most 2^-26 |x y| together, below the fp32
 // rounding of one product. bf16 MFMA runs at 16 times the fp32 MFMA's rate, so
@@ -617,6 +618,49 @@ template <int NP> __device__ __forceinline__ void to_pieces(const float (&x)[8],
   }
 }
 
+// Operands outside the range of the pieces. Three bf16 pieces hold an fp32 value
+// of 2^-100 .. 2^126, or 0, exactly, and their products stay where the value's
+// do. Below, the last piece comes near bf16's smallest value; above, the first
+// one rounds to infinity, and an infinity or NaN spreads to the value that it is
+// split with. A product with such an operand is taken on the fp32 MFMA instead,
+// with its rows read from memory. 12 operations per eight values.
+constexpr float PIECE_LO = 0x1p-100f, PIECE_HI = 0x1p126f;
+__device__ __forceinline__ bool out_of_pieces(float x) {
+  return !(fabsf(x) < PIECE_HI) | ((fabsf(x) < PIECE_LO) & (x != 0.f));
+}
+struct PieceCheck {
+  typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
+  u16x2 lo = {0xffff, 0xffff};  // least of 2 |bits of the first piece| - 1 (0: the most)
+  float hi = 0.f;               // largest magnitude, NaN if there is one
+  __device__ __forceinline__ void add(const float (&x)[8], u32x4 p0) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const uint32_t word = p0[e];
+      const u16x2 w = __builtin_bit_cast(u16x2, word);
+      lo = __builtin_elementwise_min(lo, w * u16x2{2, 2} - u16x2{1, 1});
+      hi = __builtin_elementwise_maximum(
+          __builtin_elementwise_maximum(fabsf(x[2 * e]), fabsf(x[2 * e + 1])), hi);
+    }
+    asm volatile("" : "+v"(lo), "+v"(hi));  // (now, or x and p0 stay live until bad())
+  }
+  __device__ __forceinline__ bool bad() const {
+    constexpr unsigned short least = 2 * ((127 - 100) << 7) - 1;
+    return (lo[0] < least) | (lo[1] < least) | !(hi < PIECE_HI);
+  }
+};
+// Computed operands (score gradients) have a range of their own in every row: the
+// lane's 16 values of one row are out of range by their largest. What the others
+// then lose is 2^-33 of it at most.
+__device__ __forceinline__ bool row_out_of_pieces(const float (&x)[16]) {
+  float m = 0.f;
+#pragma unroll
+  for (int r = 0; r < 16; r += 2)
+    m = __builtin_elementwise_maximum(
+        __builtin_elementwise_maximum(fabsf(x[r]), fabsf(x[r + 1])), m);
+  asm volatile("" : "+v"(m));  // (now, or x stays live until the answer is used)
+  return !(m < PIECE_HI) | ((m < PIECE_LO) & (m > 0.f));
+}
+
 // c += a b over one 16-term k-step, all its piece products.
 template <int NP>
 __device__ __forceinline__ f32x16 mma(const bf16x8 (&a)[NP], const bf16x8 (&b)[NP], f32x16 c) {
@@ -662,11 +706,12 @@ __device__ __forceinline__ f32x16 score_tile(const bf16x8 (&aop)[NP][D / 16],
 }
 
 // The lane's operand of one 32-row tile of a [T, D] slice (rows at or beyond
-// T read as zero).
+// T read as zero); whether the lane holds a value out of range of the pieces.
 template <int D, typename TI>
-__device__ __forceinline__ void load_rows(const TI *slice, int row, int T, int half,
+__device__ __forceinline__ bool load_rows(const TI *slice, int row, int T, int half,
                                           bf16x8 (&op)[Pieces<TI>::N][D / 16]) {
   const bool ok = row < T;
+  PieceCheck check;
   const TI *src = slice + (size_t)(ok ? row : 0) * D + 8 * half;
 #pragma unroll
   for (int s = 0; s < D / 16; ++s) {
@@ -680,6 +725,7 @@ __device__ __forceinline__ void load_rows(const TI *slice, int row, int T, int h
       }
       bf16x8 p[3];
       to_pieces<3>(x, p);
+      check.add(x, __builtin_bit_cast(u32x4, p[0]));
 #pragma unroll
       for (int i = 0; i < 3; ++i) op[i][s] = p[i];
     } else {
@@ -688,6 +734,7 @@ __device__ __forceinline__ void load_rows(const TI *slice, int row, int T, int h
       op[0][s] = as_op(v);
     }
   }
+  return sizeof(TI) == 4 && check.bad();
 }
 
 // ---- score operands ----------------------------------------------------------
@@ -759,7 +806,8 @@ template <int D, int ROWS, int NT, typename TI> struct Stage {
             u32x4, __builtin_amdgcn_raw_buffer_load_b128(rs, voff + 16u * g, 0, 0));
     }
   }
-  __device__ __forceinline__ void stash(uint16_t *dst, int tid) const {
+  // (check: looks the thread's values over, where given)
+  __device__ __forceinline__ void stash(uint16_t *dst, int tid, PieceCheck *check = nullptr) const {
     if (V8 % NT != 0 && tid >= V8) return;
 #pragma unroll
     for (int e = 0; e < PF; ++e) {
@@ -771,6 +819,7 @@ template <int D, int ROWS, int NT, typename TI> struct Stage {
         for (int i = 0; i < 8; ++i) f[i] = __uint_as_float(x[e][i / 4][i % 4]);
         u32x4 p[3];
         split8(f, p);
+        if (check) check->add(f, p[0]);
 #pragma unroll
         for (int i = 0; i < 3; ++i) *reinterpret_cast<u32x4 *>(d + i * PS) = p[i];
       } else {
@@ -813,6 +862,35 @@ template <int D, int ROWS, int NT> struct StageF32 {
     }
   }
 };
+
+// Rows from r0 on of a [T, D] fp32 slice, read element by element as operands of
+// the fp32 MFMA. (Rows at or past T read as zeros; d = 16: columns 16..31 are the
+// next row's, in operand columns whose results nobody reads.)
+template <int D> struct RowRead {
+  __amdgpu_buffer_rsrc_t rs;
+  uint32_t lane_off;  // bytes
+  // (slice: fp32; the callers' branch for it is not taken for other types)
+  template <typename TI>
+  __device__ __forceinline__ RowRead(const TI *slice, int r0, int T, int lane_row, int lane_col)
+      : rs(row_rsrc(reinterpret_cast<const float *>(slice), r0, T, D)),
+        lane_off(4u * (uint32_t)(lane_row * D + lane_col)) {}
+  __device__ __forceinline__ float at(int row, int col) const {
+    return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(
+                                         rs, lane_off + 4u * (uint32_t)(row * D + col), 0, 0));
+  }
+};
+// (the lane's key of register r: 4 half + krel0(r))
+__device__ __forceinline__ constexpr int krel0(int r) { return 8 * (r >> 2) + (r & 3); }
+
+// Whether any thread of the workgroup's NW waves found a staged chunk out of
+// range: each wave leaves its answer in flag[wave] before the barrier that
+// orders the chunk's stash.
+template <int NW> __device__ __forceinline__ bool any_flag(const int *flag) {
+  int f = 0;
+#pragma unroll
+  for (int w = 0; w < NW; ++w) f |= flag[w];
+  return __builtin_amdgcn_readfirstlane(f) != 0;
+}
 
 // Row-major operand: row `row` of a staged block, elements 8 half + 16 s ..
 __device__ __forceinline__ bf16x8 row_op(const uint16_t *p) {

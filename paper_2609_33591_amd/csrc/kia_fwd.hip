@@ -28,7 +28,8 @@
 //   first index and the number of its ties. The weights are absolute once the
 //   extrema are known, so the key parts' partial sums simply add (through
 //   LDS); O = (sum w v) / W at the end: W >= 1 because the argmax key has
-//   weight e^0 = 1, so no online rescaling.
+//   weight e^0 = 1, so no online rescaling. A wave whose V holds values that
+//   three pieces do not (PieceCheck) takes the pass again on the fp32 MFMA.
 // Exponential weight functions (softmax, BF16-exp, FP8-exp; App. A, App. D)
 //   take the same two passes with the maximum only: pass 2 forms z = s - M,
 //   the fp32 exponential as the weight function rounds it (kept in U) and the
@@ -71,6 +72,7 @@ __global__ __launch_bounds__(64 * RG * KP, (FwdShape<TI, D, RECON, RG, KP>::OCC)
   constexpr int RED = (KP - 1) * RG * 64 * NRED * 2;
   constexpr int SMEM = STG > RED ? STG : RED;
   __shared__ __attribute__((aligned(16))) uint16_t smem[SMEM];
+  __shared__ int Bad[EX ? RG * KP : 1];  // staged V out of range of the pieces
   __shared__ int Xc[KP > 1 ? RG * KP * 4 * 32 : 1];  // [row group][key part][field][row]
 
   const int tid = threadIdx.x;
@@ -307,8 +309,9 @@ __global__ __launch_bounds__(64 * RG * KP, (FwdShape<TI, D, RECON, RG, KP>::OCC)
       }
     }
   };
-  // its weights and their products with V
-  auto accumulate = [&](int js, const float (&v)[16], const uint16_t *vb) {
+  // its weights and their products with V (EXACT: on the fp32 MFMA, V from memory)
+  auto accumulate_as = [&](int js, const float (&v)[16], const uint16_t *vb, auto tag) {
+    constexpr bool EXACT = decltype(tag)::value;
     uint32_t cw[4];
     float tWN = 0.f, tWL = 0.f;  // sub-tile sums first: shorter running sums
     // the weights of the lane's keys 8 t .. 8 t + 7, the k-slots of one step
@@ -351,6 +354,18 @@ __global__ __launch_bounds__(64 * RG * KP, (FwdShape<TI, D, RECON, RG, KP>::OCC)
       // (the bytes are made here: only the store below needs them, and left to
       // it they would keep the 16 positions live through the products)
       if constexpr (COMPACT) asm volatile("" : "+v"(cw[2 * t]), "+v"(cw[2 * t + 1]));
+      if constexpr (EXACT) {
+        const RowRead<D> rv(vs, js, T, 4 * half, l32);
+#pragma unroll
+        for (int e = 0; e < 8; ++e)
+#pragma unroll
+          for (int c = 0; c < NC; ++c) {
+            const float x = rv.at(krel0(8 * t + e), 32 * c);
+            oacc[c] = mfma32(x, w[e], oacc[c]);
+            if constexpr (OL) olacc[c] = mfma32(x, wl[e], olacc[c]);
+          }
+        continue;
+      }
       bf16x8 wo[NP], wlo[OL ? NP : 1];
       to_pieces<NP>(w, wo);
       if constexpr (OL) to_pieces<NP>(wl, wlo);
@@ -374,6 +389,10 @@ __global__ __launch_bounds__(64 * RG * KP, (FwdShape<TI, D, RECON, RG, KP>::OCC)
     WN += tWN;
     WLs += tWL;
   };
+  auto accumulate = [&](int js, const float (&v)[16], const uint16_t *vb) {
+    accumulate_as(js, v, vb, std::false_type{});
+  };
+  PieceCheck check;  // of the V values that this thread stages
   if constexpr (KEEP) {
     // the wave's scores come back from U one tile ahead (each lane reads what
     // it wrote itself; a tile's decisions replace them after that)
@@ -390,7 +409,7 @@ __global__ __launch_bounds__(64 * RG * KP, (FwdShape<TI, D, RECON, RG, KP>::OCC)
       const int js = p * CHK + kh * 32;
       if (PRIV && js > wlim) break;
       if (!PRIV && NBUF == 1 && p > 0) lds_barrier();
-      fv.stash(vbuf(p), stid);
+      fv.stash(vbuf(p), stid, &check);
       fv.fetch(vs, min(p + 1, nstep - 1) * CHK + soff, T, stid);
       f32x16 Sn;
       load_s(js + CHK, Sn);
@@ -415,7 +434,7 @@ __global__ __launch_bounds__(64 * RG * KP, (FwdShape<TI, D, RECON, RG, KP>::OCC)
       const f32x16 S = scores(kbuf(0));
       __builtin_amdgcn_sched_barrier(0);
       // V takes K's place, the next K is fetched
-      fv.stash(vbuf(0), lane);
+      fv.stash(vbuf(0), lane, &check);
       fk.fetch(ks, min(p + 1, nstep - 1) * CHK + soff, T, lane);
       __builtin_amdgcn_sched_barrier(0);
       float v[16];
@@ -429,7 +448,7 @@ __global__ __launch_bounds__(64 * RG * KP, (FwdShape<TI, D, RECON, RG, KP>::OCC)
       const int js = p * CHK + kh * 32;
       if (NBUF == 1) lds_barrier();
       stash_k(nstep + p, tid);
-      fv.stash(vbuf(nstep + p), tid);
+      fv.stash(vbuf(nstep + p), tid, &check);
       const int nx = min(p + 1, nstep - 1) * CHK;
       fk.fetch(ks, nx, T, tid);
       fv.fetch(vs, nx, T, tid);
@@ -443,6 +462,41 @@ __global__ __launch_bounds__(64 * RG * KP, (FwdShape<TI, D, RECON, RG, KP>::OCC)
         __builtin_amdgcn_sched_barrier(0);
         accumulate(js, v, vbuf(nstep + p) + vcol);
         __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+  }
+  if constexpr (EX) {
+    // V out of range of the pieces: the wave's pass 2 again, scores and P V both
+    // on the fp32 MFMA and their operands from memory
+    bool out = __any(check.bad());
+    if constexpr (!PRIV) {
+      if (lane == 0) Bad[wave] = out;
+      __syncthreads();
+      out = any_flag<RG * KP>(Bad);
+    }
+    if (out) {
+#pragma unroll
+      for (int c = 0; c < NC; ++c)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) {
+          oacc[c][e] = 0.f;
+          if constexpr (OL) olacc[c][e] = 0.f;
+        }
+      WN = 0.f, WLs = 0.f;
+      ax = 0x7fffffff, an = 0x7fffffff, cx = 0, cn = 0;
+      int qrow = min(row, T - 1), krow = l32, h = half;
+      asm volatile("" : "+v"(qrow), "+v"(krow), "+v"(h));
+#pragma unroll 1
+      for (int js = kh * 32; js <= wlim; js += CHK) {
+        Op ko, qo;
+        qo.load(a.q + slice, qrow, T, h);
+        ko.load(ks, js + krow, T, h);
+        const f32x16 S = Op::tile(ko, qo);
+        __builtin_amdgcn_sched_barrier(0);
+        float v[16];
+        decide(js, S, v);
+        __builtin_amdgcn_sched_barrier(0);
+        accumulate_as(js, v, nullptr, std::true_type{});
       }
     }
   }

@@ -104,9 +104,11 @@ template <typename TI, int D> struct MainShape {
   static constexpr int OCC = sizeof(TI) == 4 && D == 128 ? 1 : 2;
 };
 
-// Waves per SIMD of the dQ kernel.
+// Waves per SIMD of the dQ kernel. (fp32 at d = 64: in 128 registers the q rows
+// that are loaded ahead of the key loop spill, and the loop waits for them. B8 H12
+// T1024, four / three waves: 104 / 78.5 us.)
 template <typename TI, int D> struct DqShape {
-  static constexpr int OCC = D == 128 ? (sizeof(TI) == 4 ? 2 : 3) : 4;
+  static constexpr int OCC = D == 128 ? (sizeof(TI) == 4 ? 2 : 3) : (sizeof(TI) == 4 && D == 64 ? 3 : 4);
 };
 
 using FwdArgs = FwdArgsT<float>;
