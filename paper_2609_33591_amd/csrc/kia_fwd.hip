@@ -292,6 +292,13 @@ __global__ __launch_bounds__(64 * RG * KP, (FwdShape<TI, D, RECON, RG, KP>::OCC)
           v[r] = amb ? x : v[r];
         }
       }
+      // the position of an extremum rounds to either side of its end of the grid:
+      // t stays in [0, 1], so that a chord's weight is never below 0 or above its
+      // ends (for the backward too, which reads u)
+#pragma unroll
+      for (int r = 0; r < 16; ++r)
+        v[r] = CALIB == CAL_MINMAX ? __builtin_amdgcn_fmed3f(v[r], 0.f, 2.f * Kf)
+                                   : fminf(v[r], 2.f * Kf);
       if (diag) {
         // a position that no valid key takes and whose weight is 0: the FWM
         // tail, below the argmin (u >= 0 up to rounding), or minus infinity
