@@ -327,7 +327,8 @@ __global__ __launch_bounds__(256, (MainShape<TI, D>::OCC)) void bwd_main_kernel(
         const float e = u[r];
         const float wf = RECON == REC_FP8EXP ? exp_weight_of<RECON>(e) : e;
         const float gamma = fmaf(G[r], invWX, negDXW);
-        dS[r] = RECON == REC_BF16EXP ? bf16_rne(bf16_rne(gamma) * e) : gamma * e;
+        dS[r] = RECON == REC_BF16EXP ? bf16_rne(mul_or_0(bf16_rne(gamma), e))
+                                          : mul_or_0(gamma, e);
         P[r] = wf * invWf;
         ps += dS[r];
       }
@@ -343,7 +344,11 @@ __global__ __launch_bounds__(256, (MainShape<TI, D>::OCC)) void bwd_main_kernel(
       }
       if (edge) {
 #pragma unroll
-        for (int r = 0; r < 16; ++r) u[r] = jw + krel(r, half) <= jlim ? u[r] : none;
+        for (int r = 0; r < 16; ++r) {
+          const bool valid = jw + krel(r, half) <= jlim;
+          u[r] = valid ? u[r] : none;
+          if constexpr (minmax) G[r] = valid ? G[r] : 0.f;  // (for pm)
+        }
       }
       // e' = e^{b_{r+1}} / W from one exponential (RR_B1LW): P is e' or
       // e' e^{-h} (LERP: the chord between them), dS = (g c1 + c0) e'
@@ -365,7 +370,7 @@ __global__ __launch_bounds__(256, (MainShape<TI, D>::OCC)) void bwd_main_kernel(
         float wLp = 0.f;
         if constexpr (!nearest || minmax) wLp = fmaf(t01, Ep - Elp, Elp);
         P[r] = nearest ? (t01 >= 0.5f ? Ep : Elp) : wLp;
-        dS[r] = fmaf(G[r], c1, c0) * Ep;
+        dS[r] = mul_or_0(fmaf(G[r], c1, c0), Ep);
         ps += dS[r];
         if (want_cm) {
           // dw^L/dM = X - w^L - Delta u / K, X = (r w^L + t e^{b_{r+1}}) / K,

@@ -380,6 +380,13 @@ __device__ __forceinline__ float bf16_rne(float x) {
   return __uint_as_float(b & 0xFFFF0000u);
 }
 
+// a w with a zero w giving 0 whatever a is (infinite, NaN): a score gradient whose
+// key has no weight. At the cost of a product: v_mul_legacy_f32, which keeps
+// denormals as v_mul_f32 does. (The intrinsic and not inline asm: the compiler has
+// to see the wait that an exponential's result needs before its use.)
+__device__ float amdgcn_fmul_legacy(float, float) __asm("llvm.amdgcn.fmul.legacy");
+__device__ __forceinline__ float mul_or_0(float a, float w) { return amdgcn_fmul_legacy(a, w); }
+
 // Two fp32 values as one word of two bf16 (round to nearest even; a in the
 // low half).
 __device__ __forceinline__ uint32_t pack_bf16x2(float a, float b) {
