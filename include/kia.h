@@ -456,18 +456,18 @@ int kia_timing_read(const char *name, double *total_ms, int *launches);
 /*
  * Launch-shape policy (process-wide, not thread-safe; affects later calls).
  * KIA_GRID_AUTO (default) picks per call. The forward takes workgroups of
- * 128 rows where there are more than two such blocks per CU, of two 32-row
- * groups with two key halves down to one per CU, and below that of one row
- * group with four key quarters (fp32 inputs at d = 64 below half a block per
- * CU: eight key parts). The backward's main kernel splits each key block's
- * query range over several workgroups where that shortens the longest one by
- * more than the added atomics cost (dK, dV added atomically), and where the
- * dQ kernel's groups of query tiles do not fill the chip their keys are cut
- * into pieces (dQ added atomically); both for fp32 and bf16 inputs.
+ * four 32-row groups on large grids, then two with two key halves, and one
+ * with four or eight key parts on the smallest. The backward's main kernel
+ * splits each key block's query range over several workgroups where that
+ * shortens the longest one by more than the added atomics cost (dK, dV added
+ * atomically), and where the dQ kernel's groups of query tiles do not fill the
+ * chip their keys are cut into pieces (dQ added atomically); both for fp32 and
+ * bf16 inputs.
  * KIA_GRID_WIDE never splits; KIA_GRID_SPLIT always does (the forward's
- * smallest row groups, the backward's splits in at least two parts). The policies compute the same decisions,
- * extrema and codes; O, W and the gradients differ only in fp32 summation
- * order (neither backward is bitwise repeatable: see Determinism above).
+ * smallest row groups, the backward's splits in at least two parts). The
+ * policies compute the same decisions, extrema and codes; O, W and the
+ * gradients differ only in fp32 summation order (neither backward is bitwise
+ * repeatable: see Determinism above).
  * Returns KIA_ERR_ENUM for another value.
  */
 #define KIA_GRID_AUTO 0

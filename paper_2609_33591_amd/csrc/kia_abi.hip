@@ -197,24 +197,42 @@ void launch_fwd_k(const FwdArgsT<TI> &a, hipStream_t s) {
     hipLaunchKernelGGL((fwd_kernel<TI, D, CALIB, REC_NEAREST, false, RG, KP>), grid, block, 0, s, a);
 }
 
-// Launch shape by the number of 128-row blocks. Above two per CU, 128 rows
-// share each staged tile; below, row groups are given up for key parts, so
-// that the longest causal row's keys are spread over two or four waves and
-// there are enough workgroups. Measured at d = 64, T = 1024, FWM with Nearest
-// and Prob-STE, fp32 (us): 192 blocks 126 / 94 / 72 (4 x 1 / 2 x 2 / 1 x 4),
-// 320 blocks 134 / 98 / 101, 512 blocks 145 / 147 / 147, 768 blocks
-// 175 / 195 / 213; bf16 192 blocks 66 / 42 / 33, 512 blocks 69 / 58 / 64. With
-// fp32 inputs at d = 64 a 1 x 8 workgroup still gains on the smallest grids
-// (96 blocks: 49 against 53).
+// Launch shape by the number of 128-row blocks. On large grids 128 rows share each
+// staged tile; below, row groups are given up for key parts, so that the longest
+// causal row's keys are spread over two, four or eight waves and there are enough
+// workgroups. Measured at T = 1024, FWM with Nearest and Prob-STE, a training
+// forward (us; 1 x 8 / 1 x 4 / 2 x 2 / 4 x 1):
+//   fp32 d = 16   96 blocks 29 / 31 / 54 / 98, 320 74 / 62 / 66 / 104,
+//                 512 112 / 86 / 92 / 108, 768 - / 123 / 124 / 131
+//   fp32 d = 32   96 blocks 33 / 37 / 59 / 113, 320 88 / 71 / 69 / 124,
+//                 512 132 / 102 / 102 / 138, 768 - / 147 / 139 / 163
+//   fp32 d = 64   96 blocks 48 / 52 / 80 / 135, 320 128 / 99 / 96 / 147,
+//                 512 191 / 143 / 141 / 155, 768 - / 218 / 190 / 197
+//   fp32 d = 128  96 blocks - / 79 / 120 / 209, 192 - / 148 / 128 / 213,
+//                 512 - / 346 / 273 / 255
+//   bf16 d = 64   96 blocks - / 26 / 40 / 66, 320 - / 48 / 44 / 69, 768 - / 92 / 78 / 78
+//   bf16 d = 128  96 blocks - / 45 / 61 / 86, 192 - / 72 / 61 / 88, 768 - / 270 / 140 / 111
+// Up to three blocks per CU 4 x 1 leaves its second round half empty. fp32 at
+// d = 16 takes it from two up all the same where a backward follows: it leaves the
+// scores out of U, which between two kernels does not stay in cache (a step at 768
+// blocks 306 / 304 / 299 for the last three, the forward alone 100 / 100 / 106).
+// One 1 x 4 workgroup fills a CU's LDS with fp32 V or with O and O_l sums at
+// d = 128 (`alone`). Eight parts need more than four key tiles.
 template <typename TI, int D, int CALIB>
 void launch_fwd_c(const FwdArgsT<TI> &a, hipStream_t s) {
+  constexpr bool F32 = sizeof(TI) == 4;
   const long blocks = (long)a.BH * ((a.T + 127) / 128), cus = device_cus();
   const bool split = g_grid == KIA_GRID_SPLIT, autog = g_grid == KIA_GRID_AUTO;
-  if constexpr (D == 64 && sizeof(TI) == 4) {
-    if (split || (autog && blocks < cus / 2)) return launch_fwd_k<TI, D, CALIB, 1, 8>(a, s);
+  if constexpr (F32 && D <= 64) {
+    if (split || (autog && blocks <= cus / 2 && a.T > 128))
+      return launch_fwd_k<TI, D, CALIB, 1, 8>(a, s);
   }
-  if (split || (autog && blocks <= cus)) return launch_fwd_k<TI, D, CALIB, 1, 4>(a, s);
-  if (autog && blocks <= 2 * cus) return launch_fwd_k<TI, D, CALIB, 2, 2>(a, s);
+  const bool alone = a.st.OL ? FwdShape<TI, D, REC_NEAREST, true, 1, 4>::OCC == 1
+                             : FwdShape<TI, D, REC_LERP, false, 1, 4>::OCC == 1;
+  const long most14 = alone ? cus / 2 : F32 && D == 16 ? 2 * cus : cus;
+  const long most22 = D == 128 || (F32 && D == 16 && a.keep) ? 2 * cus : 3 * cus;
+  if (split || (autog && blocks <= most14)) return launch_fwd_k<TI, D, CALIB, 1, 4>(a, s);
+  if (autog && blocks <= most22) return launch_fwd_k<TI, D, CALIB, 2, 2>(a, s);
   launch_fwd_k<TI, D, CALIB, 4, 1>(a, s);
 }
 

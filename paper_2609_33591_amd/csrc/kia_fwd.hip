@@ -43,8 +43,8 @@
 namespace kia {
 
 template <typename TI, int D, int CALIB, int RECON, bool OL, int RG, int KP>
-__global__ __launch_bounds__(64 * RG * KP, (FwdShape<TI, D, RECON, RG, KP>::OCC)) void fwd_kernel(FwdArgsT<TI> a) {
-  using Shape = FwdShape<TI, D, RECON, RG, KP>;
+__global__ __launch_bounds__(64 * RG * KP, (FwdShape<TI, D, RECON, OL, RG, KP>::OCC)) void fwd_kernel(FwdArgsT<TI> a) {
+  using Shape = FwdShape<TI, D, RECON, OL, RG, KP>;
   constexpr int NP = Pieces<TI>::N, NC = D >= 32 ? D / 32 : 1;
   // MinMax and the resolved grid need the row minimum (resolved: for the
   // rounding margin of its far keys only)
@@ -62,14 +62,13 @@ __global__ __launch_bounds__(64 * RG * KP, (FwdShape<TI, D, RECON, RG, KP>::OCC)
   using StK = std::conditional_t<EX, StageF32<D, SROWS, SNT>, St>;
   using Op = ScoreOp<TI, D>;
   constexpr int RS = St::RS, PS = St::PS;
-  // per-lane values a wave of key part > 0 hands to part 0 at the end
-  constexpr int NRED = NC * 16 * (OL ? 2 : 1) + 2;
+  constexpr int NRED = Shape::NRED;
   // K chunks, then V chunks; at the end the key parts' sums (16-bit units; a K
   // block fits in a V block's place)
   constexpr int KSIZE = EX ? 2 * StK::SIZE : St::SIZE;
   static_assert(KSIZE <= St::SIZE, "K in V's place");
   constexpr int STG = PRIV ? KP * St::SIZE : NBUF * (KEEP ? St::SIZE : KSIZE + St::SIZE);
-  constexpr int RED = (KP - 1) * RG * 64 * NRED * 2;
+  constexpr int RED = Shape::RED / 2;
   constexpr int SMEM = STG > RED ? STG : RED;
   __shared__ __attribute__((aligned(16))) uint16_t smem[SMEM];
   __shared__ int Bad[EX ? RG * KP : 1];  // staged V out of range of the pieces
@@ -608,14 +607,14 @@ __global__ __launch_bounds__(64 * RG * KP, (FwdShape<TI, D, RECON, RG, KP>::OCC)
   template __global__ void fwd_kernel<float, D, CAL_FWM, REC_SOFTMAX, false, RG, KP>(FwdArgs); \
   template __global__ void fwd_kernel<float, D, CAL_FWM, REC_BF16EXP, false, RG, KP>(FwdArgs); \
   template __global__ void fwd_kernel<float, D, CAL_FWM, REC_FP8EXP, false, RG, KP>(FwdArgs);
-// every launch shape of one head dimension (d = 64 in fp32 has one more)
-#define KIA_FWD_D(D)             \
-  KIA_FWD_GRID(float, D, 4, 1)   \
-  KIA_FWD_EXP(D, 4, 1)           \
-  KIA_FWD_GRID(float, D, 2, 2)   \
-  KIA_FWD_EXP(D, 2, 2)           \
-  KIA_FWD_GRID(float, D, 1, 4)   \
-  KIA_FWD_EXP(D, 1, 4)           \
+#define KIA_FWD_F32(D, RG, KP)    \
+  KIA_FWD_GRID(float, D, RG, KP)  \
+  KIA_FWD_EXP(D, RG, KP)
+// the launch shapes of one head dimension
+#define KIA_FWD_D(D)              \
+  KIA_FWD_F32(D, 4, 1)            \
+  KIA_FWD_F32(D, 2, 2)            \
+  KIA_FWD_F32(D, 1, 4)            \
   KIA_FWD_GRID(uint16_t, D, 4, 1) \
   KIA_FWD_GRID(uint16_t, D, 2, 2) \
   KIA_FWD_GRID(uint16_t, D, 1, 4)
@@ -623,12 +622,13 @@ __global__ __launch_bounds__(64 * RG * KP, (FwdShape<TI, D, RECON, RG, KP>::OCC)
 // One head dimension per compilation (KIA_HEAD, set by the build).
 #if KIA_HEAD == 16
 KIA_FWD_D(16)
+KIA_FWD_F32(16, 1, 8)
 #elif KIA_HEAD == 32
 KIA_FWD_D(32)
+KIA_FWD_F32(32, 1, 8)
 #elif KIA_HEAD == 64
 KIA_FWD_D(64)
-KIA_FWD_GRID(float, 64, 1, 8)
-KIA_FWD_EXP(64, 1, 8)
+KIA_FWD_F32(64, 1, 8)
 #elif KIA_HEAD == 128
 KIA_FWD_D(128)
 #else

@@ -23,15 +23,16 @@ template <typename TI> struct FwdArgsT {
 };
 
 // Launch shape of the forward: NBUF staging buffers per tensor, OCC waves per
-// SIMD (one where large chunks take more than half the LDS; fp32 inputs at
-// d = 128 with Nearest: one as well, two spill). fp32 scores come from the fp32
+// SIMD (one where a chunk or the key parts' sums take more than half the LDS; fp32
+// inputs at d = 128 with O_l: one as well, two spill. Without O_l two are faster,
+// MinMax Nearest B1 H40 T1024 159 -> 126 us). fp32 scores come from the fp32
 // MFMA (EX) and K is staged as it is. KEEP: the scores are kept in U between the
 // passes, and V takes K's place in LDS in the second. Computing them again
 // instead grows with d, the trip through U does not, and small grids have the
 // bandwidth to spare. Measured (us, kept / again), B8 H12 T1024 (4 x 1), MinMax
 // LERP: d = 16 117 / 99, d = 32 145 / 130, d = 64 175 / 213; B1 H12 T1024 (1 x 4),
 // FWM Nearest Prob-STE: d = 16 27.3 / 28.3, d = 32 31.8 / 34.7.
-template <typename TI, int D, int RECON, int RG, int KP> struct FwdShape {
+template <typename TI, int D, int RECON, bool OL, int RG, int KP> struct FwdShape {
   static constexpr bool EX = fp32_scores<TI>();
   static constexpr bool KEEP = EX && (D >= 64 || RG < 4);
   // bytes of one staged block of V and of K
@@ -39,8 +40,11 @@ template <typename TI, int D, int RECON, int RG, int KP> struct FwdShape {
   static constexpr int KB = EX ? 32 * KP * (D + 4) * 4 : VB;
   static constexpr int WGS = RG * KP == 8 ? 1 : 2;  // workgroups that make two waves per SIMD
   static constexpr int LDS = RG == 1 || KEEP ? VB : VB + KB;  // a buffer for each tensor, or one for both
+  // values a lane of key part > 0 hands to part 0 at the end, and their bytes
+  static constexpr int NRED = (D >= 32 ? D / 32 : 1) * 16 * (OL ? 2 : 1) + 2;
+  static constexpr int RED = (KP - 1) * RG * 64 * NRED * 4;
   static constexpr int OCC =
-      LDS * WGS > 156 * 1024 || (EX && D == 128 && RECON == REC_NEAREST) ? 1 : 2;
+      (LDS > RED ? LDS : RED) * WGS > 156 * 1024 || (EX && D == 128 && OL) ? 1 : 2;
   static constexpr int NBUF =
       2 * (KEEP ? VB : VB + KB) * (OCC == 2 ? WGS : 1) <= 156 * 1024 ? 2 : 1;
 };

@@ -182,9 +182,9 @@ def test_exact_score_parity_small(oracle_mod, variant):
                          ids=lambda v: "-".join(map(str, v)))
 def test_exact_score_parity_grid_policies(oracle_mod, policy, variant):
     """The small shapes again with the launch shape forced: "wide" takes the
-    forward's two row groups x two key halves and the unsplit backward, which
-    the default policy keeps for grids that fill the chip; "split" takes four
-    key quarters (d <= 64) and the split backward at every size."""
+    forward's four row groups and the unsplit backward, which the default policy
+    keeps for grids that fill the chip; "split" takes one row group with eight
+    (d <= 64) or four key parts and the split backward at every size."""
     calib, recon, ste, detach = variant
     kia.kia_set_grid_policy(policy)
     try:

@@ -1,7 +1,7 @@
 """The tiled kernels at the edges of their tiles, against the fp64 oracle.
 
-The forward works on 32-key x 32-query tiles in workgroups of 128, 64 or 32
-queries, the backward on 128-key blocks whose query range may be split and on
+The forward works on 32-key x 32-query tiles in workgroups of 128 ("wide") or 32
+queries here (64: see the launch shapes' own test), the backward on 128-key blocks whose query range may be split and on
 64-key chunks for dQ; T takes the values on both sides of each. Dyadic q and k
 make every score exact, so that codes, extrema and tie counts are compared bit
 for bit; the rest keeps the bounds of the parity tests (fp32: 1e-4 for O, 1e-3
