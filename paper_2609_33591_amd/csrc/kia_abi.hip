@@ -493,14 +493,25 @@ int attn_bwd(const TI *q, const TI *k, const TI *v, const float *o, const TI *dO
     const bool force = g_grid == KIA_GRID_SPLIT;
     const int cus = device_cus();
     // dQ: groups of dq_tiles(d) query tiles; when they do not fill the chip,
-    // their keys are cut into pieces so that there are about two per CU
+    // their keys are cut into pieces so that there are about two per CU. A bf16
+    // group at d = 128 takes its keys twice as fast as an fp32 one and a piece has
+    // the same atomic epilogue: one piece per CU of at least eight chunks, and none
+    // where the longest group has 16 chunks at most or three quarters of the CUs
+    // have one. Measured there, FWM Nearest / MinMax LERP (us; none, eight chunks
+    // at least, two per CU): B1 H24 T1024 27 / 37, 38 / 48, 47 / 59; B1 H14 T2048
+    // 38 / 54, 53 / 71, -; B1 H4 T2048 37 / 44, 25 / 36, -; B1 H1 T8192 (17 chunks)
+    // 102 / 114, 50 / 63, 59 / 70.
     const int qg = dq_tiles(d);
     const int npq = (T + 32 * qg - 1) / (32 * qg);
-    if (B * H * npq < cus || force) {
+    const bool light = sizeof(TI) == 2 && d == 128;
+    const int groups = B * H * npq, wanted = light ? cus : 2 * cus;
+    const bool split = light ? 4 * groups < 3 * cus && dq_chunks(npq - 1, T, causal, qg) > 16
+                             : groups < cus;
+    if (split || force) {
       long chunks = 0;
       for (int g = 0; g < npq; ++g) chunks += dq_chunks(g, T, causal, qg);
       chunks *= (long)B * H;
-      a.dq_piece = (int)std::max(2L, (chunks + 2L * cus - 1) / (2L * cus));
+      a.dq_piece = (int)std::max(light && !force ? 8L : 2L, (chunks + wanted - 1) / wanted);
     }
   }
   // the deterministic backward takes the unsplit launch shapes

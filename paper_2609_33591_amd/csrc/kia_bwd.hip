@@ -703,7 +703,8 @@ __global__ __launch_bounds__(128 * QG, (DqShape<TI, D>::OCC)) void bwd_dq_kernel
   bool ok = false;
   float cMt = 0.f, cm = 0.f;
   int am = 0, an = 0;
-  if (sp == 0 && grad_channels(a.grad) && row < T && rflag == 0.f) {
+  const bool cal = sp == 0 && grad_channels(a.grad);  // piece 0 adds them
+  if (cal && row < T && rflag == 0.f) {
     const int nmin = minmax ? rnmin : 1;
     ok = (rnmax == 1) & (nmin == 1);
     cMt = minmax ? rcM : -rss;
@@ -723,17 +724,28 @@ __global__ __launch_bounds__(128 * QG, (DqShape<TI, D>::OCC)) void bwd_dq_kernel
   if (kh == 0) {
 #pragma unroll
   for (int e0 = 0; e0 < 16; e0 += EB) {
-    float kM[EB][NC], km[EB][NC];
+    float kM[EB][NC] = {}, km[EB][NC] = {};
+    if (cal) {
 #pragma unroll
-    for (int b = 0; b < EB; ++b) {
-      const int src = krel(e0 + b, half);
-      const int iam = __shfl(am, src), ian = __shfl(an, src);
+      for (int b = 0; b < EB; ++b) {
+        const int src = krel(e0 + b, half);
+        const int iam = __shfl(am, src);
 #pragma unroll
-      for (int c = 0; c < NC; ++c) {
-        const int n = 32 * c + l32;
-        const int nn = n < D ? n : 0;
-        kM[b][c] = load1(ks + (size_t)iam * D + nn);
-        km[b][c] = minmax ? load1(ks + (size_t)ian * D + nn) : 0.f;
+        for (int c = 0; c < NC; ++c) {
+          const int n = 32 * c + l32;
+          kM[b][c] = load1(ks + (size_t)iam * D + (n < D ? n : 0));
+        }
+      }
+      if (minmax) {
+#pragma unroll
+        for (int b = 0; b < EB; ++b) {
+          const int ian = __shfl(an, krel(e0 + b, half));
+#pragma unroll
+          for (int c = 0; c < NC; ++c) {
+            const int n = 32 * c + l32;
+            km[b][c] = load1(ks + (size_t)ian * D + (n < D ? n : 0));
+          }
+        }
       }
     }
 #pragma unroll
@@ -762,8 +774,8 @@ __global__ __launch_bounds__(128 * QG, (DqShape<TI, D>::OCC)) void bwd_dq_kernel
   // per row for it
   if (a.det && grad_channels(a.grad) && kh == 0 && half == 0 && row < T)
     put_calib_record(a.st.part, ridx, ok, minmax, am, an, cMt * a.scale, cm * a.scale);
-  if constexpr (NE > 1) load_qv();
-  if (sp == 0 && grad_channels(a.grad) && !a.det) {
+  if (cal && !a.det) {
+    if constexpr (NE > 1) load_qv();
 #pragma unroll
     for (int u = 0; u < 16; ++u) {
       const int rr = 16 * kh + u;
