@@ -38,10 +38,10 @@
  *     (S_self, and cM under MinMax) are accumulated with float atomics, and
  *     so are the calibration terms and tie splits scattered onto the
  *     argmax/argmin keys of dK, so dQ and dK can differ in their last bits
- *     from run to run (within fp32 rounding); dV is repeatable unless the
- *     query ranges are split (KIA_GRID_*). kia_set_deterministic(1) makes
- *     every backward reduction run in a fixed order, so that the backward
- *     too is bitwise repeatable.
+ *     from run to run (within fp32 rounding); dV is repeatable unless a
+ *     small grid is split (KIA_GRID_*: fewer 128-key blocks than CUs).
+ *     kia_set_deterministic(1) makes every backward reduction run in a fixed
+ *     order, so that the backward too is bitwise repeatable.
  *   - calib: 0 MinMax, 1 FWM, 2 resolved (FWM and resolved need a finite
  *     tau > 0; tau ignored for MinMax).
  *     recon: 0 LERP, 1 Nearest (2-4: exponential weight functions, see

@@ -446,9 +446,12 @@ int main_parts(int BH, int T, int d, bool f32, int causal) {
   const double blocks = (double)BH * ((T + 127) / 128), L = (T + 31) / 32;
   const double slots = device_cus() * (f32 && d == 128 ? 1.0 : 2.0);
   const double cost = (f32 ? 0.02 : 0.035) * std::min(d, 80) / 64.0;
-  // no further than the point where every slot is busy throughout
-  const double most = std::ceil((causal ? 2.0 : 1.0) * slots / blocks);
-  int n = (int)std::min(8.0, std::min(most, std::floor(std::sqrt(L / (cost * blocks)) + 0.5)));
+  // no further than the point where every slot is busy throughout, nor than one
+  // query tile a part
+  const double most = std::min(L, std::ceil((causal ? 2.0 : 1.0) * slots / blocks));
+  // (from one block per CU up four at most, see BwdArgsT::fold)
+  const double cap = blocks < device_cus() ? 8.0 : 4.0;
+  int n = (int)std::min(cap, std::min(most, std::floor(std::sqrt(L / (cost * blocks)) + 0.5)));
   return std::max(n, g_grid == KIA_GRID_SPLIT ? 2 : 1);
 }
 
@@ -514,8 +517,15 @@ int attn_bwd(const TI *q, const TI *k, const TI *v, const float *o, const TI *dO
       a.dq_piece = (int)std::max(light && !force ? 8L : 2L, (chunks + wanted - 1) / wanted);
     }
   }
+  // from one 128-key block per CU up dV is bitwise repeatable: at most two parts
+  // add into one buffer (the groups of the dQ kernel fill the chip there, so it
+  // is free; not where the policy cuts them all the same)
+  if (a.qsplit > 2 && (long)B * H * ((T + 127) / 128) >= device_cus()) {
+    if (a.dq_piece > 0) a.qsplit = 2;
+    else a.fold = 1;
+  }
   // the deterministic backward takes the unsplit launch shapes
-  if (g_det) { a.qsplit = 1; a.dq_piece = 0; a.det = 1; }
+  if (g_det) { a.qsplit = 1; a.dq_piece = 0; a.fold = 0; a.det = 1; }
   if (bo && a.qsplit == 1) a.dv16 = bo->dv;
   a.tau = calib != KIA_CALIB_MINMAX ? tau : 0.f;
   if (is_exp_rec(recon)) { a.calib = CAL_FWM; a.tau = 0.f; a.K = 1; a.ste = STE_WEIGHT; }

@@ -52,7 +52,7 @@ __global__ __launch_bounds__(256) void bwd_pre_kernel(BwdArgsT<TI> a) {
   const bool live = ridx < R;
   const bool probN = (a.recon == REC_NEAREST) & (a.ste == STE_PROB);
   float dot = 0.f;
-  if (live && a.dq_piece > 0) {  // the dQ pieces add into dQ
+  if (live && (a.dq_piece > 0 || a.fold)) {  // the dQ pieces, or parts of dV, add into dQ
     const f32x4 z = {0.f, 0.f, 0.f, 0.f};
     *reinterpret_cast<f32x4 *>(a.dq + ridx * D + sub * 4) = z;
   }
@@ -460,10 +460,9 @@ __global__ __launch_bounds__(256, (MainShape<TI, D>::OCC)) void bwd_main_kernel(
       pp[(wave * 32 + l32) * 2 + 1] = pm;
     }
   }
-  if (nt > 0) {
-    lds_barrier();
-    flush(nt - 1);
-  }
+  if (nt == 0) return;  // a part without a tile has nothing to add
+  lds_barrier();
+  flush(nt - 1);
   if constexpr (NP == 3) {
     // a dS out of range of the pieces: the wave's dK again on the fp32 MFMA, from
     // the dS tiles it stored
@@ -497,7 +496,7 @@ __global__ __launch_bounds__(256, (MainShape<TI, D>::OCC)) void bwd_main_kernel(
       if (j < T && 32 * c + l32 < D) {
         const size_t e = slice + (size_t)j * D + 32 * c + l32;
         if (a.qsplit > 1) {  // parts of the query range add up (zeroed by bwd_pre)
-          atomicAdd(a.dv + e, dva[c][r]);
+          atomicAdd((a.fold && qpart > 1 ? a.dq : a.dv) + e, dva[c][r]);
           atomicAdd(a.dk + e, a.scale * dka[c][r]);
         } else {
           if (NP == 1 && a.dv16) a.dv16[e] = (uint16_t)(__float_as_uint(bf16_rne(dva[c][r])) >> 16);
@@ -611,6 +610,23 @@ __global__ __launch_bounds__(128 * QG, (DqShape<TI, D>::OCC)) void bwd_dq_kernel
       }
     }
   };
+  if (a.fold) {
+    // the parts of dV that bwd_main left in this workgroup's rows of dq
+    constexpr int PER = 32 * QG * D / 4 / NT;
+    f32x4 x[PER], y[PER];
+    const size_t e0 = (size_t)g * 32 * QG * D;
+#pragma unroll
+    for (int u = 0; u < PER; ++u) {
+      const size_t e = min(e0 + 4 * (tid + u * NT), (size_t)T * D - 4);
+      x[u] = load4(a.dq + slice + e);
+      y[u] = load4(a.dv + slice + e);
+    }
+#pragma unroll
+    for (int u = 0; u < PER; ++u) {
+      const size_t e = e0 + 4 * (tid + u * NT);
+      if (e < (size_t)T * D) *reinterpret_cast<f32x4 *>(a.dv + slice + e) = y[u] + x[u];
+    }
+  }
   fetch_k(0);
   fetch_d(0, dA);
   fetch_d(1, dB);

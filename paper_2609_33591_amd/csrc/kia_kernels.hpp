@@ -89,6 +89,10 @@ template <typename TI> struct BwdArgsT {
   // dq_piece > 0: bwd_dq cuts each query group's 64-key chunks into pieces
   // of at most dq_piece chunks, which add into dq (zeroed by bwd_pre)
   int dq_piece;
+  // 1 (qsplit 3 or 4, dq_piece 0): the third and fourth part add their dV into dq,
+  // which bwd_dq adds to dv before it writes dq. A sum of two does not depend on
+  // their order, so that dV is the same on every call.
+  int fold = 0;
   // 1: every reduction in a fixed order (kia_set_deterministic): row sums
   // through st.part, calibration terms gathered per key, ties one wave per
   // slice; qsplit = 1 and dq_piece = 0

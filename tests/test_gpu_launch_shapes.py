@@ -46,3 +46,29 @@ def test_launch_shapes(oracle_mod, dtype, d, B, H, T, op):
     r = P.run_oracle(oracle_mod, *few, *args)
     (B16.compare16 if dtype == "bf16" else P.compare)(n, r, oracle_mod, calib, [(0, 0), (0, 1)],
                                                       tag=tag)
+
+
+@pytest.mark.parametrize("T", (1024, 1001))
+@pytest.mark.parametrize("d", (16, 128))
+@pytest.mark.parametrize("dtype", (torch.float32, torch.bfloat16))
+def test_dv_repeats_from_one_block_per_cu(dtype, d, T):
+    """From one 128-key block per CU up, dV is bitwise the same on every call, and
+    that of the unsplit launch up to the order of its sums (two fp32 sums of T
+    terms at most: 2 T 2^-24 of the norm)."""
+    B, H = 2, 16  # 256 blocks
+    P.flush(f"case dv repeats {dtype} d{d} T{T}")
+    assert B * H * ((T + 127) // 128) >= \
+        torch.cuda.get_device_properties(0).multi_processor_count
+    q, k, v, dO = (t.to(dtype).cuda() for t in make_inputs(B, H, T, d, seed=77))
+    args = (4, "fwm", 8.0, "lerp", "weight", False, 1)
+    o, st = kia.forward(q, k, v, *args)
+    ref = kia.backward(q, k, v, o, dO, st, *args)
+    for _ in range(4):
+        assert torch.equal(kia.backward(q, k, v, o, dO, st, *args)[2], ref[2])
+    kia.kia_set_grid_policy("wide")
+    try:
+        wide = kia.backward(q, k, v, o, dO, st, *args)
+    finally:
+        kia.kia_set_grid_policy("auto")
+    for a, b, n in zip(ref, wide, ("dq", "dk", "dv")):
+        assert (a - b).norm() <= 2 * T * 2.0 ** -24 * b.norm(), n
