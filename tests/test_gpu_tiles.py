@@ -54,16 +54,25 @@ def test_tile_edges(oracle_mod, dtype, d, policy):
 
 @pytest.mark.parametrize("d", (16, 32, 64, 128))
 def test_tiny_query_rows(d):
-    """Query rows whose elements lie at or below fp32's normal range keep the
-    scores' full precision: q 2^-n against k 2^n gives the same products, and
-    so the same result, bit for bit, as the rows as they were (every factor a
-    power of two; MinMax, so that nothing but the scores sees q and k)."""
+    """Query rows whose elements lie near fp32's smallest normal value keep the
+    scores' full precision: q 2^-n against k 2^n gives the same products, and so
+    the same result, bit for bit, as the rows as they were (every factor a power
+    of two; MinMax, so that nothing but the scores sees q and k). q has full
+    24-bit significands: as three bf16 pieces, whose last one would lie below
+    bf16's smallest value, it would lose bits (checked here)."""
     P.flush(f"case tiny rows d{d}")
-    q, k, v, _ = make_inputs(1, 1, 97, d, seed=31, dyadic=True)
+    q, k, v, _ = make_inputs(1, 1, 97, d, seed=31)
+    q, k = (torch.where(x.abs() < 2.0 ** -5, torch.full_like(x, 2.0 ** -5), x) for x in (q, k))
     args = (4, "minmax", 8.0, "lerp", "weight", False, 1)
     ref, _ = kia.forward(q.cuda(), k.cuda(), v.cuda(), *args)
-    for n in (110, 120):  # the smallest elements: 2^-113, 2^-123
-        o, _ = kia.forward((q * 2.0 ** -n).cuda(), (k * 2.0 ** n).cuda(), v.cuda(), *args)
+    for n in (110, 120):  # the smallest elements: 2^-115, 2^-125
+        x = q * 2.0 ** -n
+        assert torch.equal(x * 2.0 ** n, q)
+        left = x.double()
+        for _ in range(3):
+            left = left - left.to(torch.bfloat16).double()
+        assert (left != 0).any()
+        o, _ = kia.forward(x.cuda(), (k * 2.0 ** n).cuda(), v.cuda(), *args)
         torch.cuda.synchronize()
         assert np.array_equal(o.cpu().numpy(), ref.cpu().numpy()), n
 
