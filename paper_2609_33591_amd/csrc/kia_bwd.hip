@@ -21,7 +21,9 @@
 //               and cm = -(S_self + cM) (from Delta + dw/dM + dw/dm = 0) on
 //               the argmin key; FWM has cM = -S_self. For rows with unique
 //               extrema it also scatter-adds dK_amax += scale cM q_i and
-//               dK_amin += scale cm q_i.
+//               dK_amin += scale cm q_i. (Where the main kernel's query range is
+//               in three or four parts, it first adds their dV up, see
+//               BwdArgsT::fold.)
 //  4. bwd_ties  (full gradient only) rows with tied extrema: recompute the
 //               row's scores with the canonical sub-tile and split cM / cm
 //               evenly over every key equal to M / m (edge-case table).
@@ -124,7 +126,7 @@ __global__ __launch_bounds__(256) void bwd_pre_kernel(BwdArgsT<TI> a) {
 //   through a wave-private LDS tile as bf16 pieces, written by rows of 4 keys
 //   and read back transposed, as the A operands of dV += P^T dO and
 //   dK += dS^T Q.
-// Three products of 24 (d = 64, fp32) MFMAs each, about 700 VALU operations
+// Three products of 24 (d = 64, fp32) MFMAs each, about 750 VALU operations
 // and 60 KiB of LDS traffic per 32x32 tile: no single unit bounds it, so two
 // workgroups per CU (256 registers a wave) run out of phase; fp32 at d = 128
 // needs 512.
@@ -398,9 +400,10 @@ __global__ __launch_bounds__(256, (MainShape<TI, D>::OCC)) void bwd_main_kernel(
       }
     }
     const int tb2 = tr_base<D>(lane);
-    // (one piece: dS takes P's place in LDS before the first product, whose
-    // MFMAs its reads then run under: B4 H16 T2048 d128 350 -> 335 us; with
-    // three pieces the 24 more registers cost more than that)
+    // (one piece: dS takes P's place in LDS before the first product, whose MFMAs
+    // its reads then run under; B4 H16 T2048 d128 backward, this order / the other:
+    // FWM Nearest 395 / 396 us, MinMax LERP 529 / 519, MinMax Nearest 682 / 690.
+    // With three pieces the 24 more registers cost more than that)
     bf16x8 x[2][NP], xd[2][NP];
     if constexpr (EXACT) {
       product32(P, dos, i0, dva);

@@ -45,8 +45,8 @@ __global__ __launch_bounds__(256) void codes_kernel(CodesArgsT<TI> a) {
         for (int r = 0; r < 16; ++r) code[r] = 0;
       } else {
         ScoreOp<TI, D> kop;
-        kop.load(a.k + slice, js + l32, T, half);
-        const f32x16 acc = ScoreOp<TI, D>::tile(kop, qop);
+      kop.load(a.k + slice, js + l32, T, half);
+      const f32x16 acc = ScoreOp<TI, D>::tile(kop, qop);
         if constexpr (EXPW) {
           // bit 15 valid; bits 0-14 the bf16 pattern (BF16-exp) or the E4M3
           // byte (FP8-exp) of the weight, 0 for softmax (w <= 1: bit 14 clear)

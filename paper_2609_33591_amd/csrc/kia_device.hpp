@@ -23,12 +23,12 @@
 // for bf16 inputs, with the key block and the query block aligned to multiples
 // of 32. The A operand is K (rows = keys), the B operand Q (columns = queries).
 // Lane l (half h = l/32) feeds, at k-step s, K[key0 + l%32][h d/2 + s] and the
-// same of Q (bf16: [16 s + 8 h + e], e = 0..7). Output register r of lane l holds S^T[key0 + krel(r, h)]
-// [query0 + l%32] with krel(r, h) = 8*(r/4) + 4*h + r%4. Same operands, same
-// instruction sequence, same lane/register position: the fp32 score of a pair
-// is bit-identical wherever it is computed (both passes of the forward, the
-// tie path and the debug exports), which the exact extremum ties and index
-// decisions rely on.
+// same of Q (bf16: [16 s + 8 h + e], e = 0..7). Output register r of lane l holds
+// S^T[key0 + krel(r, h)][query0 + l%32] with krel(r, h) = 8*(r/4) + 4*h + r%4.
+// Same operands, same instruction sequence, same lane/register position: the fp32
+// score of a pair is bit-identical wherever it is computed (both passes of the
+// forward, the tie path and the debug exports), which the exact extremum ties and
+// index decisions rely on.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -70,7 +70,7 @@ struct Stats {
   float *sself, *cM;
   float *OL;      // [R][d] or nullptr
   float *dS;      // backward scratch: dS in 32x32 tiles, 1024 floats each
-  float *U;       // forward -> backward: raw scores, then decided u, same tiles
+  float *U;       // fp32 scores between the forward's passes, then its decisions, same tiles
   float *part;    // deterministic backward: row-sum partials [2][ceil(T/128)][R],
                   // then the calibration records [R][4] of the dK gather
 };
@@ -529,7 +529,6 @@ __device__ __forceinline__ void tile_store(float *tile, int lane, const float (&
   }
 }
 
-// ---- buffer loads of row blocks ---------------------------------------------
 // ---- gradient modes (the backward's `detach` argument) ---------------------
 // 0 full (Eq. full), 1 detach, 2 max_only / 3 min_only (one extremum
 // channel; appendix on the detached-gradient record), 4 detach with the P1
