@@ -212,12 +212,12 @@ void launch_fwd_k(const FwdArgsT<TI> &a, hipStream_t s) {
 //                 512 - / 346 / 273 / 255
 //   bf16 d = 64   96 blocks - / 26 / 40 / 66, 320 - / 48 / 44 / 69, 768 - / 92 / 78 / 78
 //   bf16 d = 128  96 blocks - / 45 / 61 / 86, 192 - / 72 / 61 / 88, 768 - / 270 / 140 / 111
-// Up to three blocks per CU 4 x 1 leaves its second round half empty. fp32 at
-// d = 16 takes it from two up all the same where a backward follows: it leaves the
-// scores out of U, which between two kernels does not stay in cache (a step at 768
-// blocks 306 / 304 / 299 for the last three, the forward alone 100 / 100 / 106).
-// One 1 x 4 workgroup fills a CU's LDS with fp32 V or with O and O_l sums at
-// d = 128 (`alone`). Eight parts need more than four key tiles.
+// Up to three blocks per CU 4 x 1 leaves its second round half empty. One 1 x 4
+// workgroup fills a CU's LDS with fp32 V or with O and O_l sums at d = 128
+// (`alone`); without O_l bf16 Nearest would gain from it up to one block per CU (192
+// blocks 40 / 48), but the shape sets the order of the sums, and surrogate and
+// gradient mode leave the forward's bits as they are: the rule looks at neither.
+// Eight parts need more than four key tiles.
 template <typename TI, int D, int CALIB>
 void launch_fwd_c(const FwdArgsT<TI> &a, hipStream_t s) {
   constexpr bool F32 = sizeof(TI) == 4;
@@ -227,10 +227,11 @@ void launch_fwd_c(const FwdArgsT<TI> &a, hipStream_t s) {
     if (split || (autog && blocks <= cus / 2 && a.T > 128))
       return launch_fwd_k<TI, D, CALIB, 1, 8>(a, s);
   }
-  const bool alone = a.st.OL ? FwdShape<TI, D, REC_NEAREST, true, 1, 4>::OCC == 1
-                             : FwdShape<TI, D, REC_LERP, false, 1, 4>::OCC == 1;
+  const bool alone = a.recon == KIA_RECON_NEAREST
+                         ? FwdShape<TI, D, REC_NEAREST, true, 1, 4>::OCC == 1
+                         : FwdShape<TI, D, REC_LERP, false, 1, 4>::OCC == 1;
   const long most14 = alone ? cus / 2 : F32 && D == 16 ? 2 * cus : cus;
-  const long most22 = D == 128 || (F32 && D == 16 && a.keep) ? 2 * cus : 3 * cus;
+  const long most22 = D == 128 ? 2 * cus : 3 * cus;
   if (split || (autog && blocks <= most14)) return launch_fwd_k<TI, D, CALIB, 1, 4>(a, s);
   if (autog && blocks <= most22) return launch_fwd_k<TI, D, CALIB, 2, 2>(a, s);
   launch_fwd_k<TI, D, CALIB, 4, 1>(a, s);

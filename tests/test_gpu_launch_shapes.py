@@ -48,6 +48,22 @@ def test_launch_shapes(oracle_mod, dtype, d, B, H, T, op):
                                                       tag=tag)
 
 
+@pytest.mark.parametrize("recon", ("nearest", "lerp"))
+@pytest.mark.parametrize("B,H,T", GRIDS)
+@pytest.mark.parametrize("d", (16, 32, 64, 128))
+@pytest.mark.parametrize("dtype", (torch.float32, torch.bfloat16))
+def test_forward_bits_at_every_launch_shape(dtype, d, B, H, T, recon):
+    """The forward is bitwise independent of the surrogate and of the gradient mode
+    (the forward-only mode among them), and so is its launch shape."""
+    P.flush(f"case forward bits {dtype} B{B} H{H} T{T} d{d} {recon}")
+    q, k, v, _ = (t.to(dtype).cuda() for t in make_inputs(B, H, T, d, seed=1100 + T))
+    for calib in ("fwm", "minmax"):
+        ref = kia.forward(q, k, v, 4, calib, 8.0, recon, "prob", False, 1)[0]
+        for ste, mode in (("weight", False), ("prob", "none"), ("weight", "none")):
+            o = kia.forward(q, k, v, 4, calib, 8.0, recon, ste, mode, 1)[0]
+            assert torch.equal(o, ref), (calib, ste, mode)
+
+
 @pytest.mark.parametrize("T", (1024, 1001))
 @pytest.mark.parametrize("d", (16, 128))
 @pytest.mark.parametrize("dtype", (torch.float32, torch.bfloat16))
