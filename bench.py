@@ -350,6 +350,9 @@ def main():
     }
     if not b16:
         roof["mfma_probe"] = mfma_probe(kia, torch, stream)
+        # fp32 scores run on the unit whose peak this is; the other products of fp32
+        # operands run as six bf16 piece products each, which it does not bound
+        roof["peak_is"] = "fp32 MFMA; only the scores run there, the rest as bf16 pieces"
     if args.probe:
         # two passes of score sub-tiles per (query, key) pair plus the
         # per-key statistics; counted as 2 GEMM units (Q K^T twice)
