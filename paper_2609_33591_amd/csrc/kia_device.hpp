@@ -629,29 +629,27 @@ template <int NP> __device__ __forceinline__ void to_pieces(const float (&x)[8],
 // do. Below, the last piece comes near bf16's smallest value; above, the first
 // one rounds to infinity, and an infinity or NaN spreads to the value that it is
 // split with. A product with such an operand is taken on the fp32 MFMA instead,
-// with its rows read from memory. 12 operations per eight values.
+// with its rows read from memory. 16 operations per eight values. (The values
+// themselves and not their first pieces: below 2^-134 that piece is 0.)
 constexpr float PIECE_LO = 0x1p-100f, PIECE_HI = 0x1p126f;
 __device__ __forceinline__ bool out_of_pieces(float x) {
   return !(fabsf(x) < PIECE_HI) | ((fabsf(x) < PIECE_LO) & (x != 0.f));
 }
 struct PieceCheck {
-  typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
-  u16x2 lo = {0xffff, 0xffff};  // least of 2 |bits of the first piece| - 1 (0: the most)
-  float hi = 0.f;               // largest magnitude, NaN if there is one
-  __device__ __forceinline__ void add(const float (&x)[8], u32x4 p0) {
+  uint32_t lo = 0xffffffffu;  // least of 2 |bits| - 1 (0: the most)
+  float hi = 0.f;             // largest magnitude, NaN if there is one
+  __device__ __forceinline__ void add(const float (&x)[8]) {
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const uint32_t word = p0[e];
-      const u16x2 w = __builtin_bit_cast(u16x2, word);
-      lo = __builtin_elementwise_min(lo, w * u16x2{2, 2} - u16x2{1, 1});
-      hi = __builtin_elementwise_maximum(
-          __builtin_elementwise_maximum(fabsf(x[2 * e]), fabsf(x[2 * e + 1])), hi);
+    for (int e = 0; e < 8; e += 2) {
+      const float a = x[e], b = x[e + 1];
+      lo = min(min(2u * __float_as_uint(a) - 1u, 2u * __float_as_uint(b) - 1u), lo);
+      hi = __builtin_elementwise_maximum(__builtin_elementwise_maximum(fabsf(a), fabsf(b)), hi);
     }
-    asm volatile("" : "+v"(lo), "+v"(hi));  // (now, or x and p0 stay live until bad())
+    asm volatile("" : "+v"(lo), "+v"(hi));  // (now, or x stays live until bad())
   }
   __device__ __forceinline__ bool bad() const {
-    constexpr unsigned short least = 2 * ((127 - 100) << 7) - 1;
-    return (lo[0] < least) | (lo[1] < least) | !(hi < PIECE_HI);
+    constexpr uint32_t least = 2u * ((uint32_t)(127 - 100) << 23) - 1u;
+    return (lo < least) | !(hi < PIECE_HI);
   }
 };
 // Computed operands (score gradients) have a range of their own in every row: the
@@ -731,7 +729,7 @@ __device__ __forceinline__ bool load_rows(const TI *slice, int row, int T, int h
       }
       bf16x8 p[3];
       to_pieces<3>(x, p);
-      check.add(x, __builtin_bit_cast(u32x4, p[0]));
+      check.add(x);
 #pragma unroll
       for (int i = 0; i < 3; ++i) op[i][s] = p[i];
     } else {
@@ -825,7 +823,7 @@ template <int D, int ROWS, int NT, typename TI> struct Stage {
         for (int i = 0; i < 8; ++i) f[i] = __uint_as_float(x[e][i / 4][i % 4]);
         u32x4 p[3];
         split8(f, p);
-        if (check) check->add(f, p[0]);
+        if (check) check->add(f);
 #pragma unroll
         for (int i = 0; i < 3; ++i) *reinterpret_cast<u32x4 *>(d + i * PS) = p[i];
       } else {

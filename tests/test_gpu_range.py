@@ -60,6 +60,38 @@ def test_powers_of_two(d, which, policy):
         kia.kia_set_grid_policy("auto")
 
 
+@pytest.mark.parametrize("policy", ("auto", "wide"))
+@pytest.mark.parametrize("which", ("v", "dO", "k"))
+@pytest.mark.parametrize("d", (16, 32, 64, 128))
+def test_values_below_the_smallest_piece(d, which, policy):
+    """Operands that are denormal throughout, below half of bf16's smallest value: no
+    piece holds any of them. They have six bits (exact at 2^-138 2^-3), results are
+    sums of at most T terms rounded to fp32's smallest step: T 2^-149, and TOL of
+    the result."""
+    kia.kia_set_grid_policy(policy)
+    try:
+        for op in OPS:
+            print(f"case denormal d{d} {which} {policy} {op}", flush=True)
+            q, k, v, dO = ((x * 8).round() / 8 for x in inputs(d, 70 + d))
+            if which == "k":  # scores of 2^-18: q 2^120, k 2^-138
+                dO = dO * 2.0 ** 10
+                ref = call(q * 2.0 ** -18, k, v, dO, op)
+                got = call(q * 2.0 ** 120, k * 2.0 ** -138, v, dO, op)
+                names = ("dq",)
+            else:
+                ref = call(q, k, v, dO, op)
+                got = call(q, k, *((v * 2.0 ** -138, dO) if which == "v" else
+                                   (v, dO * 2.0 ** -138)), op)
+                names = ("o", "dq", "dk") if which == "v" else ("dv", "dq", "dk")
+            for n in names:
+                y = ref[n] * 2.0 ** -138
+                err = (got[n] - y).abs().max().item()
+                assert y.abs().max().item() > 3 * T * 2.0 ** -149
+                assert err <= T * 2.0 ** -149 + TOL * y.abs().max().item(), (op, n, err)
+    finally:
+        kia.kia_set_grid_policy("auto")
+
+
 @pytest.mark.parametrize("d", (16, 64, 128))
 def test_one_value_that_rounds_to_infinity_in_bf16(d):
     """A finite v above bf16's largest value takes part as what it is."""
