@@ -28,11 +28,11 @@
  *   - The other products of fp32 operands are formed from three bf16 pieces
  *     each (an exact sum) with fp32 accumulation; their error is below that
  *     of an fp32 product. Where v, dO, q or k hold values that the pieces do
- *     not (non-zero below 2^-100, 2^126 and above, infinite, NaN), or a row's
- *     score gradients leave that range as a whole, the products they enter
- *     are taken as fp32 products, as exact and slower. Weights below 2^-100
- *     of the row's largest keep 2^-134 of it, less than the smallest weight
- *     there is (2^-126; below, a weight is 0).
+ *     not (non-zero below 2^-100, 2^126 and above, infinite, NaN), or the score
+ *     gradients of 32 keys or 32 queries leave that range as a whole, the
+ *     products they enter are taken as fp32 products, as exact and slower.
+ *     Weights and score gradients below 2^-100 beside larger ones keep 2^-134
+ *     (the smallest weight is 2^-126; below, a weight is 0).
  *   - Determinism: the forward is bitwise repeatable. By default the
  *     backward is not: the row sums of every key block's score gradients
  *     (S_self, and cM under MinMax) are accumulated with float atomics, and

@@ -275,7 +275,7 @@ __global__ __launch_bounds__(256, (MainShape<TI, D>::OCC)) void bwd_main_kernel(
     __builtin_amdgcn_wave_barrier();
   };
 
-  bool dsout = false;  // some dS of this lane is out of range of the pieces
+  GradRange dsr;  // of the dS that went into dK by pieces
   // one 32-query tile (EXACT: its products on the fp32 MFMA)
   auto tile_as = [&](int i0, const uint16_t *Qb, const uint16_t *dOb, float &ps, float &pm,
                      auto tag) {
@@ -426,7 +426,7 @@ __global__ __launch_bounds__(256, (MainShape<TI, D>::OCC)) void bwd_main_kernel(
       get_op(0, x[0]);
       get_op(1, x[1]);
       product(x, Qb + tb2, dka);
-      dsout = dsout | row_out_of_pieces(dS);
+      dsr.add(dS);
     }
   };
 
@@ -467,9 +467,9 @@ __global__ __launch_bounds__(256, (MainShape<TI, D>::OCC)) void bwd_main_kernel(
   lds_barrier();
   flush(nt - 1);
   if constexpr (NP == 3) {
-    // a dS out of range of the pieces: the wave's dK again on the fp32 MFMA, from
-    // the dS tiles it stored
-    if (__any(dsout)) {
+    // dS out of range of the pieces: the wave's dK again on the fp32 MFMA, from the
+    // dS tiles it stored
+    if (dsr.out()) {
       __threadfence();
 #pragma unroll
       for (int c = 0; c < NC; ++c)
@@ -585,13 +585,13 @@ __global__ __launch_bounds__(128 * QG, (DqShape<TI, D>::OCC)) void bwd_dq_kernel
   };
   const uint16_t *kb = Ks + kh * 32 * RS + tr_base<D>(lane);
   PieceCheck check;  // of the K values that this thread staged
-  bool dout = false;  // some dS tile of this lane is out of range of the pieces
+  GradRange dsr;  // of this wave's dS
   auto mma_step = [&](const u32x4 (&dx)[ND]) {
     if constexpr (NP == 3) {
       float x[16];
 #pragma unroll
       for (int r = 0; r < 16; ++r) x[r] = __uint_as_float(dx[r / 4][r % 4]);
-      dout = dout | row_out_of_pieces(x);
+      dsr.add(x);
     }
 #pragma unroll
     for (int t = 0; t < 2; ++t) {
@@ -679,9 +679,10 @@ __global__ __launch_bounds__(128 * QG, (DqShape<TI, D>::OCC)) void bwd_dq_kernel
   // key half 1 hands its partial sums to key half 0
   __syncthreads();
   if constexpr (NP == 3) {
-    // a value out of range of the pieces in the K chunks or in this wave's dS:
-    // the wave's product again on the fp32 MFMA, its operands from memory
-    if (any_flag<2 * QG>(Bad) || __any(dout)) {
+    // values out of range of the pieces in the K chunks or in this wave's dS, or a
+    // row of dO or q that is marked (its own dS may be): the wave's product again
+    // on the fp32 MFMA, its operands from memory
+    if (any_flag<2 * QG>(Bad) || dsr.out() || __any(signbit(rflag))) {
 #pragma unroll
       for (int c = 0; c < NC; ++c)
 #pragma unroll

@@ -652,18 +652,26 @@ struct PieceCheck {
     return (lo < least) | !(hi < PIECE_HI);
   }
 };
-// Computed operands (score gradients) have a range of their own in every row: the
-// lane's 16 values of one row are out of range by their largest. What the others
-// then lose is 2^-33 of it at most.
-__device__ __forceinline__ bool row_out_of_pieces(const float (&x)[16]) {
-  float m = 0.f;
+// Score gradients are computed operands, spread over many orders of size in every
+// call with wide scores, and a sum of them is as exact as its largest term: a wave's
+// are out of range by the largest of all it has seen (what smaller ones then lose is
+// 2^-34 of PIECE_LO each). By the largest of each lane's 16 in a tile half of the
+// waves took the fp32 MFMA at a score span of 100 (q, k ~ 4 N(0,1) at d = 64,
+// bwd_main 160 -> 360 us).
+struct GradRange {
+  float m = 0.f;  // largest magnitude, NaN if there is one
+  __device__ __forceinline__ void add(const float (&x)[16]) {
 #pragma unroll
-  for (int r = 0; r < 16; r += 2)
-    m = __builtin_elementwise_maximum(
-        __builtin_elementwise_maximum(fabsf(x[r]), fabsf(x[r + 1])), m);
-  asm volatile("" : "+v"(m));  // (now, or x stays live until the answer is used)
-  return !(m < PIECE_HI) | ((m < PIECE_LO) & (m > 0.f));
-}
+    for (int r = 0; r < 16; r += 2)
+      m = __builtin_elementwise_maximum(
+          __builtin_elementwise_maximum(fabsf(x[r]), fabsf(x[r + 1])), m);
+    asm volatile("" : "+v"(m));  // (now, or x stays live until the answer is used)
+  }
+  // of the whole wave
+  __device__ __forceinline__ bool out() const {
+    return __any(!(m < PIECE_HI)) || (__any(m > 0.f) && !__any(m >= PIECE_LO));
+  }
+};
 
 // c += a b over one 16-term k-step, all its piece products.
 template <int NP>

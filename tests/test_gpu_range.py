@@ -93,6 +93,19 @@ def test_values_below_the_smallest_piece(d, which, policy):
 
 
 @pytest.mark.parametrize("d", (16, 64, 128))
+def test_one_tiny_row_of_dO(d):
+    """A row of dO far below the others keeps its own row of dQ to fp32 rounding."""
+    for op in OPS:
+        print(f"case tiny row d{d} {op}", flush=True)
+        q, k, v, dO = inputs(d, 80 + d)
+        ref = call(q, k, v, dO, op)
+        dO[:, :, 60] *= 2.0 ** -115
+        got = call(q, k, v, dO, op)
+        y = ref["dq"][:, :, 60] * 2.0 ** -115
+        assert ((got["dq"][:, :, 60] - y).norm() / y.norm()).item() <= TOL, op
+
+
+@pytest.mark.parametrize("d", (16, 64, 128))
 def test_one_value_that_rounds_to_infinity_in_bf16(d):
     """A finite v above bf16's largest value takes part as what it is."""
     print(f"case near the largest d{d}", flush=True)
