@@ -126,7 +126,7 @@ __global__ __launch_bounds__(256) void bwd_pre_kernel(BwdArgsT<TI> a) {
 //   through a wave-private LDS tile as bf16 pieces, written by rows of 4 keys
 //   and read back transposed, as the A operands of dV += P^T dO and
 //   dK += dS^T Q.
-// Three products of 24 (d = 64, fp32) MFMAs each, about 580 VALU instructions
+// Three products of 24 (d = 64, fp32) MFMAs each, about 570 VALU instructions
 // and 60 KiB of LDS traffic per 32x32 tile: no single unit bounds it, so two
 // workgroups per CU (256 registers a wave) run out of phase; fp32 at d = 128
 // needs 512.
